@@ -58,84 +58,95 @@ __device__ unsigned long long g_phase_times[1024][8];
 
 
 
+// Inclusive prefix sum over the 512 threads of a workgroup; wsum: eight words of LDS that nobody else uses.
+__device__ __forceinline__ int scan512(int v, int* wsum) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(v, d, 64);
+        if (lane >= d) v += o;
+    }
+    if (lane == 63) wsum[wave] = v;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 7; w++)
+        if (w < wave) v += wsum[w];
+    return v;
+}
+
+// Size class of a row count, larger counts in later classes: steps of 16 rows below 2048, a sixteenth of a
+// power of two above.
+constexpr int kSizeClasses = 512;
+__device__ __forceinline__ int size_class(int rows) {
+    if (rows < 2048) return rows >> 4;
+    const int e = 31 - __clz(rows);
+    return 128 + (e - 11) * 16 + ((rows >> (e - 4)) & 15);
+}
+
+// Tile table of one launch sequence, by one workgroup: its time is a chain of LDS latencies, so there is
+// nothing in it that grows with E.  Experts are ordered by size class with a counting sort (two 512-wide
+// scans); comparing every pair of row counts instead, as an exact sort by rank, cost 2 x 512 LDS reads per
+// wavefront and took 24 us at E = 512 and 16 us at E = 192 (now 5.2 and 5.4, of which 4 are the launch).  The order of experts of one class
+// follows the arrival of LDS atomics: it decides where a tile runs, never what it computes.
 __global__ __launch_bounds__(512) void build_tiles_kernel(const int32_t* __restrict__ offsets, int E,
                                                           int total_rows, int BM, int pad_even,
                                                           int32_t* __restrict__ meta, int32_t* __restrict__ pair_cnt) {
-    if (pair_cnt != nullptr)
-        for (int i = threadIdx.x; i < kPairCap; i += 512) pair_cnt[i] = 0;
-    __shared__ __attribute__((aligned(16))) int lrows[512];   // rows per expert (0 past E)
-    __shared__ __attribute__((aligned(16))) int lkey[512];    // place of an expert in the dealt order
+    __shared__ int hist[kSizeClasses];    // experts per class, then the next free rank of the class
     __shared__ int ltiles[512];           // tiles of the expert at a given place
-    __shared__ int scan[2][512];
+    __shared__ int wsum[2][8];
     const int t = threadIdx.x;
     int r0 = 0, r1 = 0;
     if (t < E) {
         r0 = offsets ? offsets[t] : 0;
         r1 = offsets ? offsets[t + 1] : total_rows;
     }
-    const int nt = (r1 - r0 + BM - 1) / BM;
+    hist[t] = 0;
+    ltiles[t] = 0;
+    if (pair_cnt != nullptr)
+        for (int i = t; i < kPairCap / 4; i += 512) reinterpret_cast<int4*>(pair_cnt)[i] = make_int4(0, 0, 0, 0);
+    const int rt = r1 - r0;
+    const int nt = (rt + BM - 1) / BM;
     // Every expert takes an even number of places in the list (the odd one out is an entry without
     // rows, which the workgroups skip): the kernels hand out the list in pairs of row tiles that run
     // side by side and share the weight tile through L2, and a pair must not straddle two experts.
     const int ns = pad_even ? (nt + 1) & ~1 : nt;
-    lrows[t] = r1 - r0;
+    __syncthreads();
+    const int cls = kSizeClasses - 1 - size_class(rt);          // descending sizes
+    if (t < E) atomicAdd(&hist[cls], 1);
+    __syncthreads();
+    const int h = hist[t];
+    const int upto = scan512(h, wsum[0]);
+    hist[t] = upto - h;                   // a class's first rank
     __syncthreads();
     // Order of the experts in the tile list.  The persistent workgroups walk the list in a fixed
     // pattern (one eighth of it per XCD, dealt in rounds to the workgroups of the XCD), so the list
-    // is laid out for them: experts sorted by rows, descending, are dealt to the eight parts in
+    // is laid out for them: experts sorted by size, descending, are dealt to the eight parts in
     // serpentine order (0..7, 7..0, ...), which gives every XCD the same amount of work to within
     // one small expert and makes the tiles that run at the same time equally long.
-    // (entries past E hold no rows and take no part; the loops read four experts per LDS access)
-    const int E4 = (E + 3) / 4;
-    const int rt = r1 - r0;
-    int rank = 0;                         // experts with more rows (ties: lower index first)
-    for (int o4 = 0; o4 < E4; o4++) {
-        const int4 v = reinterpret_cast<const int4*>(lrows)[o4];
-        const int o = 4 * o4;
-        rank += (v.x > rt) || (v.x == rt && o < t);
-        rank += (v.y > rt) || (v.y == rt && o + 1 < t);
-        rank += (v.z > rt) || (v.z == rt && o + 2 < t);
-        rank += (v.w > rt) || (v.w == rt && o + 3 < t);
-    }
-    const int lap = rank / kNumXcd, posn = rank % kNumXcd;
-    const int part = (lap & 1) ? kNumXcd - 1 - posn : posn;
-    const int place = t < E ? part * (512 / kNumXcd) + lap : 0x7fffffff;     // unique below E: lap < 64
-    lkey[t] = place;
-    ltiles[t] = 0;
-    __syncthreads();
-    int dense = 0;                        // experts placed before this one
-    for (int o4 = 0; o4 < E4; o4++) {
-        const int4 v = reinterpret_cast<const int4*>(lkey)[o4];
-        dense += (v.x < place) + (v.y < place) + (v.z < place) + (v.w < place);
+    int dense = 0;                        // place of the expert: experts of the parts before its own, then its lap
+    if (t < E) {
+        const int rank = atomicAdd(&hist[cls], 1);
+        const int lap = rank / kNumXcd, posn = rank % kNumXcd;
+        const int part = (lap & 1) ? kNumXcd - 1 - posn : posn;
+        // the last lap is short: its experts sit in the first parts, or in the last ones if it runs backwards
+        const int laps = E / kNumXcd, left = E % kNumXcd;
+        dense = part * laps + ((laps & 1) ? max(0, part - (kNumXcd - left)) : min(part, left)) + lap;
+        ltiles[dense] = ns;
     }
     __syncthreads();
-    if (t < E) ltiles[dense] = ns;
-    __syncthreads();
-    // exclusive prefix sum of the tiles in list order (inclusive Hillis-Steele scan over 512 entries)
     const int mine = ltiles[t];
-    scan[0][t] = mine;
-    __syncthreads();
-    int cur = 0;
-    for (int d = 1; d < 512; d <<= 1) {
-        scan[cur ^ 1][t] = scan[cur][t] + (t >= d ? scan[cur][t - d] : 0);
-        cur ^= 1;
-        __syncthreads();
-    }
-    ltiles[t] = scan[cur][t] - mine;      // first tile of the expert at place t
-    if (t == 0) meta[0] = scan[cur][511];
+    const int end = scan512(mine, wsum[1]);
+    ltiles[t] = end - mine;               // first tile of the expert at place t
+    if (t == 511) meta[0] = end;
     __syncthreads();
     // The rows of an expert are cut into equal tiles (multiples of 16 rows, the MFMA's row count)
     // rather than into full tiles plus a remainder: tiles that share an expert's weights then take
     // equally long and stay in step, so the second reader of a weight tile still finds it in L2.
     if (t < E) {
-        const int my_first = ltiles[dense];
-        const int per = nt > 0 ? (((r1 - r0 + nt - 1) / nt + 15) / 16) * 16 : 0;
-        for (int i = 0; i < ns; i++) {
-            int32_t* m = meta + kTileBase + 4 * (my_first + i);
-            m[0] = t;
-            m[1] = r0 + i * per;
-            m[2] = max(0, min(per, r1 - (r0 + i * per)));
-        }
+        const int per = nt > 0 ? (((rt + nt - 1) / nt + 15) / 16) * 16 : 0;
+        int4* m = reinterpret_cast<int4*>(meta + kTileBase) + ltiles[dense];
+        for (int i = 0; i < ns; i++)
+            m[i] = make_int4(t, r0 + i * per, max(0, min(per, r1 - (r0 + i * per))), 0);
     }
 }
 
