@@ -16,25 +16,17 @@ size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 size_t align_up_256(size_t v) { return (v + 255) & ~(size_t)255; }
 namespace {
 
-// Debugging builds (-DUNIPOOL_DEBUG_SWITCHES) read two switches from the environment; a regular build has
-// none and keeps no state.  UNIPOOL_FORCE_NAIVE=1 sends bfloat16 contractions to the plain
-// one-thread-per-element kernels; UNIPOOL_UNFUSED_ROUTER=1 keeps the logits GEMM and the selection in
-// separate kernels.
+// Debugging builds (-DUNIPOOL_DEBUG_SWITCHES) read a switch from the environment; a regular build has none
+// and keeps no state.  UNIPOOL_UNFUSED_ROUTER=1 keeps the logits GEMM and the selection in separate kernels.
 #ifdef UNIPOOL_DEBUG_SWITCHES
-bool env_switch(const char* name) {
-    const char* e = getenv(name);
-    return e && e[0] == '1';
-}
-bool force_naive() {
-    static const bool v = env_switch("UNIPOOL_FORCE_NAIVE");
-    return v;
-}
 bool unfused_router() {
-    static const bool v = env_switch("UNIPOOL_UNFUSED_ROUTER");
+    static const bool v = [] {
+        const char* e = getenv("UNIPOOL_UNFUSED_ROUTER");
+        return e && e[0] == '1';
+    }();
     return v;
 }
 #else
-constexpr bool force_naive() { return false; }
 constexpr bool unfused_router() { return false; }
 #endif
 
@@ -181,7 +173,7 @@ int unipool_route(const unipool_shape* shape, const void* x, const void* w_route
     hipStream_t st = (hipStream_t)stream;
     float* z = logits ? logits : (float*)(base + w.dz);
     hipError_t e;
-    if (router_fused_supported(*shape) && !force_naive() && !unfused_router()) {
+    if (router_fused_supported(*shape) && !unfused_router()) {
         // logits, scores, top-k and block statistics in one kernel; then the sum over the blocks
         int32_t* cnt_part = (int32_t*)(base + w.dsigma_part);
         float* psum_part = (float*)(base + w.psum_part);
@@ -190,10 +182,10 @@ int unipool_route(const unipool_shape* shape, const void* x, const void* w_route
         return check_hip(launch_route_finalize(*shape, cnt_part, psum_part, counts, psum, st),
                          "unipool_route: statistics");
     }
-    if (mfma_router_supported(*shape) && !force_naive())
+    if (mfma_router_supported(*shape))
         e = mfma_logits(*shape, x, w_router, z, (int32_t*)(base + w.tile_meta), st);
     else
-        e = naive_logits(*shape, x, w_router, z, st);
+        e = f32_logits(*shape, x, w_router, z, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route: logits");
     e = launch_route_score_topk(*shape, z, topk_idx, topk_gate, counts, psum,
                                 (int32_t*)(base + w.dsigma_part), (float*)(base + w.psum_part), st);
@@ -215,10 +207,12 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz,
                                        (float*)(base + w.dsigma_part), d_sigma, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route_bwd: dz");
-    if (mfma_router_supported(*shape) && !force_naive()) {
+    if (mfma_router_supported(*shape)) {
         e = mfma_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate,
                               (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart),
                               base + w.zeros, st);
+    } else if (shape->dtype == UNIPOOL_F32) {
+        e = f32_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, (float*)(base + w.wpart), st);
     } else {
         e = naive_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, st);
     }
@@ -252,11 +246,11 @@ int unipool_expert_ffn_fwd(const unipool_shape* shape, const void* x_perm,
     const WsLayout w = ws_layout(*shape);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape) && !force_naive())
+    if (mfma_ffn_supported(*shape))
         e = mfma_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h,
                          y_perm, (int32_t*)((char*)ws + w.tile_meta), st);
     else
-        e = naive_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h,
+        e = f32_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h,
                           y_perm, st);
     return check_hip(e, "unipool_expert_ffn_fwd");
 }
@@ -272,11 +266,11 @@ int unipool_expert_ffn_fwd_gather(const unipool_shape* shape, const void* x, con
     const WsLayout w = ws_layout(*shape);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape) && !force_naive())
+    if (mfma_ffn_supported(*shape))
         e = mfma_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm,
                          (int32_t*)((char*)ws + w.tile_meta), st, slot_of_row);
     else
-        e = naive_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st,
+        e = f32_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st,
                           slot_of_row);
     return check_hip(e, "unipool_expert_ffn_fwd_gather");
 }
@@ -292,11 +286,11 @@ int unipool_expert_ffn_recompute(const unipool_shape* shape, const void* x_perm,
     const WsLayout w = ws_layout(*shape);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape) && !force_naive())
+    if (mfma_ffn_supported(*shape))
         e = mfma_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h,
                              (int32_t*)((char*)ws + w.tile_meta), st);
     else
-        e = naive_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h, st);
+        e = f32_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h, st);
     return check_hip(e, "unipool_expert_ffn_recompute");
 }
 
@@ -316,13 +310,13 @@ int unipool_expert_ffn_bwd(const unipool_shape* shape, const void* dy_perm, cons
     const WsLayout w = ws_layout(*shape);
     char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
-    const bool mfma = mfma_ffn_supported(*shape) && !force_naive();
+    const bool mfma = mfma_ffn_supported(*shape);
     hipError_t e;
     if (mfma)
         e = mfma_ffn_dgrad(*shape, dy_perm, act_a, act_b, expert_offsets, w_gate_up, w_down, dx_perm,
                            d_act, (int32_t*)(base + w.tile_meta), st);
     else
-        e = naive_ffn_dgrad(*shape, dy_perm, act_a, act_b, expert_offsets, w_gate_up, w_down, dx_perm,
+        e = f32_ffn_dgrad(*shape, dy_perm, act_a, act_b, expert_offsets, w_gate_up, w_down, dx_perm,
                             d_act, st);
     if (e != hipSuccess) return check_hip(e, "unipool_expert_ffn_bwd: dgrad");
     if (!d_w_gate_up) return UNIPOOL_OK;
@@ -336,7 +330,7 @@ int unipool_expert_ffn_bwd(const unipool_shape* shape, const void* dy_perm, cons
                            (const int32_t* const*)(tab + 4), d_w_gate_up, d_w_down, 1,
                            base + w.zeros, st);
     } else {
-        e = naive_ffn_wgrad(*shape, 1, tab + 0, tab + 1, tab + 2, tab + 3,
+        e = f32_ffn_wgrad(*shape, 1, tab + 0, tab + 1, tab + 2, tab + 3,
                             (const int32_t* const*)(tab + 4), d_w_gate_up, d_w_down, 1, st);
     }
     return check_hip(e, "unipool_expert_ffn_bwd: wgrad");
@@ -357,13 +351,13 @@ int unipool_expert_wgrad(const unipool_shape* shape, int n_layers, const void* c
     char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape) && !force_naive()) {
+    if (mfma_ffn_supported(*shape)) {
         e = launch_fill_zero(base + w.zeros, 256, st);
         if (e != hipSuccess) return check_hip(e, "unipool_expert_wgrad: zero page");
         e = mfma_ffn_wgrad(*shape, n_layers, x_perm_l, d_act_l, act_h_l, dy_perm_l, expert_offsets_l,
                            d_w_gate_up, d_w_down, accumulate, base + w.zeros, st);
     } else {
-        e = naive_ffn_wgrad(*shape, n_layers, x_perm_l, d_act_l, act_h_l, dy_perm_l, expert_offsets_l,
+        e = f32_ffn_wgrad(*shape, n_layers, x_perm_l, d_act_l, act_h_l, dy_perm_l, expert_offsets_l,
                             d_w_gate_up, d_w_down, accumulate, st);
     }
     return check_hip(e, "unipool_expert_wgrad");

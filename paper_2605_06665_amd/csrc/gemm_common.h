@@ -44,8 +44,6 @@ struct TileRef {
     int pair;       // index of the meeting counter shared with the partner tile, or -1
 };
 
-int num_cus();
-
 namespace {
 
 constexpr int EPI_STORE = 0;       // bf16 store (optionally added to the destination)

@@ -1,0 +1,532 @@
+// Contractions on v_mfma_f32_16x16x4_f32: float mode (which is checked to 1e-5), and the router logits of the
+// bfloat16 shapes that the bfloat16 router kernels do not take.  Any sizes, any alignment.
+//
+// The instruction adds its four products in index order, each with one rounding (checked on the device against
+// a chain of fmaf, 512000 of 512000 results equal), so a sum here is the plain index-order chain of fused
+// multiply-adds and does not depend on tile sizes; no kernel in this file cuts a reduction except the router's
+// weight gradient over the tokens.
+//
+// A workgroup is four wavefronts (2 x 2) of WT x WT outputs, WT = 32 or 16.  A 16x16x4 step keeps the matrix
+// core busy for 32 cycles (157 TFLOP/s for the card), eight times the share of a bfloat16 step, so what is hidden is latency:
+// tiles pass through registers (the next stage is requested before the current one is multiplied) into two LDS
+// buffers, one barrier per stage.  Both operands are laid out K-contiguous in LDS whatever they are in memory,
+// and the 16 indices of a chunk are stored as a 4 x 4 transpose (index k at place 4 (k mod 4) + k / 4): the 16
+// bytes that a lane reads are then its operands of four successive instructions.
+// One thread per output element did this work before: 3003 rows, d = 252, f = 500, 12 experts took 2824 us for
+// gate-up, 1454 down, 227 dH, 552 dX, 861 + 453 for the weight gradients of two layers and 262 for the router's;
+// now 30, 19, 23, 33, 65 + 49 and 7 (gate-up 51 TFLOP/s; the strided operands' 4-way conflicts in LDS writes
+// hold back the weight gradients).
+#include "kernels.h"
+
+namespace unipool {
+
+namespace {
+
+constexpr int kThreads = 256;
+
+enum Epilogue {
+    kStore,        // output in the activation type, optionally added to the destination
+    kFloat,        // float output (logits, weight gradients), optionally added
+    kSwigluFwd,    // columns come in pairs of 16 gate and 16 up: writes A, B, H
+    kSwigluBwd,    // the product is dH: reads A, B, writes dA | dB
+};
+
+// C[m][n] = sum_k A(m, k) B(n, k); layouts by template, leading dimensions here.
+struct Args {
+    const void* A;
+    const void* B;
+    int lda, ldb;
+    long long b_stride;            // elements of B between experts
+    int M, N, K;                   // M: rows of all groups (or of the matrix); N per half for kSwigluFwd
+    int n_tiles;                   // column tiles
+    const int32_t* offsets;        // row groups [E + 1]; null: one matrix
+    int E;
+    const int32_t* gather;         // row r of A is row gather[r] / gather_div (null: r)
+    int gather_div;
+    void* out0;
+    void* out1;
+    void* out2;
+    int ldo, add;
+    const void* aux_a;
+    const void* aux_b;
+    int vec_a, vec_b, vec_o;       // four elements at a time: leading dimension and pointers allow it
+    // kFloat over row groups of several layers (K runs over the rows of expert e in every layer)
+    int n_layers;
+    const void* const* a_l;
+    const void* const* b_l;
+    const int32_t* const* off_l;
+    int m_tiles;
+    long long out_stride;
+    int chunk;                     // rows per partial sum (flat K ranges); 0: none
+};
+
+template <typename TA> __device__ __forceinline__ f32x4 fetch_vec(const TA* p);
+template <> __device__ __forceinline__ f32x4 fetch_vec<float>(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+template <> __device__ __forceinline__ f32x4 fetch_vec<bf16>(const bf16* p) {
+    const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
+    return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+// four elements from p on, of which the first n exist (n <= 0: none; with vec: all or none)
+template <typename TA>
+__device__ __forceinline__ f32x4 fetch4(const TA* p, int n, bool vec) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (vec) {
+        if (n > 0) v = fetch_vec(p);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            if (i < n) v[i] = to_f32(p[i]);
+    }
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ void store4(T* p, f32x4 v, int n, bool vec, bool add) {
+    if (vec && n >= 4) {
+        if (add) {
+            const f32x4 o = fetch_vec(p);
+            v = o + v;
+        }
+        if constexpr (std::is_same<T, float>::value) {
+            *reinterpret_cast<f32x4*>(p) = v;
+        } else {
+            const bf16x4 h = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+            *reinterpret_cast<bf16x4*>(p) = h;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            if (i < n) p[i] = from_f32<T>((add ? to_f32(p[i]) : 0.f) + v[i]);
+    }
+}
+
+// Row tile `want` of the row groups, BM rows a tile: every wavefront finds it by itself.
+struct RowTile {
+    int expert, row0, rows;        // rows = 0: past the last tile
+};
+template <int BM>
+__device__ __forceinline__ RowTile find_row_tile(const int32_t* offsets, int E, int want, int lane) {
+    int before = 0;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        const int e = e0 + lane;
+        const int r0 = e < E ? offsets[e] : 0, r1 = e < E ? offsets[e + 1] : 0;
+        const int mine = (r1 - r0 + BM - 1) / BM;
+        int upto = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(upto, d, 64);
+            if (lane >= d) upto += o;
+        }
+        const int first = before + upto - mine;
+        const unsigned long long hit = __ballot(mine > 0 && want >= first && want < first + mine);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            const int f = __shfl(first, src, 64), a = __shfl(r0, src, 64), b = __shfl(r1, src, 64);
+            const int row0 = a + (want - f) * BM;
+            return RowTile{e0 + src, row0, min(BM, b - row0)};
+        }
+        before += __shfl(upto, 63, 64);
+    }
+    return RowTile{0, 0, 0};
+}
+
+// ATR / BTR: the operand's reduction index is the strided one in memory ([k][m], [k][n]).
+// LAYERS: K runs over the rows of one expert in all layers (weight gradients; both operands strided).
+template <typename TA, int WT, bool ATR, bool BTR, Epilogue EPI, bool LAYERS>
+__global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
+    constexpr int BM = 2 * WT;                 // tile of the workgroup, both ways
+    constexpr int BK = WT == 32 ? 32 : 64;     // reduction indices per stage: 2048 values of each operand
+    constexpr int CH = BK / 16;                // 16-index chunks per stage
+    constexpr int LD = BK + 4;                 // LDS row in floats: 16-byte reads of 16 rows meet every bank once
+    constexpr int NF = WT / 16;                // 16-wide fragments per wavefront and side
+    static_assert(BM * BK == 8 * kThreads, "two groups of four values per thread and operand");
+    __shared__ __attribute__((aligned(16))) float lds[2][2][BM * LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l16 = lane & 15, lg = lane >> 4;
+
+    // ---- which tile
+    int expert = 0, row0 = 0, rows = 0, n0, k_begin = 0, k_end = g.K;
+    if constexpr (LAYERS) {
+        const int per = g.m_tiles * g.n_tiles;
+        expert = blockIdx.x / per;
+        const int r = blockIdx.x % per;
+        row0 = (r / g.n_tiles) * BM;
+        rows = min(BM, g.M - row0);
+        n0 = (r % g.n_tiles) * BM;
+        if (g.n_layers == 0) {                 // one matrix cut into chunks of rows: "expert" is the chunk
+            k_begin = expert * g.chunk;
+            k_end = min(g.K, k_begin + g.chunk);
+        }
+    } else {
+        const int mt = blockIdx.x / g.n_tiles;
+        n0 = (blockIdx.x % g.n_tiles) * BM;
+        if (g.offsets != nullptr) {
+            const RowTile t = find_row_tile<BM>(g.offsets, g.E, mt, lane);
+            if (t.rows <= 0) return;
+            expert = t.expert;
+            row0 = t.row0;
+            rows = t.rows;
+        } else {
+            row0 = mt * BM;
+            rows = min(BM, g.M - row0);
+        }
+    }
+    const TA* A = reinterpret_cast<const TA*>(g.A);
+    const TA* B = reinterpret_cast<const TA*>(g.B);
+    if constexpr (!LAYERS) B += (long long)expert * g.b_stride;
+
+    // ---- this thread's two groups of four values of either operand: fixed tile rows (K-contiguous operands)
+    // or fixed tile columns and K rows that advance by BK per stage (strided operands)
+    constexpr int KG = BK / 4, MG = BM / 4;    // groups per row
+    int kq[2], mq[2];                          // K-contiguous: first index, tile row
+    int kr[2], nq[2];                          // strided: K row, first tile column
+    const TA* arow[2];
+    const TA* brow[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const int id = i * kThreads + tid;
+        kq[i] = (id % KG) * 4;
+        mq[i] = id / KG;
+        nq[i] = (id % MG) * 4;
+        kr[i] = id / MG;
+        arow[i] = brow[i] = nullptr;
+        if constexpr (!ATR) {
+            if (mq[i] < rows) {
+                size_t r = (size_t)(row0 + mq[i]);
+                if (g.gather != nullptr) r = (size_t)(g.gather[r] / g.gather_div);
+                arow[i] = A + r * g.lda;
+            }
+        }
+        if constexpr (!BTR) {
+            int n;
+            bool ok;
+            if constexpr (EPI == kSwigluFwd) {
+                // tile rows in groups of 32: 16 gate rows, the 16 up rows of the same columns
+                const int c = n0 / 2 + (mq[i] >> 5) * 16 + (mq[i] & 15);
+                ok = c < g.N;
+                n = (mq[i] & 16) ? g.N + c : c;
+            } else {
+                n = n0 + mq[i];
+                ok = n < g.N;
+            }
+            if (ok) brow[i] = B + (size_t)n * g.ldb;
+        }
+    }
+    // cursors over the rows of the expert, layer after layer: the K rows of this thread's two groups
+    int cl[2] = {-1, -1}, cr[2] = {kr[0], kr[1]}, ce[2] = {0, 0};
+    const TA* ca[2] = {nullptr, nullptr};      // the layer's operands
+    const TA* cb[2] = {nullptr, nullptr};
+    int total_k = k_end - k_begin;
+    auto settle = [&](int i) {                 // move past ended layers
+        while (cr[i] >= ce[i] && cl[i] < g.n_layers) {
+            const int over = cr[i] - ce[i];
+            if (++cl[i] >= g.n_layers) break;
+            const int s = g.off_l[cl[i]][expert];
+            ce[i] = g.off_l[cl[i]][expert + 1];
+            cr[i] = s + over;
+            ca[i] = reinterpret_cast<const TA*>(g.a_l[cl[i]]);
+            cb[i] = reinterpret_cast<const TA*>(g.b_l[cl[i]]);
+        }
+    };
+    if constexpr (LAYERS) {
+        if (g.n_layers > 0) {
+            total_k = 0;
+            for (int l = lane; l < g.n_layers; l += 64) total_k += g.off_l[l][expert + 1] - g.off_l[l][expert];
+            total_k = wave_sum_i(total_k);
+            if (g.add && total_k == 0) return;
+            settle(0);
+            settle(1);
+        }
+    }
+    const int stages = (total_k + BK - 1) / BK;
+
+    f32x4 ra[2], rb[2];
+    auto fetch = [&](int s) {
+        const int k0 = k_begin + s * BK;
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const TA* pa = nullptr;
+            const TA* pb = nullptr;
+            int na = 0, nb = 0;
+            if constexpr (LAYERS) {
+                const int am = row0 + nq[i], bn = n0 + nq[i];
+                if (g.n_layers > 0) {
+                    if (cl[i] < g.n_layers) {
+                        pa = ca[i] + (size_t)cr[i] * g.lda + am;
+                        pb = cb[i] + (size_t)cr[i] * g.ldb + bn;
+                        na = g.M - am;
+                        nb = g.N - bn;
+                        cr[i] += BK;
+                        settle(i);
+                    }
+                } else if (k0 + kr[i] < k_end) {
+                    pa = A + (size_t)(k0 + kr[i]) * g.lda + am;
+                    pb = B + (size_t)(k0 + kr[i]) * g.ldb + bn;
+                    na = g.M - am;
+                    nb = g.N - bn;
+                }
+            } else {
+                static_assert(LAYERS || !ATR, "a strided first operand belongs to the weight gradients");
+                pa = arow[i] + k0 + kq[i];
+                na = arow[i] != nullptr ? k_end - k0 - kq[i] : 0;
+                if constexpr (BTR) {
+                    pb = B + (size_t)(k0 + kr[i]) * g.ldb + n0 + nq[i];
+                    nb = k0 + kr[i] < k_end ? g.N - n0 - nq[i] : 0;
+                } else {
+                    pb = brow[i] + k0 + kq[i];
+                    nb = brow[i] != nullptr ? k_end - k0 - kq[i] : 0;
+                }
+            }
+            // (the layers' operands are only known by address here: one that is not aligned goes value by value)
+            ra[i] = fetch4(pa, na, g.vec_a != 0 && (!LAYERS || ((size_t)pa & (4 * sizeof(TA) - 1)) == 0));
+            rb[i] = fetch4(pb, nb, g.vec_b != 0 && (!LAYERS || ((size_t)pb & (4 * sizeof(TA) - 1)) == 0));
+        }
+    };
+    // place of index k inside an LDS row: chunk, then the 4 x 4 transpose
+    auto place = [](int k) { return (k & ~15) + (k & 3) * 4 + ((k >> 2) & 3); };
+    auto put = [&](float* t, const f32x4& v, bool tr, int i) {
+        if (tr) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) t[(nq[i] + j) * LD + place(kr[i])] = v[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) t[mq[i] * LD + place(kq[i] + j)] = v[j];
+        }
+    };
+
+    f32x4 acc[NF][NF];
+#pragma unroll
+    for (int a = 0; a < NF; a++)
+#pragma unroll
+        for (int b = 0; b < NF; b++) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (stages > 0) fetch(0);
+    for (int s = 0; s < stages; s++) {
+        float* ta = lds[s & 1][0];
+        float* tb = lds[s & 1][1];
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            put(ta, ra[i], ATR, i);
+            put(tb, rb[i], BTR, i);
+        }
+        __syncthreads();                       // the other buffer is free: its readers passed the barrier before
+        if (s + 1 < stages) fetch(s + 1);
+#pragma unroll
+        for (int c = 0; c < CH; c++) {
+            f32x4 fa[NF], fb[NF];
+#pragma unroll
+            for (int a = 0; a < NF; a++)
+                fa[a] = *reinterpret_cast<const f32x4*>(ta + (wm * WT + a * 16 + l16) * LD + c * 16 + lg * 4);
+#pragma unroll
+            for (int b = 0; b < NF; b++)
+                fb[b] = *reinterpret_cast<const f32x4*>(tb + (wn * WT + b * 16 + l16) * LD + c * 16 + lg * 4);
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+#pragma unroll
+                for (int a = 0; a < NF; a++)
+#pragma unroll
+                    for (int b = 0; b < NF; b++)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][q], fa[a][q], acc[a][b], 0, 0, 0);
+        }
+    }
+
+    // ---- epilogue: acc[a][b][r] = C[row wm WT + 16 a + l16][column wn WT + 16 b + 4 lg + r]
+#pragma unroll
+    for (int a = 0; a < NF; a++) {
+        const int m = wm * WT + a * 16 + l16;
+        if (m >= rows) continue;
+        const size_t row = (size_t)(row0 + m);
+        if constexpr (EPI == kSwigluFwd) {
+            static_assert(EPI != kSwigluFwd || NF == 2, "a wavefront owns 16 gate columns and their 16 up columns");
+            const int c = n0 / 2 + wn * 16 + 4 * lg, n = g.N - c;
+            f32x4 h;
+#pragma unroll
+            for (int r = 0; r < 4; r++) h[r] = silu_f(acc[a][0][r]) * acc[a][NF - 1][r];
+            const size_t o = row * g.ldo + c;
+            store4((TA*)g.out0 + o, acc[a][0], n, g.vec_o != 0, false);
+            store4((TA*)g.out1 + o, acc[a][NF - 1], n, g.vec_o != 0, false);
+            store4((TA*)g.out2 + o, h, n, g.vec_o != 0, false);
+        } else {
+#pragma unroll
+            for (int b = 0; b < NF; b++) {
+                const int c = n0 + wn * WT + b * 16 + 4 * lg, n = g.N - c;
+                if (n <= 0) continue;
+                if constexpr (EPI == kStore) {
+                    store4((TA*)g.out0 + row * g.ldo + c, acc[a][b], n, g.vec_o != 0, g.add != 0);
+                } else if constexpr (EPI == kFloat) {
+                    float* o = (float*)g.out0 + (long long)expert * g.out_stride + row * g.ldo + c;
+                    store4(o, acc[a][b], n, g.vec_o != 0, g.add != 0);
+                } else {
+                    const f32x4 va = fetch4((const TA*)g.aux_a + row * g.N + c, n, g.vec_o != 0);
+                    const f32x4 vb = fetch4((const TA*)g.aux_b + row * g.N + c, n, g.vec_o != 0);
+                    f32x4 da, db;
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        const float sg = logistic_f(va[r]), dh = acc[a][b][r];
+                        da[r] = dh * vb[r] * sg * (1.0f + va[r] * (1.0f - sg));
+                        db[r] = dh * va[r] * sg;
+                    }
+                    TA* o = (TA*)g.out0 + row * g.ldo + c;
+                    store4(o, da, n, g.vec_o != 0, false);
+                    store4(o + g.N, db, n, g.vec_o != 0, false);
+                }
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void sum_chunks_kernel(const float* __restrict__ part, int nparts, size_t n,
+                                                         float* __restrict__ out) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    float v = 0.f;
+    for (int p = 0; p < nparts; p++) v += part[(size_t)p * n + i];
+    out[i] = v;
+}
+
+// ---------------------------------------------------------------------------------------------
+// launches
+// ---------------------------------------------------------------------------------------------
+bool aligned(const void* p, int ld, size_t elem) { return ld % 4 == 0 && ((uintptr_t)p & (4 * elem - 1)) == 0; }
+
+// Tiles of 64 x 64 where they give every compute unit a workgroup, 32 x 32 otherwise: at small sizes the time is
+// the latency of the stages, and a quarter of the tile is four times the workgroups.
+bool big_tiles(long long row_tiles_64, int n) { return row_tiles_64 * cdiv(n, 64) >= num_cus(); }
+
+template <typename TA, int WT, bool BTR, Epilogue EPI>
+hipError_t run_rows_wt(Args a, int n_cols, hipStream_t st) {
+    constexpr int BM = 2 * WT;
+    a.n_tiles = cdiv(n_cols, BM);
+    const long long row_tiles = a.offsets ? (long long)a.M / BM + min(a.E, a.M) : cdiv(a.M, BM);
+    const long long grid = row_tiles * a.n_tiles;
+    if (grid >= (1LL << 31)) return hipErrorInvalidValue;
+    gemm_f32_kernel<TA, WT, false, BTR, EPI, false><<<(unsigned)grid, kThreads, 0, st>>>(a);
+    return hipGetLastError();
+}
+// n_cols: columns of the tile axis (both halves for kSwigluFwd)
+template <typename TA, bool BTR, Epilogue EPI>
+hipError_t run_rows(const Args& a, int n_cols, hipStream_t st) {
+    if (EPI == kSwigluFwd || big_tiles(cdiv(a.M, 64), n_cols)) return run_rows_wt<TA, 32, BTR, EPI>(a, n_cols, st);
+    if constexpr (EPI != kSwigluFwd) return run_rows_wt<TA, 16, BTR, EPI>(a, n_cols, st);
+    return hipErrorUnknown;
+}
+template <typename TA>
+hipError_t run_layers(Args a, int groups, hipStream_t st) {
+    if (big_tiles((long long)groups * cdiv(a.M, 64), a.N)) {
+        a.m_tiles = cdiv(a.M, 64); a.n_tiles = cdiv(a.N, 64);
+        gemm_f32_kernel<TA, 32, true, true, kFloat, true>
+            <<<(unsigned)((long long)groups * a.m_tiles * a.n_tiles), kThreads, 0, st>>>(a);
+    } else {
+        a.m_tiles = cdiv(a.M, 32); a.n_tiles = cdiv(a.N, 32);
+        gemm_f32_kernel<TA, 16, true, true, kFloat, true>
+            <<<(unsigned)((long long)groups * a.m_tiles * a.n_tiles), kThreads, 0, st>>>(a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t f32_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st) {
+    Args a = {};
+    a.A = x; a.lda = s.d_model; a.B = w; a.ldb = s.d_model;
+    a.M = s.T; a.N = s.E; a.K = s.d_model;
+    a.out0 = z; a.ldo = s.E;
+    const size_t el = s.dtype == UNIPOOL_BF16 ? 2 : 4;
+    a.vec_a = aligned(x, s.d_model, el); a.vec_b = aligned(w, s.d_model, el); a.vec_o = aligned(z, s.E, 4);
+    return s.dtype == UNIPOOL_BF16 ? run_rows<bf16, false, kFloat>(a, s.E, st) : run_rows<float, false, kFloat>(a, s.E, st);
+}
+
+hipError_t f32_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets, const void* wgu,
+                           void* a_out, void* b_out, void* h_out, hipStream_t st, const int32_t* slot_of_row) {
+    const int d = s.d_model, f = s.d_ff;
+    Args a = {};
+    a.A = x_perm; a.lda = d; a.B = wgu; a.ldb = d; a.b_stride = 2LL * f * d;
+    a.M = s.T * s.k; a.N = f; a.K = d; a.offsets = offsets; a.E = s.E;
+    a.gather = slot_of_row; a.gather_div = s.k;
+    a.out0 = a_out; a.out1 = b_out; a.out2 = h_out; a.ldo = f;
+    a.vec_a = aligned(x_perm, d, 4); a.vec_b = aligned(wgu, d, 4);
+    a.vec_o = aligned(a_out, f, 4) && aligned(b_out, f, 4) && aligned(h_out, f, 4);
+    return run_rows<float, false, kSwigluFwd>(a, 2 * f, st);
+}
+
+hipError_t f32_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets, const void* wgu,
+                       const void* wd, void* a_out, void* b_out, void* h_out, void* y, hipStream_t st,
+                       const int32_t* slot_of_row) {
+    const int d = s.d_model, f = s.d_ff;
+    hipError_t e = f32_ffn_gate_up(s, x_perm, offsets, wgu, a_out, b_out, h_out, st, slot_of_row);
+    if (e != hipSuccess) return e;
+    Args a = {};
+    a.A = h_out; a.lda = f; a.B = wd; a.ldb = f; a.b_stride = (long long)d * f;
+    a.M = s.T * s.k; a.N = d; a.K = f; a.offsets = offsets; a.E = s.E;
+    a.out0 = y; a.ldo = d;
+    a.vec_a = aligned(h_out, f, 4); a.vec_b = aligned(wd, f, 4); a.vec_o = aligned(y, d, 4);
+    return run_rows<float, false, kStore>(a, d, st);
+}
+
+hipError_t f32_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_in, const void* b_in,
+                         const int32_t* offsets, const void* wgu, const void* wd, void* dx, void* d_act,
+                         hipStream_t st) {
+    const int d = s.d_model, f = s.d_ff;
+    Args a = {};                                       // dH = dY W_down, then SwiGLU backward
+    a.A = dy; a.lda = d; a.B = wd; a.ldb = f; a.b_stride = (long long)d * f;
+    a.M = s.T * s.k; a.N = f; a.K = d; a.offsets = offsets; a.E = s.E;
+    a.out0 = d_act; a.ldo = 2 * f; a.aux_a = a_in; a.aux_b = b_in;
+    a.vec_a = aligned(dy, d, 4); a.vec_b = aligned(wd, f, 4);
+    a.vec_o = aligned(d_act, f, 4) && aligned(a_in, f, 4) && aligned(b_in, f, 4);
+    hipError_t e = run_rows<float, true, kSwigluBwd>(a, f, st);
+    if (e != hipSuccess) return e;
+    Args b = {};                                       // dX = [dA | dB] W_gate_up
+    b.A = d_act; b.lda = 2 * f; b.B = wgu; b.ldb = d; b.b_stride = 2LL * f * d;
+    b.M = s.T * s.k; b.N = d; b.K = 2 * f; b.offsets = offsets; b.E = s.E;
+    b.out0 = dx; b.ldo = d;
+    b.vec_a = aligned(d_act, 2 * f, 4); b.vec_b = aligned(wgu, d, 4); b.vec_o = aligned(dx, d, 4);
+    return run_rows<float, true, kStore>(b, d, st);
+}
+
+hipError_t f32_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
+                         const void* const* d_act_l, const void* const* h_l, const void* const* dy_l,
+                         const int32_t* const* offsets_l, float* dwgu, float* dwd, int accumulate, hipStream_t st) {
+    const int d = s.d_model, f = s.d_ff;
+    Args a = {};                                       // d_w_gate_up[e][n][c] = sum d_act[row][n] x_perm[row][c]
+    a.n_layers = n_layers; a.a_l = d_act_l; a.b_l = x_perm_l; a.off_l = offsets_l;
+    a.lda = 2 * f; a.ldb = d; a.M = 2 * f; a.N = d; a.ldo = d; a.out_stride = 2LL * f * d;
+    a.out0 = dwgu; a.add = accumulate;
+    a.vec_a = (2 * f) % 4 == 0; a.vec_b = d % 4 == 0; a.vec_o = aligned(dwgu, d, 4);
+    hipError_t e = run_layers<float>(a, s.E, st);
+    if (e != hipSuccess) return e;
+    Args b = {};                                       // d_w_down[e][c][n] = sum dy[row][c] h[row][n]
+    b.n_layers = n_layers; b.a_l = dy_l; b.b_l = h_l; b.off_l = offsets_l;
+    b.lda = d; b.ldb = f; b.M = d; b.N = f; b.ldo = f; b.out_stride = (long long)d * f;
+    b.out0 = dwd; b.add = accumulate;
+    b.vec_a = d % 4 == 0; b.vec_b = f % 4 == 0; b.vec_o = aligned(dwd, f, 4);
+    return run_layers<float>(b, s.E, st);
+}
+
+hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
+                            void* dx, int dx_accumulate, float* wpart, hipStream_t st) {
+    const int d = s.d_model, E = s.E, T = s.T;
+    // d_w_router = dz^T x.  The tokens are cut into chunks of at least 128 (two stages of a 32 x 32 tile) so that
+    // the chunks' tiles fill the chip; the partial products are added in order.
+    const int tiles = cdiv(E, 32) * cdiv(d, 32);
+    const int nchunks = max(1, min(min(kRouteBwdSplit, T / 128), num_cus() / tiles));
+    const int chunk = cdiv(cdiv(T, nchunks), 64) * 64;
+    const int used = cdiv(T, chunk);
+    Args a = {};
+    a.A = dz; a.lda = E; a.B = x; a.ldb = d; a.M = E; a.N = d; a.K = T; a.chunk = chunk;
+    a.out0 = used > 1 ? wpart : dw; a.ldo = d; a.out_stride = (long long)E * d;
+    a.vec_a = aligned(dz, E, 4); a.vec_b = aligned(x, d, 4); a.vec_o = aligned(a.out0, d, 4);
+    hipError_t e = run_layers<float>(a, used, st);
+    if (e != hipSuccess) return e;
+    if (used > 1) {
+        const size_t n = (size_t)E * d;
+        sum_chunks_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(wpart, used, n, dw);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    Args b = {};                                       // dx (+)= dz W
+    b.A = dz; b.lda = E; b.B = w; b.ldb = d; b.M = T; b.N = d; b.K = E;
+    b.out0 = dx; b.ldo = d; b.add = dx_accumulate;
+    b.vec_a = aligned(dz, E, 4); b.vec_b = aligned(w, d, 4); b.vec_o = aligned(dx, d, 4);
+    return run_rows<float, true, kStore>(b, d, st);
+}
+
+}  // namespace unipool

@@ -47,24 +47,28 @@ bool router_fused_supported(const unipool_shape& s);
 hipError_t router_fused(const unipool_shape& s, const void* x, const void* w, float* z, int32_t* topk_idx,
                         float* topk_gate, int32_t* cnt_part, float* psum_part, hipStream_t st);
 
-// ---- gemm_naive.hip: one thread per output element; any shape, both dtypes ---------
-hipError_t naive_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);
+// ---- gemm_f32.hip: float contractions on the matrix cores, any sizes; logits also of bfloat16 operands -----
+hipError_t f32_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);
 // slot_of_row != nullptr: x_perm is the un-permuted x and row r reads token slot_of_row[r] / k of it
-hipError_t naive_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
-                         const void* wgu, const void* wd, void* a, void* b, void* h, void* y,
-                         hipStream_t st, const int32_t* slot_of_row = nullptr);
-hipError_t naive_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
-                            const void* wgu, void* a, void* b, void* h, hipStream_t st,
-                            const int32_t* slot_of_row = nullptr);
-hipError_t naive_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a, const void* b,
-                           const int32_t* offsets, const void* wgu, const void* wd, void* dx,
-                           void* d_act, hipStream_t st);
-hipError_t naive_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
-                           const void* const* d_act_l, const void* const* h_l,
-                           const void* const* dy_l, const int32_t* const* offsets_l,
-                           float* dwgu, float* dwd, int accumulate, hipStream_t st);
+hipError_t f32_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets, const void* wgu,
+                       const void* wd, void* a, void* b, void* h, void* y, hipStream_t st,
+                       const int32_t* slot_of_row = nullptr);
+hipError_t f32_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets, const void* wgu,
+                           void* a, void* b, void* h, hipStream_t st, const int32_t* slot_of_row = nullptr);
+hipError_t f32_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a, const void* b,
+                         const int32_t* offsets, const void* wgu, const void* wd, void* dx, void* d_act,
+                         hipStream_t st);
+hipError_t f32_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
+                         const void* const* d_act_l, const void* const* h_l, const void* const* dy_l,
+                         const int32_t* const* offsets_l, float* dwgu, float* dwd, int accumulate, hipStream_t st);
+hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
+                            void* dx, int dx_accumulate, float* wpart, hipStream_t st);
+
+// ---- gemm_naive.hip: router backward of bfloat16 pools that are not a multiple of 8 --------
 hipError_t naive_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
                               float* dw, void* dx, int dx_accumulate, hipStream_t st);
+
+int num_cus();
 
 // ---- gemm_mfma.hip: bf16 MFMA grouped GEMMs -----------------------------------------
 bool mfma_ffn_supported(const unipool_shape& s);
