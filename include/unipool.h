@@ -84,10 +84,10 @@ const char* unipool_last_error(void);
 int unipool_version(void);
 
 /*
- * Which kernels a shape gets.  In bfloat16 mode the contractions run on the matrix cores (MFMA); shapes those
- * kernels do not cover still give correct results, on plain one-thread-per-output kernels that are far slower:
- * the router logits and the router backward when E is not a multiple of 8, and everything in float mode.
- * Returns a bit mask: bit 0 the expert GEMMs use MFMA kernels, bit 1 the router contractions do, bit 2 the
+ * Which kernels a shape gets.  In bfloat16 mode the contractions run on the bfloat16 matrix cores (MFMA), except
+ * the router logits when E is not a multiple of 8; those, and everything in float mode, run on the float matrix
+ * cores, which are slower.
+ * Returns a bit mask: bit 0 the expert GEMMs use bfloat16 MFMA kernels, bit 1 all router contractions do, bit 2 the
  * router runs as one fused kernel (logits, scores, top-k, statistics: d_model a multiple of 128, E a multiple
  * of 8 and at most 512).  Negative on an invalid shape.
  */

@@ -1,4 +1,5 @@
 // C ABI of the UniPool library: argument checks, workspace carving and kernel dispatch.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -78,16 +79,16 @@ WsLayout ws_layout(const unipool_shape& s) {
     const size_t T = (size_t)s.T, E = (size_t)s.E, d = (size_t)s.d_model;
     const size_t S = T * (size_t)s.k;
     const size_t rblocks = (T + kRouterTokensPerBlock - 1) / kRouterTokensPerBlock;
-    const size_t act = s.dtype == UNIPOOL_BF16 ? 2 : 4;
+    const size_t act = s.dtype == UNIPOOL_BF16 ? 2 : 4, ez = (size_t)dz_stride(s);
     size_t o = 0;
     w.zeros = o;       o += 256;
     w.tile_meta = o;   o += align_up((4096 + 4 * (S / 256 + 2 * E + T / 128 + 16)) * sizeof(int32_t));
     w.chunk_hist = o;  o += align_up(((T + 63) / 64) * E * sizeof(int32_t));
     w.psum_part = o;   o += align_up(rblocks * E * sizeof(float));
     w.dsigma_part = o; o += align_up(rblocks * E * sizeof(int32_t));   // also holds count partials
-    w.dz = o;          o += align_up(T * E * (act > 4 ? act : 4));     // logits (float) or dz
+    w.dz = o;          o += align_up(std::max(T * E * 4, T * ez * act));   // logits (float) or dz
     w.ptr_tab = o;     o += 256;
-    w.wpart = o;       o += align_up((size_t)kRouteBwdSplit * E * d * sizeof(float));
+    w.wpart = o;       o += align_up((size_t)kRouteBwdSplit * ez * d * sizeof(float));
     w.total = o;
     return w;
 }
@@ -207,15 +208,11 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz,
                                        (float*)(base + w.dsigma_part), d_sigma, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route_bwd: dz");
-    if (mfma_router_supported(*shape)) {
+    if (shape->dtype == UNIPOOL_BF16)
         e = mfma_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate,
-                              (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart),
-                              base + w.zeros, st);
-    } else if (shape->dtype == UNIPOOL_F32) {
+                              (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart), base + w.zeros, st);
+    else
         e = f32_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, (float*)(base + w.wpart), st);
-    } else {
-        e = naive_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, st);
-    }
     return check_hip(e, "unipool_route_bwd: contractions");
 }
 

@@ -78,9 +78,9 @@ struct WsLayout {
     size_t chunk_hist;     // int32 [ceil(T/64)][E]   permute: per-64-token histograms/bases
     size_t psum_part;      // float [router blocks][E] partial score sums
     size_t dsigma_part;    // float [router blocks]
-    size_t dz;             // act   [T][E]  router backward logits gradient
+    size_t dz;             // act   [T][dz_stride]  router backward logits gradient; float [T][E] logits
     size_t ptr_tab;        // 5 device pointers for the single-layer weight gradient
-    size_t wpart;          // float [split][E][d]  router weight gradient partials
+    size_t wpart;          // float [split][dz_stride][d]  router weight gradient partials
     size_t total;
 };
 WsLayout ws_layout(const unipool_shape& s);
@@ -89,5 +89,8 @@ constexpr int kRouterTokensPerBlock = 64;   // tokens per block in the per-token
 constexpr int kRouteBwdSplit = 64;          // max row chunks of the router weight-gradient reduction
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// Row length of dz: the bfloat16 products read it in chunks of eight values, so its rows are filled up with zeros.
+inline int dz_stride(const unipool_shape& s) { return s.dtype == UNIPOOL_BF16 ? cdiv(s.E, 8) * 8 : s.E; }
 
 }  // namespace unipool

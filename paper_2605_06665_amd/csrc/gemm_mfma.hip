@@ -1024,12 +1024,12 @@ __global__ __launch_bounds__(256) void route_bwd_prep_kernel(int T, int chunk_ro
     }
 }
 
-__global__ void reduce_partials_kernel(const float* __restrict__ part, int nparts, size_t n,
+__global__ void reduce_partials_kernel(const float* __restrict__ part, int nparts, size_t stride, size_t n,
                                        float* __restrict__ out) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     float v = 0.f;
-    for (int p = 0; p < nparts; p++) v += part[(size_t)p * n + i];
+    for (int p = 0; p < nparts; p++) v += part[(size_t)p * stride + i];
     out[i] = v;
 }
 
@@ -1121,6 +1121,7 @@ bool mfma_ffn_supported(const unipool_shape& s) {
 }
 
 bool mfma_router_supported(const unipool_shape& s) {
+    // the logits of other pools take the float kernel, which keeps the index-order sums they always had
     return s.dtype == UNIPOOL_BF16 && s.d_model % 64 == 0 && s.E % 8 == 0;
 }
 
@@ -1214,11 +1215,11 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
 hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
                              float* dw, void* dx, int dx_accumulate, int32_t* tile_meta,
                              float* wpart, const void* zeros, hipStream_t st) {
-    const int d = s.d_model, E = s.E, T = s.T;
+    const int d = s.d_model, E = s.E, T = s.T, ez = dz_stride(s);
     // d_w_router = dz^T x: the token axis is cut into chunks whose partial products are summed in
     // a fixed order.
     // as many chunks as give every CU one output tile in a single round
-    const int tiles_per_chunk = cdiv(E, 256) * cdiv(d, 256);
+    const int tiles_per_chunk = cdiv(ez, 256) * cdiv(d, 256);
     const int nchunks = max(1, min(min(kRouteBwdSplit, cdiv(T, 256)), num_cus() / tiles_per_chunk));
     const int chunk_rows = cdiv(cdiv(T, nchunks), 32) * 32;
     const int used = cdiv(T, chunk_rows);
@@ -1233,18 +1234,18 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* 
     a.n_layers = 1;
     a.P = (const void* const*)(tab + 0); a.Q = (const void* const*)(tab + 1);
     a.off = (const int32_t* const*)(tab + 2);
-    a.E = used; a.mdim = E; a.ndim = d; a.m_tiles = cdiv(E, 256); a.n_tiles = cdiv(d, 256);
-    a.out = wpart; a.out_stride = (long long)E * d; a.accumulate = 0; a.zeros = zeros;
+    a.E = used; a.mdim = ez; a.ndim = d; a.m_tiles = cdiv(ez, 256); a.n_tiles = cdiv(d, 256);
+    a.out = wpart; a.out_stride = (long long)ez * d; a.accumulate = 0; a.zeros = zeros;
     e = run_ptq(a, st);
     if (e != hipSuccess) return e;
     const size_t n = (size_t)E * d;
-    reduce_partials_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(wpart, used, n, dw);
+    reduce_partials_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(wpart, used, (size_t)ez * d, n, dw);
     // dx (+)= dz W   (W is [E][d]: reduction index strided)
     GemmArgs b = {};
     // 256-row tiles where they still give every CU a tile: the short reduction (E indices) makes the pipeline
     // fill of a tile as long as its loop, and a taller tile pays it once for twice the rows
     b.flat_rows = T; b.flat_bm = (cdiv(T, kBM) * cdiv(d, kBN) >= num_cus()) ? kBM : kFlatBM;
-    b.X = (const bf16*)dz; b.ldx = E;
+    b.X = (const bf16*)dz; b.ldx = ez;                 // (values between E and ez are zeros)
     b.W = (const bf16*)w; b.w_stride = 0; b.ldw = d;
     b.K = E; b.N = d; b.n_tiles_n = cdiv(d, kBN);
     b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d; b.add = dx_accumulate; b.zeros = zeros;

@@ -64,10 +64,6 @@ hipError_t f32_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const
 hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
                             void* dx, int dx_accumulate, float* wpart, hipStream_t st);
 
-// ---- gemm_naive.hip: router backward of bfloat16 pools that are not a multiple of 8 --------
-hipError_t naive_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
-                              float* dw, void* dx, int dx_accumulate, hipStream_t st);
-
 int num_cus();
 
 // ---- gemm_mfma.hip: bf16 MFMA grouped GEMMs -----------------------------------------

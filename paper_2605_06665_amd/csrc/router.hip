@@ -101,12 +101,13 @@ __global__ __launch_bounds__(256) void route_finalize_kernel(
 
 // Backward of Eq. 7 per token, a group of GS lanes per token as in the forward selection:
 // ds = aux_coef + dgate on the selected experts; dz = J^T ds with J the Jacobian of
-// s = sigma c relu(z / (||z|| + eps)); d sigma = sum ds * s / sigma.
+// s = sigma c relu(z / (||z|| + eps)); d sigma = sum ds * s / sigma.  Rows of dz are ldz >= E values long, the
+// ones past E zero.
 template <typename TA, int GS, int VPL>
 __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ topk_idx,
     const float* __restrict__ dgate, const float* __restrict__ aux_coef, int T, int E, int k,
-    float sigma, float c, float eps, int softmax, TA* __restrict__ dz, float* __restrict__ dsigma_part) {
+    float sigma, float c, float eps, int softmax, TA* __restrict__ dz, int ldz, float* __restrict__ dsigma_part) {
     constexpr int TPW = 64 / GS;
     static_assert(kTokPerWave % TPW == 0, "whole rounds per wavefront");
     __shared__ float lds_ds[kWavesPerBlock];
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
 #pragma unroll
                 for (int i = 0; i < VPL; i++) {
                     const int e = sl + GS * i;
-                    if (e < E) dz[(size_t)t * E + e] = from_f32<TA>(pr[i] * (ds[i] - dotp));
+                    if (e < ldz) dz[(size_t)t * ldz + e] = from_f32<TA>(e < E ? pr[i] * (ds[i] - dotp) : 0.f);
                 }
             }
             continue;
@@ -201,9 +202,9 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
 #pragma unroll
             for (int i = 0; i < VPL; i++) {
                 const int e = sl + GS * i;
-                if (e < E) {
-                    const float v = (n > 0.f) ? dzh[i] * inv - z[i] * back : 0.f;
-                    dz[(size_t)t * E + e] = from_f32<TA>(v);
+                if (e < ldz) {
+                    const float v = (n > 0.f && e < E) ? dzh[i] * inv - z[i] * back : 0.f;
+                    dz[(size_t)t * ldz + e] = from_f32<TA>(v);
                 }
             }
         }
@@ -263,7 +264,7 @@ hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, cons
     const int nblocks = cdiv(s.T, kRouterTokensPerBlock);
 #define UNIPOOL_DZ(TA, GS, VPL)                                                                        \
     route_bwd_dz_kernel<TA, GS, VPL><<<nblocks, 256, 0, st>>>(logits, topk_idx, dgate, aux_coef, s.T, s.E, \
-                                                              s.k, s.sigma, s.c, s.eps, s.router, (TA*)dz, dsigma_part)
+                                                              s.k, s.sigma, s.c, s.eps, s.router, (TA*)dz, dz_stride(s), dsigma_part)
     if (s.dtype == UNIPOOL_BF16) {
         if (s.E <= 128) UNIPOOL_DZ(bf16, 16, 8);
         else if (s.E <= 256) UNIPOOL_DZ(bf16, 16, 16);

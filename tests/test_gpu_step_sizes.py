@@ -17,6 +17,10 @@ CASES = {
     "f32-many-groups": W.Workload("s", L=1, E=130, d=64, f=128, k=1, T=700, dtype="f32", seed=83, c=2.9, skew="zipf"),
     "f32-big-tiles": W.Workload("s", L=1, E=2, d=260, f=264, k=2, T=2049, dtype="f32", seed=84, c=1.2),
     "f32-mixed-alignment": W.Workload("s", L=3, E=5, d=65, f=64, k=3, T=97, dtype="f32", seed=85, c=2.0),
+    # bfloat16 pools that are not a multiple of 8: rows of the logits' gradient filled up with zeros
+    "bf16-three-experts": W.Workload("s", L=2, E=3, d=64, f=64, k=2, T=33, dtype="bf16", seed=86, c=1.5),
+    "bf16-90-experts": W.Workload("s", L=2, E=90, d=192, f=128, k=3, T=777, dtype="bf16", seed=87, c=2.6),
+    "bf16-257-experts": W.Workload("s", L=1, E=257, d=128, f=64, k=4, T=1030, dtype="bf16", seed=88, c=3.3),
 }
 
 
