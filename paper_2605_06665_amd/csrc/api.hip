@@ -243,7 +243,9 @@ int unipool_expert_ffn_fwd(const unipool_shape* shape, const void* x_perm,
     const WsLayout w = ws_layout(*shape);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape))
+    if (few_rows_supported(*shape))
+        e = few_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st);
+    else if (mfma_ffn_supported(*shape))
         e = mfma_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h,
                          y_perm, (int32_t*)((char*)ws + w.tile_meta), st);
     else
@@ -263,7 +265,9 @@ int unipool_expert_ffn_fwd_gather(const unipool_shape* shape, const void* x, con
     const WsLayout w = ws_layout(*shape);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape))
+    if (few_rows_supported(*shape))
+        e = few_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st, slot_of_row);
+    else if (mfma_ffn_supported(*shape))
         e = mfma_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm,
                          (int32_t*)((char*)ws + w.tile_meta), st, slot_of_row);
     else
@@ -283,7 +287,9 @@ int unipool_expert_ffn_recompute(const unipool_shape* shape, const void* x_perm,
     const WsLayout w = ws_layout(*shape);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape))
+    if (few_rows_supported(*shape))
+        e = few_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h, st);
+    else if (mfma_ffn_supported(*shape))
         e = mfma_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h,
                              (int32_t*)((char*)ws + w.tile_meta), st);
     else

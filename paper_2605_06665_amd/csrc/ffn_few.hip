@@ -1,0 +1,284 @@
+// Expert FFN forward for calls with few rows per expert (decoding, short prompts), bfloat16.
+//
+// With a handful of rows per expert the two products are a single pass over the weights of the experts that
+// have rows (2 FLOP per weight byte and row), so HBM is the bound and what counts is how many weight bytes
+// are in flight.  Nothing is shared between wavefronts, hence no LDS tiles, no tile table and no barriers in
+// the reduction:
+//   * a task is one expert and 16 output columns (gate-up: 16 gate columns and the 16 up columns they meet),
+//     and a wavefront owns it for all rows of the expert, so each weight is read by one wavefront only;
+//   * weights go straight from memory to registers, three to six steps of 64 reduction indices ahead.  A load
+//     covers 8 columns x 128 bytes, whole cache lines (16 columns x 64 bytes, the layout the MFMA A operand
+//     wants, reached 5.2 TB/s where this reaches 5.8), and a rotation of half of the lanes by eight turns two of
+//     them into two A operands.  Each weight is used once, so the loads are streaming loads (5.8 -> 6.3 TB/s).
+//   * activation fragments (the B operand) come the same way, up to 32 rows per pass over the weights; rows past
+//     the expert's last repeat it, so they add no cache lines;
+//   * where the tasks alone would leave SIMDs idle, the four wavefronts of a workgroup split the reduction
+//     of one task and add their parts in wavefront order.
+// Every workgroup finds the experts with rows by itself (one pass over the offsets), which costs less than
+// the launch that a table would need.
+// Measured, both products, against the tiles of gemm_xw: 192 experts of 1536 x 4096, k = 2: 1 token 54 -> 20 us, 4
+// tokens 98 -> 55 (5.5 TB/s), 64 tokens 643 -> 579 (6.3 TB/s of the 6.3 that a read stream reaches); 512 experts of
+// 1024 x 704, k = 8, 48 tokens 227 -> 201 us (5.8 TB/s).
+#include "kernels.h"
+
+namespace unipool {
+
+namespace {
+
+constexpr int kFewWaves = 4;
+constexpr int kFewThreads = 64 * kFewWaves;
+constexpr int kFewMaxE = 512;
+
+struct FewArgs {
+    const bf16* X;                      // [rows][K], or the tokens when gather is given
+    const int32_t* gather;              // row r is row gather[r] / gather_div of X
+    int gather_div;
+    const bf16* W;                      // [E][columns][K]
+    long long w_stride;
+    int up_rows;                        // gate-up: first up column (= d_ff)
+    const int32_t* offsets;
+    int E, K, N;
+    bf16* out0;                         // y, or A
+    bf16* out1;                         // B
+    bf16* out2;                         // H
+};
+
+__device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d) {
+    union { bf16 h[4]; uint2 u; } p;
+    p.h[0] = (bf16)a; p.h[1] = (bf16)b; p.h[2] = (bf16)c; p.h[3] = (bf16)d;
+    return p.u;
+}
+
+// The two MFMA operands of 16 columns x 64 indices from two loads that cover whole 128-byte lines: lane l of lo
+// (hi) holds 16-byte chunk l / 8 of row l % 8 (8 + l % 8).  even: chunks 0 2 4 6, odd: chunks 1 3 5 7, lane l with
+// row l % 16; half of the lanes keep what they loaded, the others take it from the lane eight further on.
+typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void few_fragments(const u32x4v& lo, const u32x4v& hi, bf16x8& even, bf16x8& odd) {
+    constexpr int kRowRor8 = 0x128;
+    union { u32x4v u; bf16x8 v; } e, o;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        e.u[i] = __builtin_amdgcn_update_dpp(lo[i], hi[i], kRowRor8, 0xf, 0xc, false);
+        o.u[i] = __builtin_amdgcn_update_dpp(hi[i], lo[i], kRowRor8, 0xf, 0x3, false);
+    }
+    even = e.v;
+    odd = o.v;
+}
+
+// Sum over steps [s0, s1) of 64 indices for R row fragments, NF weight fragments.  D steps are in flight.
+// wp: this lane's chunk of columns 0..7 (hi: 8 columns further on), xp: this lane's two chunks of a row.
+template <int NF, int R, int D>
+__device__ __forceinline__ void few_reduce(const bf16* const (&wp)[NF], size_t hi, const bf16* const (&xp)[R], int s0,
+                                           int s1, f32x4 (&acc)[NF][R]) {
+    u32x4v wq[D][NF][2];
+    bf16x8 xq[D][R][2];
+#pragma unroll
+    for (int f = 0; f < NF; f++)
+#pragma unroll
+        for (int r = 0; r < R; r++) acc[f][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (s0 >= s1) return;
+    auto fetch = [&](int u, int s) {
+        const size_t o = (size_t)min(s, s1 - 1) * 64;          // past the end: the last step again, never used
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const u32x4v* src = reinterpret_cast<const u32x4v*>(wp[f] + o + h * hi);
+                wq[u][f][h] = __builtin_nontemporal_load(src);
+            }
+#pragma unroll
+        for (int r = 0; r < R; r++)
+#pragma unroll
+            for (int h = 0; h < 2; h++) xq[u][r][h] = *reinterpret_cast<const bf16x8*>(xp[r] + o + 8 * h);
+    };
+    auto multiply = [&](int u) {
+#pragma unroll
+        for (int f = 0; f < NF; f++) {
+            bf16x8 even, odd;
+            few_fragments(wq[u][f][0], wq[u][f][1], even, odd);
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(even, xq[u][r][0], acc[f][r], 0, 0, 0);
+                acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(odd, xq[u][r][1], acc[f][r], 0, 0, 0);
+            }
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < D; u++) fetch(u, s0 + u);
+    int s = s0;
+    for (; s + D <= s1; s += D) {
+#pragma unroll
+        for (int u = 0; u < D; u++) {
+            multiply(u);
+            fetch(u, s + D + u);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < D; u++)
+        if (s + u < s1) multiply(u);
+}
+
+// One task: rows row0 .. row0 + rows - 1 (at most 16 R) of an expert against columns c0 .. c0 + 15.
+template <bool GATE_UP, bool SPLIT, int R, int D>
+__device__ __forceinline__ void few_task(const FewArgs& a, const bf16* We, int c0, int row0, int rows, int wave, int lane,
+                                         f32x4* red) {
+    constexpr int NF = GATE_UP ? 2 : 1;
+    const int l16 = lane & 15, lg = lane >> 4;
+    const bf16* xp[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        int row = row0 + min(16 * r + l16, rows - 1);
+        if (a.gather != nullptr) row = a.gather[row] / a.gather_div;
+        xp[r] = a.X + (size_t)row * a.K + 16 * lg;
+    }
+    const bf16* wp[NF];
+#pragma unroll
+    for (int f = 0; f < NF; f++) wp[f] = We + (size_t)(f * a.up_rows + c0 + (lane & 7)) * a.K + 8 * (lane >> 3);
+    const int ns = a.K / 64;
+    f32x4 acc[NF][R];
+    if constexpr (SPLIT) {
+        few_reduce<NF, R, D>(wp, (size_t)8 * a.K, xp, wave * ns / kFewWaves, (wave + 1) * ns / kFewWaves, acc);
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int r = 0; r < R; r++) red[((wave * NF + f) * R + r) * 64 + lane] = acc[f][r];
+        __syncthreads();
+    } else {
+        few_reduce<NF, R, D>(wp, (size_t)8 * a.K, xp, 0, ns, acc);
+    }
+    // acc[f][r][i] = C[row 16 r + l16][column c0 + 4 lg + i]; split: wavefront r adds up the parts of fragment r
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        f32x4 v[NF];
+        if constexpr (SPLIT) {
+            if (r != wave) continue;
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                v[f] = red[(f * R + r) * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < kFewWaves; w++) v[f] += red[((w * NF + f) * R + r) * 64 + lane];
+            }
+        } else {
+#pragma unroll
+            for (int f = 0; f < NF; f++) v[f] = acc[f][r];
+        }
+        if (16 * r + l16 < rows) {
+            const size_t o = (size_t)(row0 + 16 * r + l16) * a.N + c0 + 4 * lg;
+            *reinterpret_cast<uint2*>(a.out0 + o) = pack_bf16x4(v[0][0], v[0][1], v[0][2], v[0][3]);
+            if constexpr (GATE_UP) {
+                float h[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) h[i] = silu_f(v[0][i]) * v[1][i];
+                *reinterpret_cast<uint2*>(a.out1 + o) = pack_bf16x4(v[1][0], v[1][1], v[1][2], v[1][3]);
+                *reinterpret_cast<uint2*>(a.out2 + o) = pack_bf16x4(h[0], h[1], h[2], h[3]);
+            }
+        }
+    }
+    if constexpr (SPLIT) __syncthreads();         // the parts have been read
+}
+
+// RM: most row fragments per pass over an expert's weights
+template <bool GATE_UP, bool SPLIT, int RM>
+__global__ __launch_bounds__(kFewThreads) void ffn_few_kernel(const FewArgs a) {
+    __shared__ int list_e[kFewMaxE], list_r0[kFewMaxE], list_n[kFewMaxE];
+    __shared__ int wcnt[2][kFewWaves];
+    __shared__ f32x4 red[SPLIT ? kFewWaves * (GATE_UP ? 2 : 1) * RM * 64 : 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // experts with rows, in ascending order
+    int n_list = 0;
+#pragma unroll
+    for (int p = 0; p < kFewMaxE / kFewThreads; p++) {
+        const int e = p * kFewThreads + tid;
+        int r0 = 0, n = 0;
+        if (e < a.E) {
+            r0 = a.offsets[e];
+            n = a.offsets[e + 1] - r0;
+        }
+        const unsigned long long has = __ballot(n > 0);
+        if (lane == 0) wcnt[p][wave] = __popcll(has);
+        __syncthreads();
+        int at = n_list;
+#pragma unroll
+        for (int w = 0; w < kFewWaves; w++) {
+            if (w < wave) at += wcnt[p][w];
+            n_list += wcnt[p][w];
+        }
+        if (n > 0) {
+            at += __popcll(has & ((1ull << lane) - 1ull));
+            list_e[at] = e;
+            list_r0[at] = r0;
+            list_n[at] = n;
+        }
+    }
+    __syncthreads();
+    const int per_e = a.N / 16;
+    const int tasks = n_list * per_e;
+    const int first = SPLIT ? blockIdx.x : blockIdx.x * kFewWaves + wave;
+    const int step = SPLIT ? gridDim.x : gridDim.x * kFewWaves;
+    constexpr int D1 = GATE_UP ? 4 : 6;           // steps in flight: about 100 registers of fragments
+    for (int t = first; t < tasks; t += step) {
+        const int i = t / per_e, c0 = (t % per_e) * 16;
+        const int e = __builtin_amdgcn_readfirstlane(list_e[i]);
+        const int r0 = __builtin_amdgcn_readfirstlane(list_r0[i]);
+        const int n = __builtin_amdgcn_readfirstlane(list_n[i]);
+        const bf16* We = a.W + (long long)e * a.w_stride;
+        for (int c = 0; c < n; c += 16 * RM) {
+            const int rows = min(n - c, 16 * RM);
+            if (RM == 1 || rows <= 16) few_task<GATE_UP, SPLIT, 1, D1>(a, We, c0, r0 + c, rows, wave, lane, red);
+            else few_task<GATE_UP, SPLIT, RM, 3>(a, We, c0, r0 + c, rows, wave, lane, red);
+        }
+    }
+}
+
+template <bool GATE_UP>
+hipError_t run_few(const FewArgs& a, int tokens, int total_rows, hipStream_t st) {
+    // tasks if every row had an expert of its own; below two wavefronts per SIMD the reduction is split
+    const int most = (total_rows < a.E ? total_rows : a.E) * (a.N / 16);
+    const int cus = num_cus();
+    const bool one = tokens <= 16;                // an expert gets a token at most once
+    if (most < 8 * cus) {
+        if (one) ffn_few_kernel<GATE_UP, true, 1><<<most, kFewThreads, 0, st>>>(a);
+        else ffn_few_kernel<GATE_UP, true, 2><<<most, kFewThreads, 0, st>>>(a);
+    } else {
+        const int blocks = cdiv(most, kFewWaves) < 4 * cus ? cdiv(most, kFewWaves) : 4 * cus;
+        if (one) ffn_few_kernel<GATE_UP, false, 1><<<blocks, kFewThreads, 0, st>>>(a);
+        else ffn_few_kernel<GATE_UP, false, 2><<<blocks, kFewThreads, 0, st>>>(a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool few_rows_supported(const unipool_shape& s) {
+    // Up to 16 tokens an expert has at most one row fragment; up to 64 it pays while the experts have eight rows on
+    // average.  Both products, this path against the tiles (us): 192 experts of 1536 x 4096, k = 2, 4 tokens 55 / 98,
+    // 64 tokens 605 / 666; 512 experts of 1024 x 704, k = 8, 64 tokens 245 / 288; 16 experts of 1024 x 1024, k = 4,
+    // 32 tokens (8 rows) 39 / 39, 64 tokens (16 rows) 44 / 38.  At 128 tokens skewed use already puts more rows on
+    // one expert than a pass holds: 582 / 558.
+    return mfma_ffn_supported(s) && (s.T <= 16 || (s.T <= 64 && s.T * s.k <= 8 * s.E));
+}
+
+hipError_t few_ffn_gate_up(const unipool_shape& s, const void* x, const int32_t* offsets, const void* wgu, void* a_out,
+                           void* b_out, void* h_out, hipStream_t st, const int32_t* slot_of_row) {
+    FewArgs a = {};
+    a.X = (const bf16*)x; a.gather = slot_of_row; a.gather_div = s.k;
+    a.W = (const bf16*)wgu; a.w_stride = 2LL * s.d_ff * s.d_model; a.up_rows = s.d_ff;
+    a.offsets = offsets; a.E = s.E; a.K = s.d_model; a.N = s.d_ff;
+    a.out0 = (bf16*)a_out; a.out1 = (bf16*)b_out; a.out2 = (bf16*)h_out;
+    return run_few<true>(a, s.T, s.T * s.k, st);
+}
+
+hipError_t few_ffn_fwd(const unipool_shape& s, const void* x, const int32_t* offsets, const void* wgu, const void* wd,
+                       void* a_out, void* b_out, void* h_out, void* y, hipStream_t st, const int32_t* slot_of_row) {
+    hipError_t e = few_ffn_gate_up(s, x, offsets, wgu, a_out, b_out, h_out, st, slot_of_row);
+    if (e != hipSuccess) return e;
+    FewArgs a = {};
+    a.X = (const bf16*)h_out;
+    a.W = (const bf16*)wd; a.w_stride = (long long)s.d_model * s.d_ff;
+    a.offsets = offsets; a.E = s.E; a.K = s.d_ff; a.N = s.d_model;
+    a.out0 = (bf16*)y;
+    return run_few<false>(a, s.T, s.T * s.k, st);
+}
+
+}  // namespace unipool

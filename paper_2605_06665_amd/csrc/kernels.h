@@ -89,6 +89,14 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* 
                              float* dw, void* dx, int dx_accumulate, int32_t* tile_meta,
                              float* wpart, const void* zeros, hipStream_t st);
 
+// ---- ffn_few.hip: bf16 expert FFN forward where an expert has few rows -----------------------
+bool few_rows_supported(const unipool_shape& s);
+hipError_t few_ffn_gate_up(const unipool_shape& s, const void* x, const int32_t* offsets, const void* wgu, void* a_out,
+                           void* b_out, void* h_out, hipStream_t st, const int32_t* slot_of_row = nullptr);
+hipError_t few_ffn_fwd(const unipool_shape& s, const void* x, const int32_t* offsets, const void* wgu, const void* wd,
+                       void* a_out, void* b_out, void* h_out, void* y, hipStream_t st,
+                       const int32_t* slot_of_row = nullptr);
+
 // ---- small utilities (api.hip) ---------------------------------------------------------
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_set_ptrs(void** table, const void* p0, const void* p1, const void* p2,
