@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libunipool.so")
 SOURCES = ["api.hip", "router.hip", "router_fused.hip", "permute.hip", "combine.hip", "aux_loss.hip", "analysis.hip", "gemm_f32.hip",
-           "gemm_mfma.hip", "ffn_few.hip"]
+           "gemm_mfma.hip", "ffn_few.hip", "router_few.hip"]
 
 def _hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")):

@@ -174,22 +174,28 @@ int unipool_route(const unipool_shape* shape, const void* x, const void* w_route
     hipStream_t st = (hipStream_t)stream;
     float* z = logits ? logits : (float*)(base + w.dz);
     hipError_t e;
-    if (router_fused_supported(*shape) && !unfused_router()) {
+    const bool few = router_few_supported(*shape);
+    if (!few && router_fused_supported(*shape) && !unfused_router()) {
         // logits, scores, top-k and block statistics in one kernel; then the sum over the blocks
-        int32_t* cnt_part = (int32_t*)(base + w.dsigma_part);
-        float* psum_part = (float*)(base + w.psum_part);
+        const bool one_block = shape->T <= kRouterTokensPerBlock;     // then its statistics are the layer's
+        int32_t* cnt_part = one_block ? counts : (int32_t*)(base + w.dsigma_part);
+        float* psum_part = one_block ? psum : (float*)(base + w.psum_part);
         e = router_fused(*shape, x, w_router, z, topk_idx, topk_gate, cnt_part, psum_part, st);
         if (e != hipSuccess) return check_hip(e, "unipool_route: fused router");
+        if (one_block) return UNIPOOL_OK;
         return check_hip(launch_route_finalize(*shape, cnt_part, psum_part, counts, psum, st),
                          "unipool_route: statistics");
     }
-    if (mfma_router_supported(*shape))
+    if (few)
+        e = router_few_logits(*shape, x, w_router, z, st);
+    else if (mfma_router_supported(*shape))
         e = mfma_logits(*shape, x, w_router, z, (int32_t*)(base + w.tile_meta), st);
     else
         e = f32_logits(*shape, x, w_router, z, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route: logits");
     e = launch_route_score_topk(*shape, z, topk_idx, topk_gate, counts, psum,
-                                (int32_t*)(base + w.dsigma_part), (float*)(base + w.psum_part), st);
+                                (int32_t*)(base + w.dsigma_part), (float*)(base + w.psum_part),
+                                (float*)(base + w.wpart), st);
     return check_hip(e, "unipool_route: score/top-k");
 }
 

@@ -19,7 +19,7 @@
 // Measured, both products, against the tiles of gemm_xw: 192 experts of 1536 x 4096, k = 2: 1 token 54 -> 20 us, 4
 // tokens 98 -> 55 (5.5 TB/s), 64 tokens 643 -> 579 (6.3 TB/s of the 6.3 that a read stream reaches); 512 experts of
 // 1024 x 704, k = 8, 48 tokens 227 -> 201 us (5.8 TB/s).
-#include "kernels.h"
+#include "few_rows.h"
 
 namespace unipool {
 
@@ -49,75 +49,6 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
     return p.u;
 }
 
-// The two MFMA operands of 16 columns x 64 indices from two loads that cover whole 128-byte lines: lane l of lo
-// (hi) holds 16-byte chunk l / 8 of row l % 8 (8 + l % 8).  even: chunks 0 2 4 6, odd: chunks 1 3 5 7, lane l with
-// row l % 16; half of the lanes keep what they loaded, the others take it from the lane eight further on.
-typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void few_fragments(const u32x4v& lo, const u32x4v& hi, bf16x8& even, bf16x8& odd) {
-    constexpr int kRowRor8 = 0x128;
-    union { u32x4v u; bf16x8 v; } e, o;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        e.u[i] = __builtin_amdgcn_update_dpp(lo[i], hi[i], kRowRor8, 0xf, 0xc, false);
-        o.u[i] = __builtin_amdgcn_update_dpp(hi[i], lo[i], kRowRor8, 0xf, 0x3, false);
-    }
-    even = e.v;
-    odd = o.v;
-}
-
-// Sum over steps [s0, s1) of 64 indices for R row fragments, NF weight fragments.  D steps are in flight.
-// wp: this lane's chunk of columns 0..7 (hi: 8 columns further on), xp: this lane's two chunks of a row.
-template <int NF, int R, int D>
-__device__ __forceinline__ void few_reduce(const bf16* const (&wp)[NF], size_t hi, const bf16* const (&xp)[R], int s0,
-                                           int s1, f32x4 (&acc)[NF][R]) {
-    u32x4v wq[D][NF][2];
-    bf16x8 xq[D][R][2];
-#pragma unroll
-    for (int f = 0; f < NF; f++)
-#pragma unroll
-        for (int r = 0; r < R; r++) acc[f][r] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (s0 >= s1) return;
-    auto fetch = [&](int u, int s) {
-        const size_t o = (size_t)min(s, s1 - 1) * 64;          // past the end: the last step again, never used
-#pragma unroll
-        for (int f = 0; f < NF; f++)
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const u32x4v* src = reinterpret_cast<const u32x4v*>(wp[f] + o + h * hi);
-                wq[u][f][h] = __builtin_nontemporal_load(src);
-            }
-#pragma unroll
-        for (int r = 0; r < R; r++)
-#pragma unroll
-            for (int h = 0; h < 2; h++) xq[u][r][h] = *reinterpret_cast<const bf16x8*>(xp[r] + o + 8 * h);
-    };
-    auto multiply = [&](int u) {
-#pragma unroll
-        for (int f = 0; f < NF; f++) {
-            bf16x8 even, odd;
-            few_fragments(wq[u][f][0], wq[u][f][1], even, odd);
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(even, xq[u][r][0], acc[f][r], 0, 0, 0);
-                acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(odd, xq[u][r][1], acc[f][r], 0, 0, 0);
-            }
-        }
-    };
-#pragma unroll
-    for (int u = 0; u < D; u++) fetch(u, s0 + u);
-    int s = s0;
-    for (; s + D <= s1; s += D) {
-#pragma unroll
-        for (int u = 0; u < D; u++) {
-            multiply(u);
-            fetch(u, s + D + u);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < D; u++)
-        if (s + u < s1) multiply(u);
-}
-
 // One task: rows row0 .. row0 + rows - 1 (at most 16 R) of an expert against columns c0 .. c0 + 15.
 template <bool GATE_UP, bool SPLIT, int R, int D>
 __device__ __forceinline__ void few_task(const FewArgs& a, const bf16* We, int c0, int row0, int rows, int wave, int lane,
@@ -137,14 +68,14 @@ __device__ __forceinline__ void few_task(const FewArgs& a, const bf16* We, int c
     const int ns = a.K / 64;
     f32x4 acc[NF][R];
     if constexpr (SPLIT) {
-        few_reduce<NF, R, D>(wp, (size_t)8 * a.K, xp, wave * ns / kFewWaves, (wave + 1) * ns / kFewWaves, acc);
+        few_reduce<NF, R, D, true>(wp, (size_t)8 * a.K, xp, wave * ns / kFewWaves, (wave + 1) * ns / kFewWaves, acc);
 #pragma unroll
         for (int f = 0; f < NF; f++)
 #pragma unroll
             for (int r = 0; r < R; r++) red[((wave * NF + f) * R + r) * 64 + lane] = acc[f][r];
         __syncthreads();
     } else {
-        few_reduce<NF, R, D>(wp, (size_t)8 * a.K, xp, 0, ns, acc);
+        few_reduce<NF, R, D, true>(wp, (size_t)8 * a.K, xp, 0, ns, acc);
     }
     // acc[f][r][i] = C[row 16 r + l16][column c0 + 4 lg + i]; split: wavefront r adds up the parts of fragment r
 #pragma unroll

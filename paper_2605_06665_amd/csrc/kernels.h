@@ -9,7 +9,7 @@ namespace unipool {
 // Per-token NormRouter score, top-k, gates and block-partial statistics from logits.
 hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, int32_t* topk_idx,
                                    float* topk_gate, int32_t* counts, float* psum,
-                                   int32_t* cnt_part, float* psum_part, hipStream_t st);
+                                   int32_t* cnt_part, float* psum_part, float* wpart, hipStream_t st);
 // Per-token backward of the score: writes dz (act dtype) and d_sigma.
 hipError_t launch_route_finalize(const unipool_shape& s, const int32_t* cnt_part, const float* psum_part,
                                  int32_t* counts, float* psum, hipStream_t st);
@@ -46,6 +46,10 @@ hipError_t launch_distinct_experts(const int32_t* const* idx_layers, int L, int 
 bool router_fused_supported(const unipool_shape& s);
 hipError_t router_fused(const unipool_shape& s, const void* x, const void* w, float* z, int32_t* topk_idx,
                         float* topk_gate, int32_t* cnt_part, float* psum_part, hipStream_t st);
+
+// ---- router_few.hip: logits of a few bfloat16 tokens ------------------------------------------
+bool router_few_supported(const unipool_shape& s);
+hipError_t router_few_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);
 
 // ---- gemm_f32.hip: float contractions on the matrix cores, any sizes; logits also of bfloat16 operands -----
 hipError_t f32_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);

@@ -227,18 +227,113 @@ __global__ __launch_bounds__(64) void permute_copy_scalar_kernel(const uint32_t*
     }
 }
 
+// A few tokens (up to kSmallTokens) in one launch instead of three (kernel time 13.5 -> 2.2 us at 4 tokens of 192 experts): every workgroup
+// builds the masks of all chunks, the expert offsets and the chunk bases for itself in LDS, then places its own four
+// tokens; without a copy a single workgroup writes the index maps of all tokens.
+constexpr int kSmallTokens = 64 * kChunkWaves;      // one chunk per wavefront
+
+template <typename V, int K>
+__global__ __launch_bounds__(256) void permute_small_kernel(const V* __restrict__ x, const int32_t* __restrict__ topk_idx,
+                                                            const int32_t* __restrict__ counts, int T, int E,
+                                                            int row_words, V* __restrict__ x_perm,
+                                                            int32_t* __restrict__ expert_offsets,
+                                                            int32_t* __restrict__ row_of_slot,
+                                                            int32_t* __restrict__ slot_of_row) {
+    __shared__ unsigned long long mask[kChunkWaves][kMaxE];
+    __shared__ int base[kMaxE];                      // first row of the expert
+    __shared__ int wsum[kChunkWaves];
+    __shared__ int own_row[kChunkWaves][K];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(kMaxE == 512 && kChunkWaves == 4, "two experts per thread");
+    // expert offsets: exclusive prefix sum of the counts, two experts per thread
+    const int c0 = 2 * tid < E ? counts[2 * tid] : 0, c1 = 2 * tid + 1 < E ? counts[2 * tid + 1] : 0;
+    const int t_own = wave * 64 + lane;
+    int sel[K];
+#pragma unroll
+    for (int j = 0; j < K; j++) sel[j] = t_own < T ? topk_idx[(size_t)t_own * K + j] : 0;
+    for (int i = tid; i < kChunkWaves * kMaxE; i += 256) (&mask[0][0])[i] = 0ull;
+    int incl = c0 + c1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kChunkWaves - 1; w++)
+        if (w < wave) incl += wsum[w];
+    base[2 * tid] = incl - c0 - c1;
+    base[2 * tid + 1] = incl - c1;
+    if (t_own < T) {
+#pragma unroll
+        for (int j = 0; j < K; j++) atomicOr(&mask[wave][sel[j]], 1ull << lane);
+    }
+    if (blockIdx.x == 0) {
+        if (2 * tid < E) expert_offsets[2 * tid] = incl - c0 - c1;
+        if (2 * tid + 1 < E) expert_offsets[2 * tid + 1] = incl - c1;
+        if (tid == 255) expert_offsets[E] = incl;
+    }
+    __syncthreads();
+    auto row_of = [&](int t, int e) {
+        int r = base[e] + __popcll(mask[t >> 6][e] & ((1ull << (t & 63)) - 1ull));
+        for (int c = 0; c < (t >> 6); c++) r += __popcll(mask[c][e]);
+        return r;
+    };
+    if (x_perm == nullptr) {
+        if (t_own < T) {
+#pragma unroll
+            for (int j = 0; j < K; j++) {
+                const int r = row_of(t_own, sel[j]);
+                row_of_slot[(size_t)t_own * K + j] = r;
+                slot_of_row[r] = t_own * K + j;
+            }
+        }
+        return;
+    }
+    const int t = blockIdx.x * kChunkWaves + wave;
+    if (t < T && lane < K) {
+        const int r = row_of(t, topk_idx[(size_t)t * K + lane]);
+        row_of_slot[(size_t)t * K + lane] = r;
+        slot_of_row[r] = t * K + lane;
+        own_row[wave][lane] = r;
+    }
+    __syncthreads();
+    if (t >= T) return;
+    for (int c = lane; c < row_words; c += 64) {
+        const V v = x[(size_t)t * row_words + c];
+#pragma unroll
+        for (int j = 0; j < K; j++) x_perm[(size_t)own_row[wave][j] * row_words + c] = v;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* topk_idx,
                           const int32_t* counts, void* x_perm, int32_t* expert_offsets,
                           int32_t* row_of_slot, int32_t* slot_of_row, int32_t* chunk_hist,
                           hipStream_t st) {
+    const size_t row_bytes = (size_t)s.d_model * (s.dtype == UNIPOOL_BF16 ? 2 : 4);
+    if (s.T <= kSmallTokens) {
+        const int nblocks = x_perm ? cdiv(s.T, kChunkWaves) : 1;
+        with_top_k(s.k, [&](auto kc) {
+            constexpr int K = decltype(kc)::value;
+            if (row_bytes % 16 == 0)
+                permute_small_kernel<uint4, K><<<nblocks, 256, 0, st>>>((const uint4*)x, topk_idx, counts, s.T, s.E,
+                                                                        (int)(row_bytes / 16), (uint4*)x_perm,
+                                                                        expert_offsets, row_of_slot, slot_of_row);
+            else
+                permute_small_kernel<uint32_t, K><<<nblocks, 256, 0, st>>>((const uint32_t*)x, topk_idx, counts, s.T, s.E,
+                                                                           (int)(row_bytes / 4), (uint32_t*)x_perm,
+                                                                           expert_offsets, row_of_slot, slot_of_row);
+        });
+        return hipGetLastError();
+    }
     const int nchunks = cdiv(s.T, 64);
     const int nblocks = cdiv(nchunks, kChunkWaves);
     const size_t lds = (size_t)kChunkWaves * s.E * sizeof(unsigned long long);
     permute_hist_kernel<<<nblocks, 256, lds, st>>>(topk_idx, s.T, s.E, s.k, chunk_hist);
     permute_scan_kernel<<<s.E, 256, 0, st>>>(counts, s.E, nchunks, expert_offsets, chunk_hist);
-    const size_t row_bytes = (size_t)s.d_model * (s.dtype == UNIPOOL_BF16 ? 2 : 4);
     with_top_k(s.k, [&](auto kc) {
         constexpr int K = decltype(kc)::value;
         if (row_bytes % 16 == 0) {

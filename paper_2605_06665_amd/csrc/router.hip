@@ -11,6 +11,52 @@ namespace {
 constexpr int kWavesPerBlock = 4;
 constexpr int kTokPerWave = kRouterTokensPerBlock / kWavesPerBlock;
 
+// Selection of a few tokens by one workgroup of 16 wavefronts, which then also has the whole statistics: saves the
+// reduction over blocks and its launch (4.6 us).  The sums run over the token groups of a wavefront, then over the
+// wavefronts, in a fixed order.
+constexpr int kOneWaves = 16;
+template <int GS, int VPL>
+__global__ __launch_bounds__(64 * kOneWaves) void route_select_one_kernel(
+    const float* __restrict__ logits, int T, int E, int k, float sigma_c, float eps, int softmax,
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, int32_t* __restrict__ counts, float* __restrict__ psum) {
+    constexpr int TPW = 64 / GS;
+    __shared__ float lds_ps[kOneWaves][GS * VPL];
+    __shared__ int lds_cnt[GS * VPL];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int grp = lane / GS, sl = lane % GS;
+    for (int i = threadIdx.x; i < GS * VPL; i += 64 * kOneWaves) lds_cnt[i] = 0;
+    __syncthreads();
+    float ps[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; i++) ps[i] = 0.f;
+    for (int t0 = wave * TPW; t0 < T; t0 += kOneWaves * TPW) {
+        const int t = t0 + grp;
+        const float* zr = logits + (size_t)min(t, T - 1) * E;
+        float z[VPL];
+#pragma unroll
+        for (int i = 0; i < VPL; i++) {
+            const int e = sl + GS * i;
+            z[i] = (e < E) ? zr[e] : 0.f;
+        }
+        route_select<GS, VPL>(z, sl, E, k, sigma_c, eps, softmax != 0, t < T, (size_t)t, topk_idx, topk_gate, lds_cnt, ps);
+    }
+#pragma unroll
+    for (int i = 0; i < VPL; i++) {
+#pragma unroll
+        for (int o = GS; o < 64; o <<= 1) ps[i] += __shfl_xor(ps[i], o, 64);
+        if (grp == 0) lds_ps[wave][sl + GS * i] = ps[i];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += 64 * kOneWaves) {
+        float v = lds_ps[0][e];
+#pragma unroll
+        for (int w = 1; w < kOneWaves; w++) v += lds_ps[w][e];
+        psum[e] = v;
+        counts[e] = lds_cnt[e];
+    }
+}
+
 // Statistics and selection for the tokens of one block.  A group of GS lanes owns one token at a
 // time (64 / GS tokens per wavefront in flight); lane s of the group holds the logits of experts
 // s, s + GS, ... (VPL of them, E <= GS * VPL).  Partial sums leave the block in a fixed order, so the
@@ -19,8 +65,8 @@ template <int GS, int VPL>
 __global__ __launch_bounds__(256) void route_score_topk_kernel(
     const float* __restrict__ logits, int T, int E, int k, float sigma_c, float eps, int softmax,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate,
-    int32_t* __restrict__ cnt_part, float* __restrict__ psum_part) {
-    constexpr int TPW = 64 / GS;                       // tokens per wavefront at a time
+    int32_t* __restrict__ cnt_part, float* __restrict__ psum_part, int tok_per_wave) {
+    constexpr int TPW = 64 / GS;                       // tokens per wavefront at a time (tok_per_wave: a multiple)
     static_assert(VPL <= 32 && kTokPerWave % TPW == 0, "taken-mask width; whole rounds per wavefront");
     __shared__ float lds_ps[kWavesPerBlock][kMaxE];
     __shared__ int lds_cnt[kMaxE];
@@ -34,7 +80,7 @@ __global__ __launch_bounds__(256) void route_score_topk_kernel(
 #pragma unroll
     for (int i = 0; i < VPL; i++) ps[i] = 0.f;
 
-    const int t0 = blockIdx.x * kRouterTokensPerBlock + wave * kTokPerWave + grp;
+    const int t0 = (blockIdx.x * kWavesPerBlock + wave) * tok_per_wave + grp;
     float z[VPL], zn[VPL];
     auto fetch = [&](int t, float* dst) {
         const float* zr = logits + (size_t)min(t, T - 1) * E;
@@ -45,11 +91,11 @@ __global__ __launch_bounds__(256) void route_score_topk_kernel(
         }
     };
     fetch(t0, zn);
-    for (int tt = 0; tt < kTokPerWave; tt += TPW) {
+    for (int tt = 0; tt < tok_per_wave; tt += TPW) {
         const int t = t0 + tt;
 #pragma unroll
         for (int i = 0; i < VPL; i++) z[i] = zn[i];
-        if (tt + TPW < kTokPerWave) fetch(t + TPW, zn);          // the next token's logits, a round ahead
+        if (tt + TPW < tok_per_wave) fetch(t + TPW, zn);          // the next token's logits, a round ahead
         route_select<GS, VPL>(z, sl, E, k, sigma_c, eps, softmax != 0, t < T, (size_t)t, topk_idx, topk_gate, lds_cnt, ps);
     }
     // score sums: over the token groups of the wavefront (fixed order), then over the wavefronts
@@ -235,18 +281,39 @@ __global__ __launch_bounds__(256) void dsigma_finalize_kernel(const float* __res
 
 hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, int32_t* topk_idx,
                                    float* topk_gate, int32_t* counts, float* psum,
-                                   int32_t* cnt_part, float* psum_part, hipStream_t st) {
-    const int nblocks = cdiv(s.T, kRouterTokensPerBlock);
+                                   int32_t* cnt_part, float* psum_part, float* wpart, hipStream_t st) {
     // lanes per token and logits per lane by pool size
-    if (s.E <= 128)
-        route_score_topk_kernel<16, 8><<<nblocks, 256, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,
-                                                                topk_idx, topk_gate, cnt_part, psum_part);
-    else if (s.E <= 256)
-        route_score_topk_kernel<16, 16><<<nblocks, 256, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,
-                                                                 topk_idx, topk_gate, cnt_part, psum_part);
-    else
-        route_score_topk_kernel<32, 16><<<nblocks, 256, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,
-                                                                 topk_idx, topk_gate, cnt_part, psum_part);
+#define UNIPOOL_SELECT(KERNEL, GRID, THREADS, ...)                                                           \
+    do {                                                                                                     \
+        if (s.E <= 128)                                                                                      \
+            KERNEL<16, 8><<<GRID, THREADS, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,   \
+                                                    topk_idx, topk_gate, __VA_ARGS__);                       \
+        else if (s.E <= 256)                                                                                 \
+            KERNEL<16, 16><<<GRID, THREADS, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,  \
+                                                     topk_idx, topk_gate, __VA_ARGS__);                      \
+        else                                                                                                 \
+            KERNEL<32, 16><<<GRID, THREADS, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,  \
+                                                     topk_idx, topk_gate, __VA_ARGS__);                      \
+    } while (0)
+    // A pick takes a wavefront about 0.2 us of a SIMD's issue slots, and a launch with the sum over the blocks 6 us:
+    // one workgroup (four wavefronts per SIMD) up to 32 picks per SIMD.  512 experts, k = 8: 4 tokens (16 picks in
+    // all) 8 us, 48 tokens (192) 21 us in one workgroup.
+    const int tpw = s.E <= 256 ? 4 : 2;                       // tokens of a wavefront at a time
+    if (s.T <= 128 && cdiv(s.T, tpw) * s.k <= 128) {
+        UNIPOOL_SELECT(route_select_one_kernel, 1, 64 * kOneWaves, counts, psum);
+        return hipGetLastError();
+    }
+    // up to 64 tokens: as many workgroups as there are four wavefronts' worth of tokens; their partial sums
+    // (at most 8 blocks) are more than the areas for blocks of 64 tokens hold and go into the gradient partials'
+    const bool spread = s.T <= kRouterTokensPerBlock;
+    const int per_wave = spread ? tpw : kTokPerWave;
+    const int nblocks = cdiv(s.T, kWavesPerBlock * per_wave);
+    if (spread) {
+        psum_part = wpart;
+        cnt_part = reinterpret_cast<int32_t*>(wpart + (size_t)nblocks * s.E);
+    }
+    UNIPOOL_SELECT(route_score_topk_kernel, nblocks, 256, cnt_part, psum_part, per_wave);
+#undef UNIPOOL_SELECT
     route_finalize_kernel<<<s.E, 256, 0, st>>>(cnt_part, psum_part, nblocks, s.E, counts, psum);
     return hipGetLastError();
 }
