@@ -658,6 +658,7 @@ struct PtqArgs {
     float* out;
     long long out_stride;        // elements between experts
     int accumulate;
+    int stream;                  // the output is larger than the caches and nobody reads it soon
     const void* zeros;           // >= 16 readable zero bytes
 };
 
@@ -961,8 +962,30 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         float* stg = reinterpret_cast<float*>(smem) + wave * (32 * SLD);
         const int jw = n0 + wn * CW;          // first column of the wavefront's block
         const bool vec_ok = (g.ndim & 3) == 0 && (reinterpret_cast<size_t>(g.out) & 15) == 0;
+        // Accumulating, the old values are fetched a pass of 32 rows ahead (the fragments' registers are free by
+        // now): 8 KiB per wavefront in flight at any time, where fetching four rows, adding and storing them
+        // in turn left the reads waiting for each other (one layer's gradients of 90 experts of 832 x 1472, 200 rows
+        // each: 945 -> 780 us).  Gradients of a pool are streamed past the caches, old values too: the operands that
+        // neighbouring tiles share stay there (of these 780, 3 % of the step; 16 experts of 768 x 2048, 188 rows: 100 ->
+        // 91 us a layer).  The router's partial sums are read again by the next launch and stay cached.
+        constexpr int ITS = 32 / RPI;
+        const bool add_vec = vec_ok && g.accumulate;
+        const int c4 = (lane % LPR) * 4, j = jw + c4;
+        f32x4 old[2][ITS];
+        auto fetch_old = [&](int a2) {
+#pragma unroll
+            for (int it = 0; it < ITS; it++) {
+                const int i = m0 + wm * 128 + a2 * 32 + it * RPI + lane / LPR;
+                if (i < g.mdim && j < g.ndim) {
+                    const f32x4* src = reinterpret_cast<const f32x4*>(otile + (size_t)i * g.ndim + j);
+                    old[a2 & 1][it] = __builtin_nontemporal_load(src);
+                }
+            }
+        };
+        if (add_vec) fetch_old(0);
 #pragma unroll
         for (int a2 = 0; a2 < NA / 2; a2++) {
+            if (add_vec && a2 + 1 < NA / 2) fetch_old(a2 + 1);
 #pragma unroll
             for (int ah = 0; ah < 2; ah++)
 #pragma unroll
@@ -971,22 +994,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
                     for (int r = 0; r < 4; r++)
                         stg[(16 * ah + 4 * (lane >> 4) + r) * SLD + b * 16 + (lane & 15)] = acc[2 * a2 + ah][b][r];
             const int i_blk = m0 + wm * 128 + a2 * 32;
-#pragma unroll 4
-            for (int it = 0; it < 32 / RPI; it++) {
+#pragma unroll
+            for (int it = 0; it < ITS; it++) {
                 const int row = it * RPI + lane / LPR;
-                const int c4 = (lane % LPR) * 4;
-                const int i = i_blk + row, j = jw + c4;
+                const int i = i_blk + row;
                 if (i >= g.mdim || j >= g.ndim) continue;
-                float4 v = *reinterpret_cast<const float4*>(stg + row * SLD + c4);
+                f32x4 v = *reinterpret_cast<const f32x4*>(stg + row * SLD + c4);
                 float* dst = otile + (size_t)i * g.ndim + j;
                 if (vec_ok) {                 // then j + 3 < ndim as well
-                    if (g.accumulate) {
-                        const float4 o = *reinterpret_cast<const float4*>(dst);
-                        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-                    }
-                    *reinterpret_cast<float4*>(dst) = v;
+                    if (add_vec) v += old[a2 & 1][it];
+                    if (g.stream) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+                    else *reinterpret_cast<f32x4*>(dst) = v;
                 } else {
-                    const float vv[4] = {v.x, v.y, v.z, v.w};
+                    const float vv[4] = {v[0], v[1], v[2], v[3]};
                     for (int q = 0; q < 4; q++)
                         if (j + q < g.ndim) dst[q] = (g.accumulate ? dst[q] : 0.f) + vv[q];
                 }
@@ -1202,13 +1222,13 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
     PtqArgs a = {};    // d_w_gate_up[e][n][c] = sum d_act[row][n] * x_perm[row][c]
     a.n_layers = n_layers; a.P = d_act_l; a.Q = x_perm_l; a.off = offsets_l;
     a.E = s.E; a.mdim = 2 * f; a.ndim = d; a.m_tiles = cdiv(2 * f, 256); a.n_tiles = cdiv(d, 256);
-    a.out = dwgu; a.out_stride = 2LL * f * d; a.accumulate = accumulate; a.zeros = zeros;
+    a.out = dwgu; a.out_stride = 2LL * f * d; a.accumulate = accumulate; a.stream = 1; a.zeros = zeros;
     hipError_t e = run_ptq(a, st);
     if (e != hipSuccess) return e;
     PtqArgs b = {};    // d_w_down[e][c][n] = sum dy[row][c] * h[row][n]
     b.n_layers = n_layers; b.P = dy_l; b.Q = h_l; b.off = offsets_l;
     b.E = s.E; b.mdim = d; b.ndim = f; b.m_tiles = cdiv(d, 256); b.n_tiles = cdiv(f, 256);
-    b.out = dwd; b.out_stride = (long long)d * f; b.accumulate = accumulate; b.zeros = zeros;
+    b.out = dwd; b.out_stride = (long long)d * f; b.accumulate = accumulate; b.stream = 1; b.zeros = zeros;
     return run_ptq(b, st);
 }
 
