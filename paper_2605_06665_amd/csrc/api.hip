@@ -211,12 +211,16 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
     void* dz = base + w.dz;
-    hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz,
-                                       (float*)(base + w.dsigma_part), d_sigma, st);
+    float* dsigma_part = (float*)(base + w.dsigma_part);
+    const bool bf = shape->dtype == UNIPOOL_BF16;
+    RouteBwdPrep prep = {};
+    if (bf) prep = mfma_route_bwd_prep(*shape, x, (int32_t*)(base + w.tile_meta), base + w.zeros);
+    hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz, dsigma_part,
+                                       bf ? nullptr : d_sigma, prep, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route_bwd: dz");
-    if (shape->dtype == UNIPOOL_BF16)
-        e = mfma_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate,
-                              (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart), base + w.zeros, st);
+    if (bf)
+        e = mfma_route_bwd_mm(*shape, prep, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
+                              (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart), st);
     else
         e = f32_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, (float*)(base + w.wpart), st);
     return check_hip(e, "unipool_route_bwd: contractions");

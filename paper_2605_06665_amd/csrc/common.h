@@ -70,6 +70,21 @@ __device__ __forceinline__ int wave_sum_i(int v) {
     return v;
 }
 
+// out[0] = sum of n floats by one workgroup of 256 threads, a tree of fixed shape
+__device__ __forceinline__ void block_sum_256(const float* part, int n, float* out) {
+    __shared__ float red[256];
+    const int t = threadIdx.x;
+    float v = 0.f;
+    for (int i = t; i < n; i += 256) v += part[i];
+    red[t] = v;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (t < s) red[t] += red[t + s];
+        __syncthreads();
+    }
+    if (t == 0) out[0] = red[0];
+}
+
 // ---- workspace layout ---------------------------------------------------------
 // The workspace is cut into fixed regions, all 256-byte aligned, sized from the shape.
 struct WsLayout {

@@ -13,9 +13,19 @@ hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, 
 // Per-token backward of the score: writes dz (act dtype) and d_sigma.
 hipError_t launch_route_finalize(const unipool_shape& s, const int32_t* cnt_part, const float* psum_part,
                                  int32_t* counts, float* psum, hipStream_t st);
+// Set-up of the router weight gradient (gemm_mfma.hip) that the first workgroup of the dz kernel does on the way: row
+// offsets of the token chunks, the pointer table of the reduction and the page of zeros.
+struct RouteBwdPrep {
+    int32_t* off;                // [nchunks + 1], or null: nothing to do
+    int chunk_rows, nchunks;
+    void** table;                // dz, x, off
+    const void* x;
+    uint32_t* zeros;             // 64 words
+};
+// d_sigma = nullptr: the partial sums stay in dsigma_part ([ceil(T / 64)]) for a later kernel
 hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, const int32_t* topk_idx,
                                const float* dgate, const float* aux_coef, void* dz,
-                               float* dsigma_part, float* d_sigma, hipStream_t st);
+                               float* dsigma_part, float* d_sigma, const RouteBwdPrep& prep, hipStream_t st);
 
 // ---- permute.hip ------------------------------------------------------------------
 hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* topk_idx,
@@ -89,9 +99,10 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
                           const void* const* dy_l, const int32_t* const* offsets_l,
                           float* dwgu, float* dwd, int accumulate, const void* zeros,
                           hipStream_t st);
-hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
-                             float* dw, void* dx, int dx_accumulate, int32_t* tile_meta,
-                             float* wpart, const void* zeros, hipStream_t st);
+RouteBwdPrep mfma_route_bwd_prep(const unipool_shape& s, const void* x, int32_t* tile_meta, void* zeros);
+hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, const void* w, const void* dz,
+                             float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,
+                             int32_t* tile_meta, float* wpart, hipStream_t st);
 
 // ---- ffn_few.hip: bf16 expert FFN forward where an expert has few rows -----------------------
 bool few_rows_supported(const unipool_shape& s);
