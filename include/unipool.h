@@ -88,8 +88,9 @@ int unipool_version(void);
  * the router logits when E is not a multiple of 8; those, and everything in float mode, run on the float matrix
  * cores, which are slower.
  * Returns a bit mask: bit 0 the expert GEMMs use bfloat16 MFMA kernels, bit 1 all router contractions do, bit 2 the
- * router runs as one fused kernel (logits, scores, top-k, statistics: d_model a multiple of 128, E a multiple
- * of 8 and at most 512).  Negative on an invalid shape.
+ * router can run as one fused kernel (logits, scores, top-k, statistics: d_model a multiple of 128, E a multiple
+ * of 8 and at most 512; calls with a few tokens spread the logits over more compute units instead).  Negative on
+ * an invalid shape.
  */
 #define UNIPOOL_FAST_EXPERTS      1
 #define UNIPOOL_FAST_ROUTER       2
