@@ -123,7 +123,7 @@ int unipool_route(const unipool_shape* shape, const void* x, const void* w_route
  *   dz_j     = dzhat_j/(n+eps) - z_j <dzhat, z> / (n (n+eps)^2)
  *   d_w_router = dz^T x;   dx += dz W  (dx_accumulate != 0) or dx = dz W.
  *   UNIPOOL_ROUTER_SOFTMAX:  dz_j = p_j (ds_j - <ds, p>),  d_sigma = 0.
- *   In bfloat16 mode dz is rounded to bfloat16 before the two products.
+ *   In bfloat16 mode dz is rounded to bfloat16 before the two products; dx is rounded once, after the addition.
  * in : x, w_router as in unipool_route;  logits [T, E] float from unipool_route;
  *      topk_idx [T, k];  dgate [T, k] float;  aux_coef [E] float or NULL.
  * out: d_w_router [E, d] float (overwritten);  d_sigma [1] float (overwritten);

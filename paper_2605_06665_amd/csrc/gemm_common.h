@@ -21,7 +21,6 @@ struct GemmArgs {
     void* out1;
     void* out2;
     int ldo;
-    int add;              // EPI_STORE: add to the destination
     const bf16* aux_a;
     const bf16* aux_b;
     int up_rows;          // EPI_SWIGLU_FWD: row offset of the up projection inside W_e (= d_ff)
@@ -207,8 +206,6 @@ template <int MTV> struct AccArray {
 //                 [column 16 nb + 4*(lane/16) + r of the wavefront's 64 columns];
 // MTV = strips of this wavefront that hold rows, LH = only the upper 16 rows of its last strip do.
 // Results pass through the wave-private staging area stg and leave as 16-byte row segments.
-// CAN_ADD: EPI_STORE may add to the destination (g.add); the old values of all strips then take
-// 16 registers per strip, so kernels with many strips per wavefront compile it out.
 // ---------------------------------------------------------------------------------------------
 // What the staged epilogues need of the launch arguments, by value (a handful of scalars the compiler keeps in
 // registers; a reference to the whole argument block has ended up in scratch memory in large kernels).
@@ -218,13 +215,13 @@ struct EpiArgs {
     void* out2;
     const bf16* aux_a;
     const bf16* aux_b;
-    int N, ldo, add;
+    int N, ldo;
 };
 __device__ __forceinline__ EpiArgs epi_args(const GemmArgs& a) {
-    return EpiArgs{a.out0, a.out1, a.out2, a.aux_a, a.aux_b, a.N, a.ldo, a.add};
+    return EpiArgs{a.out0, a.out1, a.out2, a.aux_a, a.aux_b, a.N, a.ldo};
 }
 
-template <int EPI, int MTV, bool LH, bool CAN_ADD, typename AccT>
+template <int EPI, int MTV, bool LH, bool ADD, typename AccT>
 __device__ __forceinline__ void xw_staged_epilogue(const EpiArgs g, const AccT& A,
                                                    char* stg, int rows, int row0, int n0, int f0,
                                                    int strip_first, int strip_step, int wn, int lane) {
@@ -252,22 +249,23 @@ UNIPOOL_LOAD_AB1(TMX, 0) UNIPOOL_LOAD_AB1(TMX, 1) UNIPOOL_LOAD_AB1(TMX, 2) UNIPO
     if constexpr (EPI == EPI_SWIGLU_BWD && MTV > 0) {
         if (cols_ok) { UNIPOOL_LOAD_AB(0) }
     }
-    // EPI_STORE adding to the destination: the old values of all strips are requested up front,
-    // in the layout the row segments leave in, so that their latency is paid once per tile.
-    [[maybe_unused]] uint4 oldv[CAN_ADD && MTV > 0 ? MTV : 1][4];
-    if constexpr (EPI == EPI_STORE && CAN_ADD) {
-        if (g.add) {
+    // ADD (EPI_STORE): the old values of all strips are requested up front, in the layout the row segments leave in, so
+    // that their latency is paid once per tile.  The float accumulators then pass through the staging area, 16 rows at a
+    // time, and meet them there: the sum is rounded once (router backward of 32768 tokens, d_model 1536: 122 us a call as
+    // with a product rounded before the addition; with accumulators that start from the old values 141).
+    [[maybe_unused]] uint4 oldv[ADD && MTV > 0 ? MTV : 1][4];
+    if constexpr (ADD) {
+        static_assert(EPI == EPI_STORE, "only plain stores add");
 #pragma unroll
-            for (int tm = 0; tm < MTV; tm++)
+        for (int tm = 0; tm < MTV; tm++)
 #pragma unroll
-                for (int it = 0; it < 4; it++) {
-                    const int id = it * 64 + lane;
-                    const int rr = min((strip_first + strip_step * tm) * 32 + id / CPRS, rows - 1);
-                    const int col = min(n0 + wn * 64 + (id % CPRS) * 8, g.N - 8);
-                    oldv[tm][it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16*>(g.out0) +
-                                                                   (size_t)(row0 + rr) * g.ldo + col);
-                }
-        }
+            for (int it = 0; it < 4; it++) {
+                const int id = it * 64 + lane;
+                const int rr = min((strip_first + strip_step * tm) * 32 + id / CPRS, rows - 1);
+                const int col = min(n0 + wn * 64 + (id % CPRS) * 8, g.N - 8);
+                oldv[tm][it] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16*>(g.out0) +
+                                                               (size_t)(row0 + rr) * g.ldo + col);
+            }
     }
     static_for<0, MTV>([&](auto tm_c) __attribute__((always_inline)) {
         constexpr int tm = decltype(tm_c)::value;
@@ -275,7 +273,34 @@ UNIPOOL_LOAD_AB1(TMX, 0) UNIPOOL_LOAD_AB1(TMX, 1) UNIPOOL_LOAD_AB1(TMX, 2) UNIPO
         f32x4 acc_s[2][4];
         A.template strip<tm>(acc_s);
         // -- registers -> staging rows
-        if constexpr (EPI == EPI_STORE) {
+        if constexpr (ADD) {
+            constexpr int FROW = SG::SC * 4 + 16;
+            static_assert(16 * FROW <= 32 * SROW, "16 float rows fit where 32 bfloat16 rows do");
+#pragma unroll
+            for (int mh = 0; mh < (LH && tm == MTV - 1 ? 1 : 2); mh++) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int nb = 0; nb < 4; nb++)
+                    *reinterpret_cast<f32x4*>(stg + l16 * FROW + (16 * nb + 4 * lg) * 4) = acc_s[mh][nb];
+#pragma unroll
+                for (int it = 0; it < 2; it++) {
+                    const int srow = it * 8 + lane / CPRS, ch = lane % CPRS;
+                    const f32x4* f = reinterpret_cast<const f32x4*>(stg + srow * FROW + ch * 32);
+                    const f32x4 lo = f[0], hi = f[1];
+                    union { uint4 u; bf16 h[8]; } o;
+                    o.u = oldv[tm][2 * mh + it];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        o.h[i] = (bf16)((float)o.h[i] + lo[i]);
+                        o.h[4 + i] = (bf16)((float)o.h[4 + i] + hi[i]);
+                    }
+                    const int rr = strip0 + 16 * mh + srow, col = n0 + wn * 64 + ch * 8;
+                    if (rr < rows && col < g.N)
+                        *reinterpret_cast<uint4*>(reinterpret_cast<bf16*>(g.out0) + (size_t)(row0 + rr) * g.ldo + col) = o.u;
+                }
+            }
+            return;
+        } else if constexpr (EPI == EPI_STORE) {
 #pragma unroll
             for (int mh = 0; mh < (LH && tm == MTV - 1 ? 1 : 2); mh++)
 #pragma unroll
@@ -355,16 +380,7 @@ UNIPOOL_LOAD_AB1(TMX, 0) UNIPOOL_LOAD_AB1(TMX, 1) UNIPOOL_LOAD_AB1(TMX, 2) UNIPO
                 const int col = n0 + wn * 64 + ch * 8;
                 if (col < g.N) {
                     bf16* dst = reinterpret_cast<bf16*>(g.out0) + grow * g.ldo + col;
-                    if (CAN_ADD && g.add) {
-                        union { uint4 u; bf16 h[8]; } o, n;
-                        o.u = oldv[tm][it];
-                        n.u = v;
-#pragma unroll
-                        for (int i = 0; i < 8; i++) n.h[i] = (bf16)((float)o.h[i] + (float)n.h[i]);
-                        *reinterpret_cast<uint4*>(dst) = n.u;
-                    } else {
-                        *reinterpret_cast<uint4*>(dst) = v;
-                    }
+                    *reinterpret_cast<uint4*>(dst) = v;
                 }
             } else if constexpr (EPI == EPI_SWIGLU_FWD) {
                 const uint4 v = *reinterpret_cast<const uint4*>(stg + srow * SROW + ch * 16);

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(512) void build_tiles_kernel(const int32_t* __restr
 
 // pre: what the previous tile has already requested for this one (bit 0: X(0) and W(0), bit 1: W(1));
 // g0: number of K stages this workgroup has run before this tile (the LDS buffers rotate on).
-template <int BM, int BN, int BK, int NS, bool WK, int EPI, bool KTAIL, int MTV, bool LH>
+template <int BM, int BN, int BK, int NS, bool WK, int EPI, bool KTAIL, bool ADD, int MTV, bool LH>
 __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef cur, TileRef nxt, int pre,
                                         int g0) {
     constexpr int NW = kXwWaves;
@@ -527,13 +527,13 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
         const int rbase = region == 0 ? xbuf(nk - 1) * XBYTES
                                       : WBASE + (region == 1 ? wbuf(nk - 1) : wbuf(nk + 1)) * WBYTES;
         char* stg = smem + rbase + (wave % SG::RW) * SG::WSTG;
-        xw_staged_epilogue<EPI, MTV, LH, true>(epi_args(g), AccArray<MTV>{acc}, stg, rows, row0, n0, f0, wm, 2, wn, lane);
+        xw_staged_epilogue<EPI, MTV, LH, ADD>(epi_args(g), AccArray<MTV>{acc}, stg, rows, row0, n0, f0, wm, 2, wn, lane);
     }
     PHASE_STAMP(t_end);
     PHASE_COMMIT(t_begin, t_filled, t_looped, t_end);
 }
 
-template <int BM, int BN, int BK, int NS, bool WK, int EPI, bool KTAIL>
+template <int BM, int BN, int BK, int NS, bool WK, int EPI, bool KTAIL, bool ADD>
 __global__ __launch_bounds__(kXwThreads) void gemm_xw_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
@@ -629,14 +629,14 @@ __global__ __launch_bounds__(kXwThreads) void gemm_xw_kernel(const GemmArgs g) {
         const int mtv = max(0, (strips - wm + 1) >> 1);
         const bool lh = mtv >= 2 && wm + 2 * (mtv - 1) == strips - 1 && (((cur.rows + 15) >> 4) & 1) != 0;
         switch (2 * mtv + (lh ? 1 : 0)) {
-            case 0: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 0, false>(g, smem, cur, nxt, pre, g0); break;
-            case 2: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 1, false>(g, smem, cur, nxt, pre, g0); break;
-            case 4: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 2, false>(g, smem, cur, nxt, pre, g0); break;
-            case 5: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 2, true>(g, smem, cur, nxt, pre, g0); break;
-            case 6: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 3, false>(g, smem, cur, nxt, pre, g0); break;
-            case 7: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 3, true>(g, smem, cur, nxt, pre, g0); break;
-            case 9: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 4, true>(g, smem, cur, nxt, pre, g0); break;
-            default: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, 4, false>(g, smem, cur, nxt, pre, g0); break;
+            case 0: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 0, false>(g, smem, cur, nxt, pre, g0); break;
+            case 2: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 1, false>(g, smem, cur, nxt, pre, g0); break;
+            case 4: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 2, false>(g, smem, cur, nxt, pre, g0); break;
+            case 5: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 2, true>(g, smem, cur, nxt, pre, g0); break;
+            case 6: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 3, false>(g, smem, cur, nxt, pre, g0); break;
+            case 7: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 3, true>(g, smem, cur, nxt, pre, g0); break;
+            case 9: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 4, true>(g, smem, cur, nxt, pre, g0); break;
+            default: xw_tile<BM, BN, BK, NS, WK, EPI, KTAIL, ADD, 4, false>(g, smem, cur, nxt, pre, g0); break;
         }
         lds_barrier();                // the staging space is free: the next tile may load into it
         pre = (!KTAIL && nxt.valid) ? ((Staging<EPI>::PREW1 && nk > 1) ? 3 : 1) : 0;
@@ -1064,9 +1064,9 @@ constexpr int kGemmLds = kNS * kBM * kBK * 2 + (kNS + 1) * kBN * kBK * 2;   // 2
 constexpr int kPtqLds = kPtqNS * 2 * kPtqBK * 256 * 2;            // 128 KiB
 
 
-template <bool WK, int EPI, bool KTAIL = false>
+template <bool WK, int EPI, bool KTAIL = false, bool ADD = false>
 hipError_t run_xw(GemmArgs a, int max_row_tiles, hipStream_t st) {
-    auto kern = gemm_xw_kernel<kBM, kBN, kBK, kNS, WK, EPI, KTAIL>;
+    auto kern = gemm_xw_kernel<kBM, kBN, kBK, kNS, WK, EPI, KTAIL, ADD>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1280,9 +1280,10 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, c
     b.X = (const bf16*)dz; b.ldx = ez;                 // (values between E and ez are zeros)
     b.W = (const bf16*)w; b.w_stride = 0; b.ldw = d;
     b.K = E; b.N = d; b.n_tiles_n = cdiv(d, kBN);
-    b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d; b.add = dx_accumulate; b.zeros = zeros;
-    if (E % kBK != 0) return run_xw<false, EPI_STORE, true>(b, cdiv(T, kBM), st);
-    return run_xw<false, EPI_STORE>(b, cdiv(T, kBM), st);
+    b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d; b.zeros = zeros;
+    if (dx_accumulate)
+        return E % kBK != 0 ? run_xw<false, EPI_STORE, true, true>(b, cdiv(T, kBM), st) : run_xw<false, EPI_STORE, false, true>(b, cdiv(T, kBM), st);
+    return E % kBK != 0 ? run_xw<false, EPI_STORE, true>(b, cdiv(T, kBM), st) : run_xw<false, EPI_STORE>(b, cdiv(T, kBM), st);
 }
 
 }  // namespace unipool

@@ -1,5 +1,6 @@
 """GPU: the sum over the router gradient's partial products, four values at a time where the output is aligned to 16
-bytes, one otherwise: numbers of parts on both sides of a group of eight, bitwise the same result from both forms."""
+bytes, one otherwise: numbers of parts on both sides of a group of eight, bitwise the same result from both forms.
+dx of the router added to what is there: the sum is rounded once."""
 import numpy as np
 import pytest
 
@@ -44,3 +45,48 @@ def test_both_forms(T):
     want = float((ds_ * 2.0 * zh.clamp_min(0)).sum())
     # T k float terms of about unit size, summed in a tree
     assert abs(float(outs[0][1][0]) - want) <= 1e-5 * float((ds_.abs() * 2.0 * zh.clamp_min(0)).sum()) + 1e-6
+
+
+def _route_bwd_inputs(T, E, d, k, seed):
+    import torch
+    import paper_2605_06665_amd as U
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn((T, d), generator=g).to(torch.bfloat16).cuda()
+    wr = torch.randn((E, d), generator=g).to(torch.bfloat16).cuda()
+    sh = U.Shape(T=T, d_model=d, d_ff=64, E=E, k=k, L=1, dtype=U.BF16, sigma=0.9, c=2.0, eps=1e-6, alpha_pool=0.0, router=0)
+    z = x.float() @ wr.float().T
+    idx = torch.topk(z, k, dim=1).indices.to(torch.int32).contiguous()
+    dgate = torch.randn((T, k), generator=g).cuda()
+    ws = torch.full((U.workspace_bytes(sh),), 0xff, dtype=torch.uint8, device="cuda")
+    # dz as the library defines it, rounded to bfloat16
+    zd = z.double()
+    n = zd.norm(dim=1, keepdim=True)
+    ds = torch.zeros_like(zd).scatter_(1, idx.long(), dgate.double())
+    dzh = ds * 0.9 * 2.0 * (zd > 0)
+    dz = dzh / (n + 1e-6) - zd * (dzh * zd).sum(1, keepdim=True) / ((n + 1e-6) ** 2 * n)
+    return sh, x, wr, z.contiguous(), idx, dgate, ws, dz.to(torch.bfloat16).double()
+
+
+@pytest.mark.parametrize("E,d,T", [(90, 192, 777), (3, 64, 33), (8, 320, 129), (64, 192, 300), (96, 832, 2049)])
+def test_accumulated_dx_is_rounded_once(E, d, T):
+    """dx starts as minus the rounded product, so what is left is the product's own rounding error: a product that is
+    rounded before the addition leaves zeros."""
+    import torch
+    import paper_2605_06665_amd as U
+    sh, x, wr, z, idx, dgate, ws, dz = _route_bwd_inputs(T, E, d, 2, E + T)
+    f32 = dict(device="cuda")
+    dw, ds = torch.empty((E, d), **f32), torch.empty(1, **f32)
+    dx = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    U.route_bwd(sh, x, wr, z, idx, dgate, None, dw, ds, dx, False, ws)
+    product = dz @ wr.double()
+    rounded = dx.clone()
+    dx.neg_()
+    U.route_bwd(sh, x, wr, z, idx, dgate, None, dw, ds, dx, True, ws)
+    left = product - rounded.double()
+    # float sums of at most 96 terms: 1e-5 of the product is ample; half of it more for the rounding of what is left.
+    # dz is computed in float by the library, so a few of its values round the other way (about 5e-4 of them, times E
+    # of a row): rows with one are off by a share of the product, all others are not
+    bad = (dx.double() - left).abs() > 2e-5 * product.abs().amax(dim=1, keepdim=True) + 2.0 ** -8 * left.abs()
+    assert float(left.abs().max()) > 0
+    assert float(bad.any(dim=1).double().mean()) <= 0.2
+    assert float((dx == 0).double().mean()) <= 0.5
