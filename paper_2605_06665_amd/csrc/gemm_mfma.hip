@@ -1065,7 +1065,7 @@ constexpr int kPtqLds = kPtqNS * 2 * kPtqBK * 256 * 2;            // 128 KiB
 
 
 template <bool WK, int EPI, bool KTAIL = false, bool ADD = false>
-hipError_t run_xw(GemmArgs a, int max_row_tiles, hipStream_t st) {
+hipError_t run_xw(GemmArgs a, hipStream_t st) {
     auto kern = gemm_xw_kernel<kBM, kBN, kBK, kNS, WK, EPI, KTAIL, ADD>;
     static bool attr_set = false;
     if (!attr_set) {
@@ -1075,7 +1075,6 @@ hipError_t run_xw(GemmArgs a, int max_row_tiles, hipStream_t st) {
         attr_set = true;
     }
     a.group_m = 2;
-    (void)max_row_tiles;
     const int grid = max(kNumXcd, num_cus() / kNumXcd * kNumXcd);
     kern<<<grid, kXwThreads, kGemmLds, st>>>(a);
     return hipGetLastError();
@@ -1154,14 +1153,13 @@ hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, flo
     a.K = s.d_model; a.N = s.E; a.n_tiles_n = cdiv(s.E, kBN);
     a.tile_meta = tile_meta; a.out0 = z; a.ldo = s.E;
     a.flat_rows = s.T; a.flat_bm = kFlatBM;
-    return run_xw<true, EPI_F32>(a, cdiv(s.T, kBM), st);
+    return run_xw<true, EPI_F32>(a, st);
 }
 
 hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
                            const void* wgu, void* a_out, void* b_out, void* h_out, int32_t* tile_meta,
                            hipStream_t st, const int32_t* slot_of_row) {
     const int S = s.T * s.k, d = s.d_model, f = s.d_ff;
-    const int max_tiles = S / kBM + s.E;
     hipError_t e = build_tiles(offsets, s.E, S, tile_meta, st);
     if (e != hipSuccess) return e;
     GemmArgs a = {};
@@ -1171,14 +1169,13 @@ hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const in
     a.tile_meta = tile_meta; a.out0 = a_out; a.out1 = b_out; a.out2 = h_out; a.ldo = f;
     a.up_rows = f;
     a.gather = slot_of_row; a.gather_div = s.k;
-    return run_xw<true, EPI_SWIGLU_FWD>(a, max_tiles, st);
+    return run_xw<true, EPI_SWIGLU_FWD>(a, st);
 }
 
 hipError_t mfma_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
                         const void* wgu, const void* wd, void* a_out, void* b_out, void* h_out,
                         void* y, int32_t* tile_meta, hipStream_t st, const int32_t* slot_of_row) {
     const int S = s.T * s.k, d = s.d_model, f = s.d_ff;
-    const int max_tiles = S / kBM + s.E;
     hipError_t e = mfma_ffn_gate_up(s, x_perm, offsets, wgu, a_out, b_out, h_out, tile_meta, st, slot_of_row);
     if (e != hipSuccess) return e;
     GemmArgs b = {};
@@ -1187,14 +1184,13 @@ hipError_t mfma_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_
     b.K = f; b.N = d; b.n_tiles_n = cdiv(d, kBN);
     b.tile_meta = tile_meta; b.launch_slot = 1; b.out0 = y; b.ldo = d;
     if (b.K >= kPairMinK) { b.pair_cnt = pair_counters(tile_meta, s.E, S); b.pair_cap = kPairCap; }
-    return run_xw<true, EPI_STORE>(b, max_tiles, st);
+    return run_xw<true, EPI_STORE>(b, st);
 }
 
 hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_in, const void* b_in,
                           const int32_t* offsets, const void* wgu, const void* wd, void* dx,
                           void* d_act, int32_t* tile_meta, hipStream_t st) {
     const int S = s.T * s.k, d = s.d_model, f = s.d_ff;
-    const int max_tiles = S / kBM + s.E;
     hipError_t e = build_tiles(offsets, s.E, S, tile_meta, st);
     if (e != hipSuccess) return e;
     GemmArgs a = {};   // dH = dY W_down (W_down[e] is [d][f]: reduction index strided), then SwiGLU backward
@@ -1203,7 +1199,7 @@ hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_
     a.K = d; a.N = f; a.n_tiles_n = cdiv(f, kBN);
     a.tile_meta = tile_meta; a.out0 = d_act; a.ldo = 2 * f;
     a.aux_a = (const bf16*)a_in; a.aux_b = (const bf16*)b_in;
-    e = run_xw<false, EPI_SWIGLU_BWD>(a, max_tiles, st);
+    e = run_xw<false, EPI_SWIGLU_BWD>(a, st);
     if (e != hipSuccess) return e;
     GemmArgs b = {};   // dX = [dA|dB] W_gate_up (W_gate_up[e] is [2f][d])
     b.X = (const bf16*)d_act; b.ldx = 2 * f;
@@ -1211,7 +1207,7 @@ hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_
     b.K = 2 * f; b.N = d; b.n_tiles_n = cdiv(d, kBN);
     b.tile_meta = tile_meta; b.launch_slot = 1; b.out0 = dx; b.ldo = d;
     if (b.K >= kPairMinK) { b.pair_cnt = pair_counters(tile_meta, s.E, S); b.pair_cap = kPairCap; }
-    return run_xw<false, EPI_STORE>(b, max_tiles, st);
+    return run_xw<false, EPI_STORE>(b, st);
 }
 
 hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
@@ -1282,8 +1278,8 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, c
     b.K = E; b.N = d; b.n_tiles_n = cdiv(d, kBN);
     b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d; b.zeros = zeros;
     if (dx_accumulate)
-        return E % kBK != 0 ? run_xw<false, EPI_STORE, true, true>(b, cdiv(T, kBM), st) : run_xw<false, EPI_STORE, false, true>(b, cdiv(T, kBM), st);
-    return E % kBK != 0 ? run_xw<false, EPI_STORE, true>(b, cdiv(T, kBM), st) : run_xw<false, EPI_STORE>(b, cdiv(T, kBM), st);
+        return E % kBK != 0 ? run_xw<false, EPI_STORE, true, true>(b, st) : run_xw<false, EPI_STORE, false, true>(b, st);
+    return E % kBK != 0 ? run_xw<false, EPI_STORE, true>(b, st) : run_xw<false, EPI_STORE>(b, st);
 }
 
 }  // namespace unipool
