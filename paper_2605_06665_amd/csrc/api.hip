@@ -212,13 +212,13 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     hipStream_t st = (hipStream_t)stream;
     void* dz = base + w.dz;
     float* dsigma_part = (float*)(base + w.dsigma_part);
-    const bool bf = shape->dtype == UNIPOOL_BF16;
+    const bool mfma = mfma_route_bwd_supported(*shape, x, w_router, dx);
     RouteBwdPrep prep = {};
-    if (bf) prep = mfma_route_bwd_prep(*shape, x, (int32_t*)(base + w.tile_meta), base + w.zeros);
+    if (mfma) prep = mfma_route_bwd_prep(*shape, x, (int32_t*)(base + w.tile_meta), base + w.zeros);
     hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz, dsigma_part,
-                                       bf ? nullptr : d_sigma, prep, st);
+                                       mfma ? nullptr : d_sigma, prep, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route_bwd: dz");
-    if (bf)
+    if (mfma)
         e = mfma_route_bwd_mm(*shape, prep, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
                               (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart), st);
     else

@@ -1,5 +1,5 @@
-// Contractions on v_mfma_f32_16x16x4_f32: float mode (which is checked to 1e-5), and the router logits of the
-// bfloat16 shapes that the bfloat16 router kernels do not take.  Any sizes, any alignment.
+// Contractions on v_mfma_f32_16x16x4_f32: float mode (which is checked to 1e-5), and the router products of the
+// bfloat16 shapes and operands that the bfloat16 router kernels do not take.  Any sizes, any alignment.
 //
 // The instruction adds its four products in index order, each with one rounding (checked on the device against
 // a chain of fmaf, 512000 of 512000 results equal), so a sum here is the plain index-order chain of fused
@@ -501,9 +501,13 @@ hipError_t f32_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const
     return run_layers<float>(b, s.E, st);
 }
 
-hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
-                            void* dx, int dx_accumulate, float* wpart, hipStream_t st) {
-    const int d = s.d_model, E = s.E, T = s.T;
+namespace {
+
+template <typename TA>
+hipError_t route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw, void* dx,
+                        int dx_accumulate, float* wpart, hipStream_t st) {
+    const int d = s.d_model, E = s.E, T = s.T, ez = dz_stride(s);
+    const size_t el = sizeof(TA);
     // d_w_router = dz^T x.  The tokens are cut into chunks of at least 128 (two stages of a 32 x 32 tile) so that
     // the chunks' tiles fill the chip; the partial products are added in order.
     const int tiles = cdiv(E, 32) * cdiv(d, 32);
@@ -511,10 +515,10 @@ hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w
     const int chunk = cdiv(cdiv(T, nchunks), 64) * 64;
     const int used = cdiv(T, chunk);
     Args a = {};
-    a.A = dz; a.lda = E; a.B = x; a.ldb = d; a.M = E; a.N = d; a.K = T; a.chunk = chunk;
+    a.A = dz; a.lda = ez; a.B = x; a.ldb = d; a.M = E; a.N = d; a.K = T; a.chunk = chunk;
     a.out0 = used > 1 ? wpart : dw; a.ldo = d; a.out_stride = (long long)E * d;
-    a.vec_a = aligned(dz, E, 4); a.vec_b = aligned(x, d, 4); a.vec_o = aligned(a.out0, d, 4);
-    hipError_t e = run_layers<float>(a, used, st);
+    a.vec_a = aligned(dz, ez, el); a.vec_b = aligned(x, d, el); a.vec_o = aligned(a.out0, d, 4);
+    hipError_t e = run_layers<TA>(a, used, st);
     if (e != hipSuccess) return e;
     if (used > 1) {
         const size_t n = (size_t)E * d;
@@ -523,10 +527,18 @@ hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w
         if (e != hipSuccess) return e;
     }
     Args b = {};                                       // dx (+)= dz W
-    b.A = dz; b.lda = E; b.B = w; b.ldb = d; b.M = T; b.N = d; b.K = E;
+    b.A = dz; b.lda = ez; b.B = w; b.ldb = d; b.M = T; b.N = d; b.K = E;
     b.out0 = dx; b.ldo = d; b.add = dx_accumulate;
-    b.vec_a = aligned(dz, E, 4); b.vec_b = aligned(w, d, 4); b.vec_o = aligned(dx, d, 4);
-    return run_rows<float, true, kStore>(b, d, st);
+    b.vec_a = aligned(dz, ez, el); b.vec_b = aligned(w, d, el); b.vec_o = aligned(dx, d, el);
+    return run_rows<TA, true, kStore>(b, d, st);
+}
+
+}  // namespace
+
+hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
+                            void* dx, int dx_accumulate, float* wpart, hipStream_t st) {
+    return s.dtype == UNIPOOL_BF16 ? route_bwd_mm<bf16>(s, x, w, dz, dw, dx, dx_accumulate, wpart, st)
+                                   : route_bwd_mm<float>(s, x, w, dz, dw, dx, dx_accumulate, wpart, st);
 }
 
 }  // namespace unipool

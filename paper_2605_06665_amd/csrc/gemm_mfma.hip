@@ -1229,6 +1229,16 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
     return run_ptq(b, st);
 }
 
+bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx) {
+    // Pools that are a multiple of 8 have their operands aligned to 16 bytes.  Others may come at any address: the float
+    // kernel reads those value by value; it also takes up to 256 tokens, where its launches are the shorter ones (all of
+    // the entry point, us, this path / the float one: 3 experts, d 256, 16 tokens 20 / 16; 90 experts, d 832, 256 tokens
+    // 31 / 23, 1024 tokens 32 / 32; 500 experts, d 1536, 256 tokens 54 / 51, 512 tokens 56 / 63).
+    if (s.dtype != UNIPOOL_BF16) return false;
+    if (s.E % 8 == 0) return true;
+    return s.T > 256 && (((uintptr_t)x | (uintptr_t)w | (uintptr_t)dx) & 15) == 0;
+}
+
 RouteBwdPrep mfma_route_bwd_prep(const unipool_shape& s, const void* x, int32_t* tile_meta, void* zeros) {
     // d_w_router = dz^T x: the token axis is cut into chunks whose partial products are summed in a fixed order;
     // as many chunks as give every CU one output tile in a single round

@@ -61,7 +61,7 @@ hipError_t router_fused(const unipool_shape& s, const void* x, const void* w, fl
 bool router_few_supported(const unipool_shape& s);
 hipError_t router_few_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);
 
-// ---- gemm_f32.hip: float contractions on the matrix cores, any sizes; logits also of bfloat16 operands -----
+// ---- gemm_f32.hip: float contractions on the matrix cores, any sizes; the router's also of bfloat16 operands -----
 hipError_t f32_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);
 // slot_of_row != nullptr: x_perm is the un-permuted x and row r reads token slot_of_row[r] / k of it
 hipError_t f32_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets, const void* wgu,
@@ -99,6 +99,7 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
                           const void* const* dy_l, const int32_t* const* offsets_l,
                           float* dwgu, float* dwd, int accumulate, const void* zeros,
                           hipStream_t st);
+bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx);
 RouteBwdPrep mfma_route_bwd_prep(const unipool_shape& s, const void* x, int32_t* tile_meta, void* zeros);
 hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, const void* w, const void* dz,
                              float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,

@@ -1,6 +1,7 @@
 """GPU: the sum over the router gradient's partial products, four values at a time where the output is aligned to 16
 bytes, one otherwise: numbers of parts on both sides of a group of eight, bitwise the same result from both forms.
-dx of the router added to what is there: the sum is rounded once."""
+dx of the router added to what is there: the sum is rounded once.  Operands of pools that are not a multiple of 8 at
+addresses that are not a multiple of 16."""
 import numpy as np
 import pytest
 
@@ -90,3 +91,31 @@ def test_accumulated_dx_is_rounded_once(E, d, T):
     assert float(left.abs().max()) > 0
     assert float(bad.any(dim=1).double().mean()) <= 0.2
     assert float((dx == 0).double().mean()) <= 0.5
+
+
+@pytest.mark.parametrize("E,d,T", [(90, 192, 33), (3, 64, 256), (13, 128, 257), (90, 192, 2049)])
+@pytest.mark.parametrize("shifted", ["x", "w_router", "dx", "all"])
+def test_odd_pools_take_any_alignment(E, d, T, shifted):
+    import torch
+    import paper_2605_06665_amd as U
+    sh, x, wr, z, idx, dgate, ws, dz = _route_bwd_inputs(T, E, d, 2, E + T)
+    dx0 = torch.randn((T, d), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+
+    def place(name, t):
+        if shifted not in (name, "all"):
+            return t.clone(), None
+        buf = torch.full((t.numel() + 2,), float("nan"), dtype=t.dtype, device="cuda")
+        v = buf[1:-1].view(t.shape)
+        v.copy_(t)
+        return v, buf
+
+    px, pw, (pdx, around) = place("x", x)[0], place("w_router", wr)[0], place("dx", dx0)
+    dw, ds = torch.full((E, d), float("nan"), device="cuda"), torch.full((1,), float("nan"), device="cuda")
+    U.route_bwd(sh, px, pw, z, idx, dgate, None, dw, ds, pdx, True, ws)
+    # float sums, and a few values of dz that round the other way (2^-8 of one term)
+    assert rel_err(host(dw), host(dz.T @ x.double())) <= 1e-3
+    want = dx0.double() + dz @ wr.double()
+    assert float((pdx.double() - want).norm() / want.norm()) <= 1.02 * float((want.to(torch.bfloat16).double() - want).norm() / want.norm())
+    assert bool(torch.isfinite(ds).all())
+    if around is not None:
+        assert bool(torch.isnan(around[0])) and bool(torch.isnan(around[-1]))
