@@ -19,7 +19,9 @@
  *   - Every function returns 0 on success or a negative UNIPOOL_E* code.  Arguments
  *     are validated before anything is launched; on error nothing has been written.
  *     unipool_last_error() gives a message for the calling thread's last failure.
- *   - Same inputs give bitwise the same outputs (no floating-point atomics).
+ *   - Same inputs give bitwise the same outputs (no floating-point atomics).  A token's rows of the forward
+ *     pass (logits, picks, gates, expert outputs) do not depend on how many other tokens share the call; sums
+ *     over tokens (psum, the gradients of weights, router and sigma) are added in an order that depends on T.
  *   - dtype UNIPOOL_F32: every floating tensor is float.
  *     dtype UNIPOOL_BF16: tensors marked "act" below are bfloat16; logits, scores,
  *     gates, statistics and all weight gradients are float; products accumulate in

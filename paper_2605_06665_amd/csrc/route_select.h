@@ -46,18 +46,45 @@ __device__ __forceinline__ int group_min_i(int v) {
     return v;
 }
 
+// Of a lane's logits, how many lie below E whatever the lane, for a pool that the one-kernel router runs in its body of
+// nb16 blocks of 16 experts: more experts than the next smaller body holds.
+constexpr int kRouterBodies[] = {2, 4, 6, 8, 12, 16, 24, 32};
+constexpr int route_full(int nb16, int GS) {
+    int below = 0;
+    for (int n : kRouterBodies) {
+        if (nb16 <= n) break;
+        below = n;
+    }
+    return (16 * below + 1) / GS;
+}
+
+// Sum of squares of a lane's logits.  Every rounding is written out, since the compiler would contract multiplication
+// and addition differently from kernel to kernel and a token's gates must not depend on which of them ran: the squares
+// of the first `full` logits (none or at least two) are added unrounded, the others after rounding.
+template <int GS, int VPL>
+__device__ __forceinline__ float sum_of_squares(const float (&z)[VPL], int sl, int E, int full) {
+#pragma clang fp contract(off)
+    float q[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; i++) q[i] = (sl + GS * i < E) ? z[i] * z[i] : 0.f;
+    float ss = full >= 2 ? __builtin_fmaf(z[0], z[0], q[1]) : q[0] + q[1];
+#pragma unroll
+    for (int i = 2; i < VPL; i++) ss = i < full ? __builtin_fmaf(z[i], z[i], ss) : ss + q[i];
+    return ss;
+}
+
 // Lane s of the group holds the logits z[i] of experts s + GS*i (anything past E).  Adds the token's
 // scores to the lane's running sums ps[], picks the k largest logits (ties: lower index), counts
 // them in cnt[] (LDS, one word per expert) and writes index and gate (= score) of every pick.
 // softmax = false: score_i = sigma_c max(0, z_i) / (||z|| + eps)   (NormRouter, Eq. 7)
 // softmax = true : score_i = exp(z_i - max z) / sum_j exp(z_j - max z)
-// `live` and `softmax` are uniform inside the group; a dead group takes part in the exchanges and writes
+// full: as in sum_of_squares.  `live` and `softmax` are uniform inside the group; a dead group takes part in the exchanges and writes
 // nothing.  Each round takes the largest logit left: its value by a maximum over the group, then the lowest
 // expert index that holds this value by a minimum.  Logits are taken to be finite (they are sums of finite
 // products); a row with fewer than k finite logits gets indices below E all the same, possibly repeated.
 template <int GS, int VPL>
 __device__ __forceinline__ void route_select(const float (&z)[VPL], int sl, int E, int k, float sigma_c,
-                                             float eps, bool softmax, bool live, size_t t,
+                                             float eps, bool softmax, int full, bool live, size_t t,
                                              int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, int* cnt,
                                              float (&ps)[VPL]) {
     const auto add = [](float a, float b) { return a + b; };
@@ -67,9 +94,7 @@ __device__ __forceinline__ void route_select(const float (&z)[VPL], int sl, int 
     for (int i = 0; i < VPL; i++) zz[i] = (sl + GS * i < E) ? z[i] : -INFINITY;
     float scale, zmax = 0.f;
     if (!softmax) {
-        float ss = 0.f;
-#pragma unroll
-        for (int i = 0; i < VPL; i++) ss += (sl + GS * i < E) ? z[i] * z[i] : 0.f;
+        float ss = sum_of_squares<GS, VPL>(z, sl, E, full);
         ss = group_reduce_f<GS>(ss, add);
         scale = sigma_c / (sqrtf(ss) + eps);
         if (live) {

@@ -15,7 +15,7 @@ constexpr int kTokPerWave = kRouterTokensPerBlock / kWavesPerBlock;
 // reduction over blocks and its launch (4.6 us).  The sums run over the token groups of a wavefront, then over the
 // wavefronts, in a fixed order.
 constexpr int kOneWaves = 16;
-template <int GS, int VPL>
+template <int GS, int VPL, int FULL>
 __global__ __launch_bounds__(64 * kOneWaves) void route_select_one_kernel(
     const float* __restrict__ logits, int T, int E, int k, float sigma_c, float eps, int softmax,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, int32_t* __restrict__ counts, float* __restrict__ psum) {
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64 * kOneWaves) void route_select_one_kernel(
             const int e = sl + GS * i;
             z[i] = (e < E) ? zr[e] : 0.f;
         }
-        route_select<GS, VPL>(z, sl, E, k, sigma_c, eps, softmax != 0, t < T, (size_t)t, topk_idx, topk_gate, lds_cnt, ps);
+        route_select<GS, VPL>(z, sl, E, k, sigma_c, eps, softmax != 0, FULL, t < T, (size_t)t, topk_idx, topk_gate, lds_cnt, ps);
     }
 #pragma unroll
     for (int i = 0; i < VPL; i++) {
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(64 * kOneWaves) void route_select_one_kernel(
 // time (64 / GS tokens per wavefront in flight); lane s of the group holds the logits of experts
 // s, s + GS, ... (VPL of them, E <= GS * VPL).  Partial sums leave the block in a fixed order, so the
 // final reduction over blocks is deterministic.
-template <int GS, int VPL>
+template <int GS, int VPL, int FULL>
 __global__ __launch_bounds__(256) void route_score_topk_kernel(
     const float* __restrict__ logits, int T, int E, int k, float sigma_c, float eps, int softmax,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate,
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void route_score_topk_kernel(
 #pragma unroll
         for (int i = 0; i < VPL; i++) z[i] = zn[i];
         if (tt + TPW < tok_per_wave) fetch(t + TPW, zn);          // the next token's logits, a round ahead
-        route_select<GS, VPL>(z, sl, E, k, sigma_c, eps, softmax != 0, t < T, (size_t)t, topk_idx, topk_gate, lds_cnt, ps);
+        route_select<GS, VPL>(z, sl, E, k, sigma_c, eps, softmax != 0, FULL, t < T, (size_t)t, topk_idx, topk_gate, lds_cnt, ps);
     }
     // score sums: over the token groups of the wavefront (fixed order), then over the wavefronts
 #pragma unroll
@@ -279,28 +279,39 @@ __global__ __launch_bounds__(256) void dsigma_finalize_kernel(const float* __res
 
 }  // namespace
 
+namespace {
+
+// Calls f with lanes per token, logits per lane and `full` (sum_of_squares) of the selection kernels: a pool that the
+// one-kernel router takes beyond a few tokens gets the sums of its body there, every other pool rounds all squares.
+template <class F>
+void with_select_form(const unipool_shape& s, F f) {
+    using std::integral_constant;
+    const int full = router_fused_supported(s) ? route_full(cdiv(s.E, 16), s.E <= 256 ? 16 : 32) : 0;
+    auto pick = [&](auto gs, auto vpl, auto... fulls) {
+        if (!((full == fulls ? (f(gs, vpl, fulls), true) : false) || ...)) f(gs, vpl, integral_constant<int, 0>{});
+    };
+    using I2 = integral_constant<int, 2>; using I4 = integral_constant<int, 4>; using I6 = integral_constant<int, 6>;
+    using I8 = integral_constant<int, 8>; using I12 = integral_constant<int, 12>;
+    using I16 = integral_constant<int, 16>; using I32 = integral_constant<int, 32>;
+    if (s.E <= 128) pick(I16{}, I8{}, I2{}, I4{}, I6{});
+    else if (s.E <= 256) pick(I16{}, I16{}, I8{}, I12{});
+    else pick(I32{}, I16{}, I8{}, I12{});
+}
+
+}  // namespace
+
 hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, int32_t* topk_idx,
                                    float* topk_gate, int32_t* counts, float* psum,
                                    int32_t* cnt_part, float* psum_part, float* wpart, hipStream_t st) {
-    // lanes per token and logits per lane by pool size
-#define UNIPOOL_SELECT(KERNEL, GRID, THREADS, ...)                                                           \
-    do {                                                                                                     \
-        if (s.E <= 128)                                                                                      \
-            KERNEL<16, 8><<<GRID, THREADS, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,   \
-                                                    topk_idx, topk_gate, __VA_ARGS__);                       \
-        else if (s.E <= 256)                                                                                 \
-            KERNEL<16, 16><<<GRID, THREADS, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,  \
-                                                     topk_idx, topk_gate, __VA_ARGS__);                      \
-        else                                                                                                 \
-            KERNEL<32, 16><<<GRID, THREADS, 0, st>>>(logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router,  \
-                                                     topk_idx, topk_gate, __VA_ARGS__);                      \
-    } while (0)
     // A pick takes a wavefront about 0.2 us of a SIMD's issue slots, and a launch with the sum over the blocks 6 us:
     // one workgroup (four wavefronts per SIMD) up to 32 picks per SIMD.  512 experts, k = 8: 4 tokens (16 picks in
     // all) 8 us, 48 tokens (192) 21 us in one workgroup.
     const int tpw = s.E <= 256 ? 4 : 2;                       // tokens of a wavefront at a time
     if (s.T <= 128 && cdiv(s.T, tpw) * s.k <= 128) {
-        UNIPOOL_SELECT(route_select_one_kernel, 1, 64 * kOneWaves, counts, psum);
+        with_select_form(s, [&](auto gs, auto vpl, auto full) {
+            route_select_one_kernel<gs(), vpl(), full()><<<1, 64 * kOneWaves, 0, st>>>(
+                logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router, topk_idx, topk_gate, counts, psum);
+        });
         return hipGetLastError();
     }
     // up to 64 tokens: as many workgroups as there are four wavefronts' worth of tokens; their partial sums
@@ -312,8 +323,10 @@ hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, 
         psum_part = wpart;
         cnt_part = reinterpret_cast<int32_t*>(wpart + (size_t)nblocks * s.E);
     }
-    UNIPOOL_SELECT(route_score_topk_kernel, nblocks, 256, cnt_part, psum_part, per_wave);
-#undef UNIPOOL_SELECT
+    with_select_form(s, [&](auto gs, auto vpl, auto full) {
+        route_score_topk_kernel<gs(), vpl(), full()><<<nblocks, 256, 0, st>>>(
+            logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router, topk_idx, topk_gate, cnt_part, psum_part, per_wave);
+    });
     route_finalize_kernel<<<s.E, 256, 0, st>>>(cnt_part, psum_part, nblocks, s.E, counts, psum);
     return hipGetLastError();
 }

@@ -225,7 +225,7 @@ __device__ __forceinline__ void rf_body(const RouterArgs& a, char* smem) {
                 const int e = sl + GS * i;
                 z[i] = (e < E) ? zr[e] : 0.f;
             }
-            route_select<GS, VPL>(z, sl, E, a.k, a.sigma_c, a.eps, a.softmax != 0, lr < rows, (size_t)(t0 + lr),
+            route_select<GS, VPL>(z, sl, E, a.k, a.sigma_c, a.eps, a.softmax != 0, route_full(NB16, GS), lr < rows, (size_t)(t0 + lr),
                                   a.topk_idx, a.topk_gate, lds_cnt + blk * E, ps);
         }
 #pragma unroll
