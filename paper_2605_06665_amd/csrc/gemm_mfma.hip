@@ -658,11 +658,10 @@ struct PtqArgs {
     float* out;
     long long out_stride;        // elements between experts
     int accumulate;
-    int stream;                  // the output is larger than the caches and nobody reads it soon
     const void* zeros;           // >= 16 readable zero bytes
 };
 
-template <int BK, int NS, int NW>
+template <int BK, int NS, int NW, bool STREAM>
 __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     // 256 x 256 float tile, 2 x 4 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16 (at the card's power
     // limit it sustains about a sixth more than the 32x32x16 form): 8 x 4 accumulator blocks of 16 x 16.
@@ -965,9 +964,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         // Accumulating, the old values are fetched a pass of 32 rows ahead (the fragments' registers are free by
         // now): 8 KiB per wavefront in flight at any time, where fetching four rows, adding and storing them
         // in turn left the reads waiting for each other (one layer's gradients of 90 experts of 832 x 1472, 200 rows
-        // each: 945 -> 780 us).  Gradients of a pool are streamed past the caches, old values too: the operands that
-        // neighbouring tiles share stay there (of these 780, 3 % of the step; 16 experts of 768 x 2048, 188 rows: 100 ->
-        // 91 us a layer).  The router's partial sums are read again by the next launch and stay cached.
+        // each: 945 -> 780 us).  STREAM: the output is larger than the caches, old and new values go past them, and the
+        // operands that neighbouring tiles share stay there (the whole backward call of these 90 experts with 256 tokens
+        // 852 -> 780 us).  A choice at run time would not do: the compiler merges the two forms of an access into the
+        // plain one.
         constexpr int ITS = 32 / RPI;
         const bool add_vec = vec_ok && g.accumulate;
         const int c4 = (lane % LPR) * 4, j = jw + c4;
@@ -978,7 +978,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
                 const int i = m0 + wm * 128 + a2 * 32 + it * RPI + lane / LPR;
                 if (i < g.mdim && j < g.ndim) {
                     const f32x4* src = reinterpret_cast<const f32x4*>(otile + (size_t)i * g.ndim + j);
-                    old[a2 & 1][it] = __builtin_nontemporal_load(src);
+                    if constexpr (STREAM) old[a2 & 1][it] = __builtin_nontemporal_load(src);
+                    else old[a2 & 1][it] = *src;
                 }
             }
         };
@@ -1003,7 +1004,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
                 float* dst = otile + (size_t)i * g.ndim + j;
                 if (vec_ok) {                 // then j + 3 < ndim as well
                     if (add_vec) v += old[a2 & 1][it];
-                    if (g.stream) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+                    if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
                     else *reinterpret_cast<f32x4*>(dst) = v;
                 } else {
                     const float vv[4] = {v[0], v[1], v[2], v[3]};
@@ -1080,8 +1081,9 @@ hipError_t run_xw(GemmArgs a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <bool STREAM>
 hipError_t run_ptq(const PtqArgs& a, hipStream_t st) {
-    auto kern = gemm_ptq_kernel<kPtqBK, kPtqNS, kPtqWaves>;
+    auto kern = gemm_ptq_kernel<kPtqBK, kPtqNS, kPtqWaves, STREAM>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1216,17 +1218,22 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
                           float* dwgu, float* dwd, int accumulate, const void* zeros,
                           hipStream_t st) {
     const int d = s.d_model, f = s.d_ff;
+    // Smaller gradients are still in the last-level cache (256 MB) when the next layer adds to them.  One layer's whole
+    // backward call, k = 2, plain / streamed, us: 16 experts of 768 x 1024 (151 MB), 256 tokens 106 / 124, 4096 tokens
+    // 214 / 207; 14 experts of 1024 x 1024 (176 MB) 147 / 138 and 224 / 208; 64 experts of 768 x 2048 (1.2 GB) 669 / 608
+    // and 770 / 712.
+    const bool stream = 12ll * s.E * d * f > (160ll << 20);
     PtqArgs a = {};    // d_w_gate_up[e][n][c] = sum d_act[row][n] * x_perm[row][c]
     a.n_layers = n_layers; a.P = d_act_l; a.Q = x_perm_l; a.off = offsets_l;
     a.E = s.E; a.mdim = 2 * f; a.ndim = d; a.m_tiles = cdiv(2 * f, 256); a.n_tiles = cdiv(d, 256);
-    a.out = dwgu; a.out_stride = 2LL * f * d; a.accumulate = accumulate; a.stream = 1; a.zeros = zeros;
-    hipError_t e = run_ptq(a, st);
+    a.out = dwgu; a.out_stride = 2LL * f * d; a.accumulate = accumulate; a.zeros = zeros;
+    hipError_t e = stream ? run_ptq<true>(a, st) : run_ptq<false>(a, st);
     if (e != hipSuccess) return e;
     PtqArgs b = {};    // d_w_down[e][c][n] = sum dy[row][c] * h[row][n]
     b.n_layers = n_layers; b.P = dy_l; b.Q = h_l; b.off = offsets_l;
     b.E = s.E; b.mdim = d; b.ndim = f; b.m_tiles = cdiv(d, 256); b.n_tiles = cdiv(f, 256);
-    b.out = dwd; b.out_stride = (long long)d * f; b.accumulate = accumulate; b.stream = 1; b.zeros = zeros;
-    return run_ptq(b, st);
+    b.out = dwd; b.out_stride = (long long)d * f; b.accumulate = accumulate; b.zeros = zeros;
+    return stream ? run_ptq<true>(b, st) : run_ptq<false>(b, st);
 }
 
 bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx) {
@@ -1268,7 +1275,7 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, c
     a.off = (const int32_t* const*)(tab + 2);
     a.E = used; a.mdim = ez; a.ndim = d; a.m_tiles = cdiv(ez, 256); a.n_tiles = cdiv(d, 256);
     a.out = wpart; a.out_stride = (long long)ez * d; a.accumulate = 0; a.zeros = zeros;
-    hipError_t e = run_ptq(a, st);
+    hipError_t e = run_ptq<false>(a, st);
     if (e != hipSuccess) return e;
     const size_t n = (size_t)E * d;                 // a multiple of 64, as d is
     const int n_dsigma = cdiv(T, kRouterTokensPerBlock);
