@@ -11,7 +11,9 @@
 //     ahead, three to six with many wavefronts per SIMD);
 //   * weights go straight from memory to registers.  A load covers 8 columns x 128 bytes, whole cache lines (16 columns
 //     x 64 bytes, the layout the MFMA A operand wants, reached 5.2 TB/s where this reached 5.8), and a rotation of half
-//     of the lanes by eight turns two of them into two A operands;
+//     of the lanes by eight turns two of them into two A operands.  Each weight is used once, so the loads are streaming
+//     loads (5.8 -> 6.3 TB/s; they serve pools that fit the caches too: 16 experts of 768 x 2048, k = 1, 16 tokens 22.9 ->
+//     21.6 us);
 //   * activation fragments (the B operand) come the same way, up to 32 rows per pass over the weights; rows past
 //     the expert's last repeat it, so they add no cache lines.
 // Every workgroup finds the experts with rows by itself (one pass over the offsets), which costs less than
@@ -49,7 +51,7 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
 }
 
 // One task: rows row0 .. row0 + rows - 1 (at most 16 R) of an expert against columns c0 .. c0 + 15.
-template <bool GATE_UP, bool STREAM, int R, int D>
+template <bool GATE_UP, int R, int D>
 __device__ __forceinline__ void few_task(const FewArgs& a, const bf16* We, int c0, int row0, int rows, int lane) {
     constexpr int NF = GATE_UP ? 2 : 1;
     const int l16 = lane & 15, lg = lane >> 4;
@@ -64,7 +66,7 @@ __device__ __forceinline__ void few_task(const FewArgs& a, const bf16* We, int c
 #pragma unroll
     for (int f = 0; f < NF; f++) wp[f] = We + (size_t)(f * a.up_rows + c0 + (lane & 7)) * a.K + 8 * few_chunk(lane);
     f32x4 acc[NF][R];
-    few_reduce<NF, R, D, STREAM>(wp, (size_t)8 * a.K, xp, a.K / 64, acc);
+    few_reduce<NF, R, D, true>(wp, (size_t)8 * a.K, xp, a.K / 64, acc);
     // acc[f][r][i] = C[row 16 r + l16][column c0 + 4 lg + i]
 #pragma unroll
     for (int r = 0; r < R; r++) {
@@ -85,7 +87,7 @@ __device__ __forceinline__ void few_task(const FewArgs& a, const bf16* We, int c
 }
 
 // RM: most row fragments per pass over an expert's weights, D1 / DM: steps in flight with one / RM fragments
-template <bool GATE_UP, bool STREAM, int WAVES, int RM, int D1, int DM>
+template <bool GATE_UP, int WAVES, int RM, int D1, int DM>
 __global__ __launch_bounds__(64 * WAVES) void ffn_few_kernel(const FewArgs a) {
     constexpr int kThreads = 64 * WAVES;
     __shared__ int list_e[kFewMaxE], list_r0[kFewMaxE], list_n[kFewMaxE];
@@ -129,22 +131,22 @@ __global__ __launch_bounds__(64 * WAVES) void ffn_few_kernel(const FewArgs a) {
         const bf16* We = a.W + (long long)e * a.w_stride;
         for (int c = 0; c < n; c += 16 * RM) {
             const int rows = min(n - c, 16 * RM);
-            if (RM == 1 || rows <= 16) few_task<GATE_UP, STREAM, 1, D1>(a, We, c0, r0 + c, rows, lane);
-            else few_task<GATE_UP, STREAM, RM, DM>(a, We, c0, r0 + c, rows, lane);
+            if (RM == 1 || rows <= 16) few_task<GATE_UP, 1, D1>(a, We, c0, r0 + c, rows, lane);
+            else few_task<GATE_UP, RM, DM>(a, We, c0, r0 + c, rows, lane);
         }
     }
 }
 
 // One wavefront per workgroup and task, D1 (D2) steps in flight with one (two) row fragments.
-template <bool GATE_UP, bool STREAM, int D1, int D2>
+template <bool GATE_UP, int D1, int D2>
 hipError_t run_one(const FewArgs& a, bool one, int tasks, hipStream_t st) {
-    if (one) ffn_few_kernel<GATE_UP, STREAM, 1, 1, D1, D1><<<tasks, 64, 0, st>>>(a);
-    else ffn_few_kernel<GATE_UP, STREAM, 1, 2, D1, D2><<<tasks, 64, 0, st>>>(a);
+    if (one) ffn_few_kernel<GATE_UP, 1, 1, D1, D1><<<tasks, 64, 0, st>>>(a);
+    else ffn_few_kernel<GATE_UP, 1, 2, D1, D2><<<tasks, 64, 0, st>>>(a);
     return hipGetLastError();
 }
 
-template <bool GATE_UP, bool STREAM>
-hipError_t run_tasks(const FewArgs& a, int tokens, int total_rows, hipStream_t st) {
+template <bool GATE_UP>
+hipError_t run_few(const FewArgs& a, int tokens, int total_rows, hipStream_t st) {
     // tasks if every row had an expert of its own
     const int most = (total_rows < a.E ? total_rows : a.E) * (a.N / 16);
     const int cus = num_cus();
@@ -153,30 +155,25 @@ hipError_t run_tasks(const FewArgs& a, int tokens, int total_rows, hipStream_t s
     // At most one task per SIMD: all registers are its own and as many steps are in flight as they hold, fewer where
     // they would mostly repeat the last step.
     if (most <= 4 * cus) {
-        if (ns < 8) return run_one<GATE_UP, false, 4, 4>(a, one, most, st);
+        if (ns < 8) return run_one<GATE_UP, 4, 4>(a, one, most, st);
         if constexpr (GATE_UP) {
-            if (ns >= 24 || ns % 12 == 0) return run_one<true, STREAM, 12, 8>(a, one, most, st);
+            if (ns >= 24 || ns % 12 == 0) return run_one<true, 12, 8>(a, one, most, st);
         } else {
-            if (ns >= 32 || ns % 16 == 0) return run_one<false, STREAM, 16, 8>(a, one, most, st);
+            if (ns >= 32 || ns % 16 == 0) return run_one<false, 16, 8>(a, one, most, st);
         }
-        return run_one<GATE_UP, STREAM, 8, 6>(a, one, most, st);
+        return run_one<GATE_UP, 8, 6>(a, one, most, st);
     }
     // At most two: half of the registers each.
     if (most <= 8 * cus) {
-        if (ns < 6) return run_one<GATE_UP, false, 4, 4>(a, one, most, st);
-        if (GATE_UP || ns < 8) return run_one<GATE_UP, STREAM, 6, 4>(a, one, most, st);
-        return run_one<false, STREAM, 8, 6>(a, one, most, st);
+        if (ns < 6) return run_one<GATE_UP, 4, 4>(a, one, most, st);
+        if (GATE_UP || ns < 8) return run_one<GATE_UP, 6, 4>(a, one, most, st);
+        return run_one<false, 8, 6>(a, one, most, st);
     }
     const int blocks = cdiv(most, 4) < 4 * cus ? cdiv(most, 4) : 4 * cus;
     constexpr int D1 = GATE_UP ? 4 : 6;
-    if (one) ffn_few_kernel<GATE_UP, STREAM, 4, 1, D1, D1><<<blocks, 256, 0, st>>>(a);
-    else ffn_few_kernel<GATE_UP, STREAM, 4, 2, D1, 3><<<blocks, 256, 0, st>>>(a);
+    if (one) ffn_few_kernel<GATE_UP, 4, 1, D1, D1><<<blocks, 256, 0, st>>>(a);
+    else ffn_few_kernel<GATE_UP, 4, 2, D1, 3><<<blocks, 256, 0, st>>>(a);
     return hipGetLastError();
-}
-
-template <bool GATE_UP>
-hipError_t run_few(const FewArgs& a, int tokens, int total_rows, hipStream_t st) {
-    return run_tasks<GATE_UP, true>(a, tokens, total_rows, st);
 }
 
 }  // namespace
