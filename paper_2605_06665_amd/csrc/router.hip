@@ -304,10 +304,12 @@ hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, 
                                    float* topk_gate, int32_t* counts, float* psum,
                                    int32_t* cnt_part, float* psum_part, float* wpart, hipStream_t st) {
     // A pick takes a wavefront about 0.2 us of a SIMD's issue slots, and a launch with the sum over the blocks 6 us:
-    // one workgroup (four wavefronts per SIMD) up to 32 picks per SIMD.  512 experts, k = 8: 4 tokens (16 picks in
-    // all) 8 us, 48 tokens (192) 21 us in one workgroup.
+    // one workgroup (four wavefronts per SIMD) up to 32 picks per SIMD, while its wavefronts do not have to wait for
+    // the logits of many rounds (36864 of them: 72 tokens of 512 experts, 128 of 288).  Float mode, d_model 64, all of
+    // the entry point, one workgroup / blocks, us: 512 experts, k = 1, 64 tokens 17 / 18, 96 tokens 23 / 18, 128 tokens
+    // 28 / 18; 264 experts, k = 2, 96 tokens 19 / 22; 120 experts, k = 2, 128 tokens 12 / 12.
     const int tpw = s.E <= 256 ? 4 : 2;                       // tokens of a wavefront at a time
-    if (s.T <= 128 && cdiv(s.T, tpw) * s.k <= 128) {
+    if (s.T <= 128 && cdiv(s.T, tpw) * s.k <= 128 && s.T * s.E <= 36864) {
         with_select_form(s, [&](auto gs, auto vpl, auto full) {
             route_select_one_kernel<gs(), vpl(), full()><<<1, 64 * kOneWaves, 0, st>>>(
                 logits, s.T, s.E, s.k, s.sigma * s.c, s.eps, s.router, topk_idx, topk_gate, counts, psum);
