@@ -19,6 +19,7 @@ CASES = [
     (8, 2, 64, 128, "f32"), (5, 3, 37, 65, "f32"), (300, 8, 30, 129, "f32"), (512, 4, 24, 255, "f32"),
     (40, 1, 33, 256, "f32"),
     (512, 1, 64, 72, "bf16"), (512, 1, 64, 73, "bf16"), (288, 2, 64, 128, "f32"), (296, 2, 64, 128, "f32"),
+    (512, 2, 128, 63, "bf16"),
 ]
 
 
