@@ -1,13 +1,12 @@
 // Contractions on v_mfma_f32_16x16x4_f32: float mode (which is checked to 1e-5), and the router products of the
 // bfloat16 shapes and operands that the bfloat16 router kernels do not take.  Any sizes, any alignment.
 //
-// The instruction adds its four products in index order, each with one rounding (checked on the device against
-// a chain of fmaf, 512000 of 512000 results equal), so a sum here is the plain index-order chain of fused
-// multiply-adds and does not depend on tile sizes; no kernel in this file cuts a reduction except the router's
-// weight gradient over the tokens.
+// The instruction adds its four products in index order, each with one rounding (test_gpu_f32_chain.py compares logits
+// with a chain of fused multiply-adds, bit for bit), so a sum here is the plain index-order chain and does not depend on
+// tile sizes; no kernel in this file cuts a reduction except the router's weight gradient over the tokens.
 //
 // A workgroup is four wavefronts (2 x 2) of WT x WT outputs, WT = 32 or 16.  A 16x16x4 step keeps the matrix
-// core busy for 32 cycles (157 TFLOP/s for the card), eight times the share of a bfloat16 step, so what is hidden is latency:
+// core busy for 32 cycles (157 TFLOP/s for the card, a sixteenth of what bfloat16 steps reach), so what is hidden is latency:
 // tiles pass through registers (the next stage is requested before the current one is multiplied) into two LDS
 // buffers, one barrier per stage.  Both operands are laid out K-contiguous in LDS whatever they are in memory,
 // and the 16 indices of a chunk are stored as a 4 x 4 transpose (index k at place 4 (k mod 4) + k / 4): the 16
