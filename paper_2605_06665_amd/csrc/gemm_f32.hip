@@ -404,22 +404,23 @@ hipError_t run_rows_wt(Args a, int n_cols, hipStream_t st) {
 // n_cols: columns of the tile axis (both halves for kSwigluFwd)
 template <typename TA, bool BTR, Epilogue EPI>
 hipError_t run_rows(const Args& a, int n_cols, hipStream_t st) {
-    if (EPI == kSwigluFwd || big_tiles(cdiv(a.M, 64), n_cols)) return run_rows_wt<TA, 32, BTR, EPI>(a, n_cols, st);
-    if constexpr (EPI != kSwigluFwd) return run_rows_wt<TA, 16, BTR, EPI>(a, n_cols, st);
-    return hipErrorUnknown;
+    if constexpr (EPI == kSwigluFwd) return run_rows_wt<TA, 32, BTR, EPI>(a, n_cols, st);
+    else return big_tiles(cdiv(a.M, 64), n_cols) ? run_rows_wt<TA, 32, BTR, EPI>(a, n_cols, st)
+                                                 : run_rows_wt<TA, 16, BTR, EPI>(a, n_cols, st);
+}
+template <typename TA, int WT>
+hipError_t run_layers_wt(Args a, int groups, hipStream_t st) {
+    a.m_tiles = cdiv(a.M, 2 * WT);
+    a.n_tiles = cdiv(a.N, 2 * WT);
+    const long long grid = (long long)groups * a.m_tiles * a.n_tiles;
+    if (grid >= (1LL << 31)) return hipErrorInvalidValue;
+    gemm_f32_kernel<TA, WT, true, true, kFloat, true><<<(unsigned)grid, kThreads, 0, st>>>(a);
+    return hipGetLastError();
 }
 template <typename TA>
-hipError_t run_layers(Args a, int groups, hipStream_t st) {
-    if (big_tiles((long long)groups * cdiv(a.M, 64), a.N)) {
-        a.m_tiles = cdiv(a.M, 64); a.n_tiles = cdiv(a.N, 64);
-        gemm_f32_kernel<TA, 32, true, true, kFloat, true>
-            <<<(unsigned)((long long)groups * a.m_tiles * a.n_tiles), kThreads, 0, st>>>(a);
-    } else {
-        a.m_tiles = cdiv(a.M, 32); a.n_tiles = cdiv(a.N, 32);
-        gemm_f32_kernel<TA, 16, true, true, kFloat, true>
-            <<<(unsigned)((long long)groups * a.m_tiles * a.n_tiles), kThreads, 0, st>>>(a);
-    }
-    return hipGetLastError();
+hipError_t run_layers(const Args& a, int groups, hipStream_t st) {
+    return big_tiles((long long)groups * cdiv(a.M, 64), a.N) ? run_layers_wt<TA, 32>(a, groups, st)
+                                                             : run_layers_wt<TA, 16>(a, groups, st);
 }
 
 }  // namespace
