@@ -964,7 +964,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         // Accumulating, the old values are fetched a pass of 32 rows ahead (the fragments' registers are free by
         // now): 8 KiB per wavefront in flight at any time, where fetching four rows, adding and storing them
         // in turn left the reads waiting for each other (one layer's gradients of 90 experts of 832 x 1472, 200 rows
-        // each: 945 -> 780 us).  STREAM: the output is larger than the caches, old and new values go past them, and the
+        // each: 945 -> 780 us, streamed 752).  STREAM: the output is larger than the caches, old and new values go past them, and the
         // operands that neighbouring tiles share stay there (the whole backward call of these 90 experts with 256 tokens
         // 852 -> 780 us).  A choice at run time would not do: the compiler merges the two forms of an access into the
         // plain one.

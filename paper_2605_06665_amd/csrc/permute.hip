@@ -227,7 +227,8 @@ __global__ __launch_bounds__(64) void permute_copy_scalar_kernel(const uint32_t*
     }
 }
 
-// A few tokens (up to kSmallTokens) in one launch instead of three (kernel time 13.5 -> 2.2 us at 4 tokens of 192 experts): every workgroup
+// A few tokens (up to kSmallTokens) in one launch instead of three (launches back to back in a graph: 192 experts, k = 2,
+// d_model 1536, 1 token 7.3 -> 2.8 us, 256 tokens 8.1 -> 3.6; 512 experts, k = 8, 256 tokens 12.8 -> 5.6): every workgroup
 // builds the masks of all chunks, the expert offsets and the chunk bases for itself in LDS, then places its own four
 // tokens; without a copy a single workgroup writes the index maps of all tokens.
 constexpr int kSmallTokens = 64 * kChunkWaves;      // one chunk per wavefront
