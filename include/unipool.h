@@ -87,8 +87,9 @@ int unipool_version(void);
 
 /*
  * Which kernels a shape gets.  In bfloat16 mode the contractions run on the bfloat16 matrix cores (MFMA), except
- * the router logits when E is not a multiple of 8; those, and everything in float mode, run on the float matrix
- * cores, which are slower.
+ * the router logits when E is not a multiple of 8 and, up to 256 tokens or with operands that are not aligned to
+ * 16 bytes, the router backward then; those, and everything in float mode, run on the float matrix cores, which
+ * are slower.
  * Returns a bit mask: bit 0 the expert GEMMs use bfloat16 MFMA kernels, bit 1 all router contractions do, bit 2 the
  * router can run as one fused kernel (logits, scores, top-k, statistics: d_model a multiple of 128, E a multiple
  * of 8 and at most 512; calls with a few tokens spread the logits over more compute units instead).  Negative on
