@@ -127,6 +127,13 @@ int need_ws(const unipool_shape* s, void* ws, size_t ws_bytes, const char* fn) {
     return UNIPOOL_OK;
 }
 
+// Second tile table of an FFN entry point, in the area of the router gradient's partial products (which no FFN entry point uses), or
+// null where it does not fit there.
+int32_t* extra_table(const unipool_shape& s, const WsLayout& w, void* ws) {
+    const size_t need = (64 + 4 * ((size_t)s.T * s.k / 128 + 2 * (size_t)s.E)) * sizeof(int32_t);
+    return need <= w.total - w.wpart ? (int32_t*)((char*)ws + w.wpart) : nullptr;
+}
+
 #define REQUIRE_PTR(p)                                                                  \
     if (!(p)) return unipool::set_error(UNIPOOL_EINVAL, "%s: argument %s is NULL", __func__, #p)
 #define PROLOGUE()                                                            \
@@ -257,7 +264,7 @@ int unipool_expert_ffn_fwd(const unipool_shape* shape, const void* x_perm,
         e = few_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st);
     else if (mfma_ffn_supported(*shape))
         e = mfma_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h,
-                         y_perm, (int32_t*)((char*)ws + w.tile_meta), st);
+                         y_perm, (int32_t*)((char*)ws + w.tile_meta), extra_table(*shape, w, ws), st);
     else
         e = f32_ffn_fwd(*shape, x_perm, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h,
                           y_perm, st);
@@ -279,7 +286,7 @@ int unipool_expert_ffn_fwd_gather(const unipool_shape* shape, const void* x, con
         e = few_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st, slot_of_row);
     else if (mfma_ffn_supported(*shape))
         e = mfma_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm,
-                         (int32_t*)((char*)ws + w.tile_meta), st, slot_of_row);
+                         (int32_t*)((char*)ws + w.tile_meta), extra_table(*shape, w, ws), st, slot_of_row);
     else
         e = f32_ffn_fwd(*shape, x, expert_offsets, w_gate_up, w_down, act_a, act_b, act_h, y_perm, st,
                           slot_of_row);
@@ -301,7 +308,7 @@ int unipool_expert_ffn_recompute(const unipool_shape* shape, const void* x_perm,
         e = few_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h, st);
     else if (mfma_ffn_supported(*shape))
         e = mfma_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h,
-                             (int32_t*)((char*)ws + w.tile_meta), st);
+                             (int32_t*)((char*)ws + w.tile_meta), extra_table(*shape, w, ws), st);
     else
         e = f32_ffn_gate_up(*shape, x_perm, expert_offsets, w_gate_up, act_a, act_b, act_h, st);
     return check_hip(e, "unipool_expert_ffn_recompute");
@@ -327,7 +334,7 @@ int unipool_expert_ffn_bwd(const unipool_shape* shape, const void* dy_perm, cons
     hipError_t e;
     if (mfma)
         e = mfma_ffn_dgrad(*shape, dy_perm, act_a, act_b, expert_offsets, w_gate_up, w_down, dx_perm,
-                           d_act, (int32_t*)(base + w.tile_meta), st);
+                           d_act, (int32_t*)(base + w.tile_meta), extra_table(*shape, w, ws), st);
     else
         e = f32_ffn_dgrad(*shape, dy_perm, act_a, act_b, expert_offsets, w_gate_up, w_down, dx_perm,
                             d_act, st);

@@ -163,21 +163,103 @@ constexpr int kPairSpins = 48;      // polls of the partner's arrival, roughly a
 constexpr int kPairCap = 2048;      // meeting counters behind the tile table
 constexpr int kPairMinK = 4096;     // tiles this long are worth the meeting (its cost: a few microseconds)
 
-constexpr int kXwWaves = 8;       // wavefronts of a gemm_xw workgroup (256 x 256 tiles)
-constexpr int kXwThreads = kXwWaves * 64;
+// The list of tiles as one workgroup walks it: persistent workgroups, static schedule.  Every wavefront works the list
+// out by itself (no counter, no hand-over through LDS), so the next tile is known while the current one runs and its first
+// stages are requested before the epilogue.
+//   * Workgroup b belongs to XCD b mod 8 (workgroups are dealt round-robin to the XCDs; if a
+//     device dealt them otherwise, only the L2 locality below would suffer).  Each XCD has its own
+//     L2, so the tile list is cut into eight contiguous parts: the row tiles of an expert, which
+//     share the expert's weights, and its column tiles, which share its rows, stay on one L2.
+//   * Inside a part, round n gives the next P tiles to the P workgroups of the XCD, rotated by n,
+//     so that no workgroup keeps the same position inside the experts' tile groups.  The tile
+//     table lists the experts of a part in descending order of rows: the workgroups of an XCD
+//     work on tiles of nearly equal length at any time and end together.
+struct TileWalk {
+    bool flat, use_pairs;
+    int n_mt, G, per_group, per_xcd, xcd, slot, P, lt_end, round;
+    __device__ __forceinline__ explicit TileWalk(const GemmArgs& g) {
+        flat = g.flat_rows > 0;
+        n_mt = flat ? (g.flat_rows + g.flat_bm - 1) / g.flat_bm : g.tile_meta[0];
+        G = flat ? 1 : g.group_m;
+        per_group = G * g.n_tiles_n;
+        const int total = ((n_mt + G - 1) / G) * per_group;
+        per_xcd = (total + kNumXcd - 1) / kNumXcd;
+        xcd = blockIdx.x % kNumXcd;
+        slot = blockIdx.x / kNumXcd;
+        P = gridDim.x / kNumXcd;                 // workgroups per XCD (the grid is a multiple of 8)
+        lt_end = min(total, (xcd + 1) * per_xcd);
+        use_pairs = !flat && G == 2 && (per_group & 1) == 0 && g.pair_cnt != nullptr && total / 2 <= g.pair_cap;
+        round = 0;
+    }
+    // the next tile of this workgroup that holds rows, or valid = 0 at the end of the list
+    __device__ __forceinline__ TileRef next(const GemmArgs& g) {
+        TileRef t = {0, 0, 0, 0, 0, -1};
+        for (;;) {
+            const int lt = xcd * per_xcd + round * P + (slot + round) % P;
+            if (lt >= lt_end) return t;
+            round++;
+            const int grp = lt / per_group;
+            const int rem = lt % per_group;
+            const int mt = grp * G + rem % G;
+            if (mt >= n_mt) continue;
+            if (flat) {
+                t.valid = 1;
+                t.row0 = mt * g.flat_bm;
+                t.rows = min(g.flat_bm, g.flat_rows - t.row0);
+                t.nt = rem;
+                return t;
+            }
+            const int rows = g.tile_meta[kTileBase + 4 * mt + 2];
+            if (rows <= 0) continue;
+            t.valid = 1;
+            t.expert = g.tile_meta[kTileBase + 4 * mt];
+            t.row0 = g.tile_meta[kTileBase + 4 * mt + 1];
+            t.rows = rows;
+            t.nt = rem / G;
+            // partner: the other row tile of the pair, same column tile (list position lt ^ 1); the
+            // test reads the same table entries on both sides, so either both wait or neither does
+            if (use_pairs) {
+                const int mt2 = mt ^ 1;
+                if (mt2 < n_mt && g.tile_meta[kTileBase + 4 * mt2 + 2] > 0 &&
+                    g.tile_meta[kTileBase + 4 * mt2] == t.expert)
+                    t.pair = lt >> 1;
+            }
+            return t;
+        }
+    }
+};
 
+// Meet the partner (bounded wait: if it is far behind, go on alone and fetch the weights twice).
+__device__ __forceinline__ void meet_partner(const GemmArgs& g, const TileRef& cur) {
+    if (cur.pair < 0) return;
+    if (threadIdx.x == 0) {
+        int32_t* c = g.pair_cnt + cur.pair;
+        __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int spin = 0; spin < kPairSpins; spin++) {
+            if (__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 2) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+    }
+    lds_barrier();
+}
 
-// Wavefronts that share one staging region of 32 KiB in the epilogue, per epilogue kind: the staging
-// areas live in the operand buffers the last stage has released.  Kinds whose eight areas fit two
-// regions leave a third buffer free, which then takes the next tile's W(1) ahead of time.
-template <int EPI> struct Staging {
+// Staging areas of the epilogue, per epilogue kind: they live in the operand buffers the last stage has
+// released (REG bytes each).  Kinds whose areas fit two buffers leave a third one free, which then takes the next
+// tile's W(1) ahead of time.  A wavefront has one area of 32 rows, SwiGLU backward two: side by side where a buffer
+// holds two, otherwise the second areas start in the third buffer.
+template <int EPI, int NW> struct Staging {
+    static constexpr int REG = NW == 8 ? 32768 : 16384;          // bytes of an operand buffer
     static constexpr int SC = EPI == EPI_SWIGLU_FWD ? 96 : 64;   // columns per staging row
     static constexpr int SROW = SC * 2 + 16;                    // row stride in bytes
-    static constexpr int WSTG = (EPI == EPI_SWIGLU_BWD ? 2 : 1) * 32 * SROW;   // bytes per wavefront
-    static constexpr int RW = 32768 / WSTG < kXwWaves ? 32768 / WSTG : kXwWaves;
-    static constexpr int REGIONS = (EPI == EPI_F32) ? 0 : (kXwWaves + RW - 1) / RW;
+    static constexpr int AREA = 32 * SROW;                      // bytes of an area
+    static constexpr bool SPLIT = EPI == EPI_SWIGLU_BWD && NW == 4;
+    static constexpr int WSTG = (EPI == EPI_SWIGLU_BWD && !SPLIT ? 2 : 1) * AREA;   // bytes per wavefront (first areas)
+    static constexpr int RW = REG / WSTG < NW ? REG / WSTG : NW;                    // wavefronts per buffer
+    static constexpr int REGIONS = (EPI == EPI_F32) ? 0 : SPLIT ? 3 : (NW + RW - 1) / RW;
     static constexpr bool PREW1 = REGIONS <= 2;
     static_assert(REGIONS <= 3, "three operand buffers are free in the epilogue");
+    // (SPLIT: buffer 1 holds the first areas of wavefronts RW.. and behind them the second areas that do not fit buffer 2)
+    static_assert(!SPLIT || (2 * RW >= NW && 2 * (NW - RW) * AREA <= REG), "second areas fit");
 };
 
 // compile-time loop: f(std::integral_constant<int, I>{}) for I = 0 .. N-1
@@ -221,11 +303,11 @@ __device__ __forceinline__ EpiArgs epi_args(const GemmArgs& a) {
     return EpiArgs{a.out0, a.out1, a.out2, a.aux_a, a.aux_b, a.N, a.ldo};
 }
 
-template <int EPI, int MTV, bool LH, bool ADD, typename AccT>
+template <int EPI, int NW, int MTV, bool LH, bool ADD, typename AccT>
 __device__ __forceinline__ void xw_staged_epilogue(const EpiArgs g, const AccT& A,
-                                                   char* stg, int rows, int row0, int n0, int f0,
+                                                   char* stg, [[maybe_unused]] char* stg_second, int rows, int row0, int n0, int f0,
                                                    int strip_first, int strip_step, int wn, int lane) {
-    using SG = Staging<EPI>;
+    using SG = Staging<EPI, NW>;
     constexpr int SROW = SG::SROW;                  // staging row stride in bytes
     constexpr int CPRS = SG::SC / 8;                // 16-byte chunks per staging row
     const int l16 = lane & 15, lg = lane >> 4;
@@ -233,7 +315,7 @@ __device__ __forceinline__ void xw_staged_epilogue(const EpiArgs g, const AccT& 
     // they are fetched as whole 128-byte row segments (one request per cache line instead of one
     // per 16 bytes in the accumulator layout), a strip ahead, picked up from LDS in the
     // accumulator layout, and replaced in place by dA and dB, which leave as row segments again.
-    [[maybe_unused]] char* stgb = stg + 32 * SROW;
+    [[maybe_unused]] char* stgb = SG::SPLIT ? stg_second : stg + 32 * SROW;
     [[maybe_unused]] uint4 av0, av1, av2, av3, bv0, bv1, bv2, bv3;
     // the 64 columns of a wavefront are inside N or outside as a whole (N is a multiple of 64)
     [[maybe_unused]] const bool cols_ok = n0 + wn * 64 < g.N;

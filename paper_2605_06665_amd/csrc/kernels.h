@@ -87,13 +87,13 @@ hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, flo
                        int32_t* tile_meta, hipStream_t st);
 hipError_t mfma_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
                         const void* wgu, const void* wd, void* a, void* b, void* h, void* y,
-                        int32_t* tile_meta, hipStream_t st, const int32_t* slot_of_row = nullptr);
+                        int32_t* tile_meta, int32_t* extra_meta, hipStream_t st, const int32_t* slot_of_row = nullptr);
 hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
                            const void* wgu, void* a, void* b, void* h, int32_t* tile_meta,
-                           hipStream_t st, const int32_t* slot_of_row = nullptr);
+                           int32_t* extra_meta, hipStream_t st, const int32_t* slot_of_row = nullptr);
 hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a, const void* b,
                           const int32_t* offsets, const void* wgu, const void* wd, void* dx,
-                          void* d_act, int32_t* tile_meta, hipStream_t st);
+                          void* d_act, int32_t* tile_meta, int32_t* extra_meta, hipStream_t st);
 hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
                           const void* const* d_act_l, const void* const* h_l,
                           const void* const* dy_l, const int32_t* const* offsets_l,

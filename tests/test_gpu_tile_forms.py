@@ -1,0 +1,67 @@
+"""GPU: the two tile sizes of the row-grouped products (256 x 256, 128 x 128) at the edges of rows, columns and
+reductions: row counts around the 16-row units, 32-row strips and both tiles, column counts that end inside a tile,
+reductions of one, two and three stages, one or both tables in a call.  Everything is compared with float64, and the row
+after the last has to stay as it is."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import TOL, has_gpu, host, rel_err
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a GPU")]
+
+EDGES = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 112, 113, 127, 128, 129, 144, 160, 255, 256, 257, 300, 0]
+# name: (d, f, rows of every expert)
+CASES = {
+    "one-stage": (64, 64, EDGES),
+    "two-stages-three-blocks": (128, 192, EDGES),
+    "odd-columns": (320, 448, EDGES),
+    "big-tiles-fill-the-chip": (1024, 256, [200 + 3 * i for i in range(70)]),         # dX in big, dH in small tiles
+    "small-rows": (576, 320, [i % 60 for i in range(200)]),
+    "one-hot-expert": (192, 640, [0] * 7 + [2000] + [5] * 30),
+    "long-reduction": (256, 2112, [150, 90, 129, 47]),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_products(name):
+    import torch
+    import paper_2605_06665_amd as U
+    d, f, counts = CASES[name]
+    E = len(counts)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    S = int(off[-1])
+    g = torch.Generator().manual_seed(E + d)
+
+    def rnd(*shape, std=1.0):
+        return (torch.randn(shape, generator=g) * std).to(torch.bfloat16)
+
+    x, dy = rnd(S, d), rnd(S, d)
+    wgu, wd = rnd(E, 2 * f, d, std=d ** -0.5), rnd(E, d, f, std=f ** -0.5)
+    sh = U.Shape(T=S, d_model=d, d_ff=f, E=E, k=1, L=1, dtype=U.BF16, sigma=1.0, c=1.0, eps=1e-6, alpha_pool=0.0,
+                 router=0)
+    ws = torch.full((U.workspace_bytes(sh),), 0xff, dtype=torch.uint8, device="cuda:0")
+    a, b, h = (torch.full((S + 1, f), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(3))
+    y, dx = (torch.full((S + 1, d), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    dact = torch.full((S + 1, 2 * f), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    goff, gwgu, gwd = torch.from_numpy(off).cuda(), wgu.cuda(), wd.cuda()
+    U.expert_ffn_fwd(sh, x.cuda(), goff, gwgu, gwd, a, b, h, y, ws)
+    U.expert_ffn_bwd(sh, dy.cuda(), x.cuda(), a, b, h, goff, gwgu, gwd, dx, dact, None, None, ws)
+    a, b, h, y, dx, dact = (host(t) for t in (a, b, h, y, dx, dact))
+    for t in (a, b, h, y, dx, dact):
+        assert np.isnan(t[S]).all() and np.isfinite(t[:S]).all()
+    for e, n in enumerate(counts):
+        if n == 0:
+            continue
+        r = slice(int(off[e]), int(off[e + 1]))
+        we, de = wgu[e].double().numpy(), wd[e].double().numpy()
+        z = x[r].double().numpy() @ we.T
+        ra, rb = z[:, :f], z[:, f:]
+        # each product from the rounded tensors it reads
+        ga, gb = a[r].astype(np.float64), b[r].astype(np.float64)
+        sg = 1 / (1 + np.exp(-ga))
+        dh = dy[r].double().numpy() @ de
+        rdact = np.concatenate([dh * gb * sg * (1 + ga * (1 - sg)), dh * ga * sg], axis=1)
+        for got, want in ((a[r], ra), (b[r], rb), (h[r], ra / (1 + np.exp(-ra)) * rb),
+                          (y[r], h[r].astype(np.float64) @ de.T), (dact[r], rdact),
+                          (dx[r], dact[r].astype(np.float64) @ we)):
+            assert rel_err(got, want) <= TOL["bf16"], (name, e)
