@@ -3,7 +3,7 @@
 Nothing here computes: it owns the device buffers (torch is the allocator) and fixes the call
 order  route -> permute -> expert_ffn_fwd -> combine  per layer,  pool_aux_loss  once, then
 combine_bwd -> expert_ffn_bwd -> combine(unit gates) -> route_bwd  per layer, and the pool
-weight gradient either inside every layer call (`wgrad="layer"`) or once at the end over all
+weight gradient either as the layers go (`wgrad="layer"`) or once at the end over all
 layers (`wgrad="pool"`, one long reduction per expert; same result)."""
 from __future__ import annotations
 
@@ -43,7 +43,8 @@ class PoolStep:
     """Sequences the entry points over the L layers that share the pool.
 
     wgrad     "pool": one weight-gradient pass over all layers at the end of the backward pass;
-              "layer": accumulate into the float gradients layer by layer.
+              "layer": accumulate into the float gradients as the backward pass goes: backward_layer layer by layer,
+              step() a few layers at a time (see _layers_per_wgrad).
     recompute keep one shared pair of A / B buffers instead of one per layer and rebuild a layer's
               A and B (unipool_expert_ffn_recompute) right before its backward pass (App. D (hyperparameter details):
               activation checkpointing with MoE recompute).  Results are bit-identical.
@@ -107,19 +108,34 @@ class PoolStep:
             st.d_w_router = torch.empty((E, d), **f32)
             st.d_sigma = torch.empty(1, **f32)
             self.layers.append(st)
-        # backward buffers: per layer when the weight gradient is deferred, shared otherwise
-        nb = L if wgrad == "pool" else 1
-        self._dy = [torch.empty((S, d), **act) for _ in range(nb)]
-        self._dact = [torch.empty((S, 2 * f), **act) for _ in range(nb)]
+        # backward buffers: per layer when the weight gradient is deferred, for the layers of one accumulation otherwise
+        per = L if wgrad == "pool" else self._layers_per_wgrad()
+        self._dy = [torch.empty((S, d), **act) for _ in range(per)]
+        self._dact = [torch.empty((S, 2 * f), **act) for _ in range(per)]
         self._dxp = torch.empty((S, d), **act)
         self.d_w_gate_up = torch.zeros((E, 2 * f, d), **f32)
         self.d_w_down = torch.zeros((E, d, f), **f32)
-        if wgrad == "pool":
-            def tab(ts):
-                return torch.tensor([t.data_ptr() for t in ts], dtype=torch.int64, device=self.dev)
-            self._tabs = (tab([s.x_perm for s in self.layers]), tab(self._dact),
-                          tab([s.act_h for s in self.layers]), tab(self._dy),
-                          tab([s.offsets for s in self.layers]))
+
+        # pointer tables of the layers that share an accumulation, in the order of the backward pass; layer l uses the
+        # buffers l mod per
+        groups = [range(max(0, hi - per), hi) for hi in range(L, 0, -per)]
+        ptrs = []
+        for ls in groups:
+            for ts in ([self.layers[l].x_perm for l in ls], [self._dact[l % per] for l in ls],
+                       [self.layers[l].act_h for l in ls], [self._dy[l % per] for l in ls],
+                       [self.layers[l].offsets for l in ls]):
+                ptrs += [t.data_ptr() for t in ts]
+        table = iter(torch.tensor(ptrs, dtype=torch.int64, device=self.dev).split([len(ls) for ls in groups for _ in range(5)]))
+        self._wgrad_groups = [(ls, [next(table) for _ in range(5)]) for ls in groups]
+
+    def _layers_per_wgrad(self):
+        """Layers that step() takes together into the float gradients with wgrad="layer".  Reading and writing the
+        gradients in every layer is most of a backward pass over few tokens; what it costs to take n layers at once are
+        n - 1 more pairs of dy / d_act buffers, which get up to a quarter of the gradients' own bytes (4 layers of 90
+        experts of 832 x 1472, 5999 tokens, k = 3, two layers at a time and no zeroing: 5.95 -> 4.20 ms a step)."""
+        pair = self.S * (self.d + 2 * self.f) * (2 if self.dtype == B.BF16 else 4)
+        most = min(self.L, 8, 1 + (3 * self.E * self.d * self.f) // pair)
+        return -(-self.L // -(-self.L // most))          # as even as the number of accumulations allows
 
     def shape(self, sigma: float, L=None) -> B.Shape:
         return B.Shape(T=self.T, d_model=self.d, d_ff=self.f, E=self.E, k=self.k, L=self.L if L is None else L,
@@ -192,15 +208,18 @@ class PoolStep:
             self.d_w_down.zero_()
 
     def backward_layer(self, l, x, w_router, sigma, w_gate_up, w_down, grad_out):
+        return self._backward_layer(l, x, w_router, sigma, w_gate_up, w_down, grad_out, self.wgrad == "layer")
+
+    def _backward_layer(self, l, x, w_router, sigma, w_gate_up, w_down, grad_out, add_wgrad):
         st, sh, ws = self.layers[l], self.shape(sigma), self.ws
-        slot = l if self.wgrad == "pool" else 0
+        slot = l % len(self._dy)
         dy, dact = self._dy[slot], self._dact[slot]
         self._call(B.combine_bwd, sh, grad_out, st.y_perm, st.row_of_slot, st.topk_gate, dy, st.dgate, ws)
         if self.recompute:
             self._call(B.expert_ffn_recompute, sh, st.x_perm, st.offsets, w_gate_up, st.act_a, st.act_b,
                        st.act_h, ws)
-        dwgu = None if self.wgrad == "pool" else self.d_w_gate_up
-        dwd = None if self.wgrad == "pool" else self.d_w_down
+        dwgu = self.d_w_gate_up if add_wgrad else None
+        dwd = self.d_w_down if add_wgrad else None
         self._call(B.expert_ffn_bwd, sh, dy, st.x_perm, st.act_a, st.act_b, st.act_h, st.offsets, w_gate_up, w_down,
                          self._dxp, dact, dwgu, dwd, ws)
         self._call(B.combine, sh, self._dxp, st.row_of_slot, None, st.dx, ws)            # backward of the dispatch
@@ -209,20 +228,25 @@ class PoolStep:
                     st.d_sigma, st.dx, True, ws)
         return st.dx
 
+    def _add_wgrad(self, group, accumulate):
+        layers, tabs = self._wgrad_groups[group]
+        self._call(B.expert_wgrad, self.shape(1.0), len(layers), *tabs, self.d_w_gate_up, self.d_w_down, accumulate,
+                   self.ws)
+
     def end_backward(self):
         if self.wgrad == "pool":
-            self._call(B.expert_wgrad, self.shape(1.0), self.L, *self._tabs, self.d_w_gate_up, self.d_w_down,
-                           False, self.ws)
+            self._add_wgrad(0, False)
 
     # ------------------------------------------------------------------ whole step
     def step(self, xs, w_routers, sigmas, w_gate_up, w_down, grad_outs, fbar_in=None):
         for l in range(self.L):
             self.forward_layer(l, xs[l], w_routers[l], sigmas[l], w_gate_up, w_down)
         self.aux_loss(fbar_in)
-        self.begin_backward()
-        for l in reversed(range(self.L)):
-            self.backward_layer(l, xs[l], w_routers[l], sigmas[l], w_gate_up, w_down, grad_outs[l])
-        self.end_backward()
+        # the first accumulation writes every gradient, so nothing is cleared before it
+        for g, (layers, _) in enumerate(self._wgrad_groups):
+            for l in reversed(layers):
+                self._backward_layer(l, xs[l], w_routers[l], sigmas[l], w_gate_up, w_down, grad_outs[l], False)
+            self._add_wgrad(g, g > 0)
 
 
     # ------------------------------------------------------------------ the step as a HIP graph
