@@ -102,8 +102,7 @@ def roofline_of(w, a, ps, agg, steps):
     xw_tflops = xw_flops_per_launch / (avg_xw_ms * 1e-3) / 1e12
     t_wg_ms = sum(agg.get("expert_wgrad", []))
     gemm_flops_layer = 3.0 * gemm_flops_third + (4.0 * S * w.d * w.f if a.recompute else 0.0)
-    all_gemm_tflops = gemm_flops_layer * w.L * steps / ((t_xw_ms + t_wg_ms) * 1e-3) / 1e12 \
-        if a.wgrad == "pool" else gemm_flops_layer * w.L * steps / (t_xw_ms * 1e-3) / 1e12
+    all_gemm_tflops = gemm_flops_layer * w.L * steps / ((t_xw_ms + t_wg_ms) * 1e-3) / 1e12
     act_b = 2 if w.dtype == "bf16" else 4
 
     def hbm(name, nbytes):
