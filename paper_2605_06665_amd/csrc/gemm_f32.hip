@@ -7,14 +7,14 @@
 //
 // A workgroup is four wavefronts (2 x 2) of WT x WT outputs, WT = 32 or 16.  A 16x16x4 step keeps the matrix
 // core busy for 32 cycles (157 TFLOP/s for the card, a sixteenth of what bfloat16 steps reach), so what is hidden is latency:
-// tiles pass through registers (the next stage is requested before the current one is multiplied) into two LDS
-// buffers, one barrier per stage.  Both operands are laid out K-contiguous in LDS whatever they are in memory,
-// and the 16 indices of a chunk are stored as a 4 x 4 transpose (index k at place 4 (k mod 4) + k / 4): the 16
-// bytes that a lane reads are then its operands of four successive instructions.
-// One thread per output element did this work before: 3003 rows, d = 252, f = 500, 12 experts took 2824 us for
-// gate-up, 1454 down, 227 dH, 552 dX, 861 + 453 for the weight gradients of two layers and 262 for the router's;
-// now 30, 19, 23, 33, 65 + 49 and 7 (gate-up 51 TFLOP/s; the strided operands' 4-way conflicts in LDS writes
-// hold back the weight gradients).
+// tiles pass through registers (the next two stages are requested, without a branch, while one is multiplied) into two LDS
+// buffers as 16-byte pieces, one barrier per stage, whichever index is the contiguous one in memory; neighbouring tiles run
+// on one XCD and meet in its L2.
+// 3003 rows, d = 252, f = 500, 12 experts, us, launches back to back in a graph: both forward products 49 -> 47, both
+// backward products 56 -> 55, weight gradients of two layers 109 -> 73 (with one stage requested ahead, a branch around
+// every load, strided operands transposed on their way into LDS, tiles dealt to the XCDs in turn -> now); 32 experts of
+// 320 x 640, 4500 rows: 96 -> 92, 109 -> 95, 216 -> 154.  The matrix cores are busy half of the time there (74.5 of 148
+// million cycles of the gate and up projections), the rest is the start of the workgroups and the last round.
 #include "kernels.h"
 
 namespace unipool {
@@ -22,6 +22,7 @@ namespace unipool {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxLayers = 256;    // of one weight gradient: what unipool_expert_wgrad takes
 
 enum Epilogue {
     kStore,        // output in the activation type, optionally added to the destination
@@ -39,7 +40,7 @@ struct Args {
     int M, N, K;                   // M: rows of all groups (or of the matrix); N per half for kSwigluFwd
     int n_tiles;                   // column tiles
     const int32_t* offsets;        // row groups [E + 1]; null: one matrix
-    int E;
+    int E;                         // row groups, or weight gradients
     const int32_t* gather;         // row r of A is row gather[r] / gather_div (null: r)
     int gather_div;
     void* out0;
@@ -98,34 +99,55 @@ __device__ __forceinline__ void store4(T* p, f32x4 v, int n, bool vec, bool add)
     }
 }
 
-// Row tile `want` of the row groups, BM rows a tile: every wavefront finds it by itself.
+// Place of this workgroup in a list of `total` tiles that is cut into eight parts, one per XCD (workgroups are dealt to the
+// XCDs in turn): neighbouring tiles, which share operands, meet in one L2.  total or more: nothing to do.
+__device__ __forceinline__ int tile_of_block(int total) {
+    const int per_xcd = (total + 7) / 8, slot = blockIdx.x / 8;
+    return slot < per_xcd ? (blockIdx.x % 8) * per_xcd + slot : total;
+}
+
+// Row tile of the row groups, BM rows a tile, that this workgroup works on with which of n_tiles column tiles: every
+// wavefront finds it by itself.
 struct RowTile {
-    int expert, row0, rows;        // rows = 0: past the last tile
+    int expert, row0, rows, nt;    // rows = 0: past the last tile
 };
 template <int BM>
-__device__ __forceinline__ RowTile find_row_tile(const int32_t* offsets, int E, int want, int lane) {
-    int before = 0;
-    for (int e0 = 0; e0 < E; e0 += 64) {
+__device__ __forceinline__ RowTile find_row_tile(const int32_t* offsets, int E, int n_tiles, int lane) {
+    // tiles of this lane's expert of a batch of 64, and of the experts of the batch up to it
+    int r0, r1, mine, upto;
+    auto batch = [&](int e0) {
         const int e = e0 + lane;
-        const int r0 = e < E ? offsets[e] : 0, r1 = e < E ? offsets[e + 1] : 0;
-        const int mine = (r1 - r0 + BM - 1) / BM;
-        int upto = mine;
+        r0 = e < E ? offsets[e] : 0;
+        r1 = e < E ? offsets[e + 1] : 0;
+        mine = (r1 - r0 + BM - 1) / BM;
+        upto = mine;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int o = __shfl_up(upto, d, 64);
             if (lane >= d) upto += o;
         }
+    };
+    int total = 0;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        batch(e0);
+        total += __shfl(upto, 63, 64);
+    }
+    const int tile = tile_of_block(total * n_tiles), want = tile / n_tiles;
+    if (want >= total) return RowTile{0, 0, 0, 0};
+    int before = 0;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        if (E > 64) batch(e0);
         const int first = before + upto - mine;
         const unsigned long long hit = __ballot(mine > 0 && want >= first && want < first + mine);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;
             const int f = __shfl(first, src, 64), a = __shfl(r0, src, 64), b = __shfl(r1, src, 64);
             const int row0 = a + (want - f) * BM;
-            return RowTile{e0 + src, row0, min(BM, b - row0)};
+            return RowTile{e0 + src, row0, min(BM, b - row0), tile % n_tiles};
         }
         before += __shfl(upto, 63, 64);
     }
-    return RowTile{0, 0, 0};
+    return RowTile{0, 0, 0, 0};
 }
 
 // ATR / BTR: the operand's reduction index is the strided one in memory ([k][m], [k][n]).
@@ -135,10 +157,20 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     constexpr int BM = 2 * WT;                 // tile of the workgroup, both ways
     constexpr int BK = WT == 32 ? 32 : 64;     // reduction indices per stage: 2048 values of each operand
     constexpr int CH = BK / 16;                // 16-index chunks per stage
-    constexpr int LD = BK + 4;                 // LDS row in floats: 16-byte reads of 16 rows meet every bank once
+    // LDS rows in floats, so that the 16 x 4 values of a fragment read lie in 64 banks: K-contiguous operands keep their
+    // rows of BK indices, strided ones their rows of BM columns
+    constexpr int LD = BK + 4, LDT = BM + 16;
+    constexpr int ABUF = ATR ? BK * LDT : BM * LD, BBUF = BTR ? BK * LDT : BM * LD;
     constexpr int NF = WT / 16;                // 16-wide fragments per wavefront and side
     static_assert(BM * BK == 8 * kThreads, "two groups of four values per thread and operand");
-    __shared__ __attribute__((aligned(16))) float lds[2][2][BM * LD];
+    __shared__ __attribute__((aligned(16))) float lds[2][ABUF + BBUF];
+    // row ranges and operands of the expert in every layer
+    struct Layer {
+        const TA* a;
+        const TA* b;
+        int r0, r1;
+    };
+    __shared__ Layer layers[LAYERS ? kMaxLayers : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, lg = lane >> 4;
@@ -147,8 +179,10 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     int expert = 0, row0 = 0, rows = 0, n0, k_begin = 0, k_end = g.K;
     if constexpr (LAYERS) {
         const int per = g.m_tiles * g.n_tiles;
-        expert = blockIdx.x / per;
-        const int r = blockIdx.x % per;
+        const int tile = tile_of_block(g.E * per);
+        expert = tile / per;
+        if (expert >= g.E) return;
+        const int r = tile % per;
         row0 = (r / g.n_tiles) * BM;
         rows = min(BM, g.M - row0);
         n0 = (r % g.n_tiles) * BM;
@@ -156,19 +190,19 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
             k_begin = expert * g.chunk;
             k_end = min(g.K, k_begin + g.chunk);
         }
+    } else if (g.offsets != nullptr) {
+        const RowTile t = find_row_tile<BM>(g.offsets, g.E, g.n_tiles, lane);
+        if (t.rows <= 0) return;
+        expert = t.expert;
+        row0 = t.row0;
+        rows = t.rows;
+        n0 = t.nt * BM;
     } else {
-        const int mt = blockIdx.x / g.n_tiles;
-        n0 = (blockIdx.x % g.n_tiles) * BM;
-        if (g.offsets != nullptr) {
-            const RowTile t = find_row_tile<BM>(g.offsets, g.E, mt, lane);
-            if (t.rows <= 0) return;
-            expert = t.expert;
-            row0 = t.row0;
-            rows = t.rows;
-        } else {
-            row0 = mt * BM;
-            rows = min(BM, g.M - row0);
-        }
+        const int m_tiles = (g.M + BM - 1) / BM, tile = tile_of_block(m_tiles * g.n_tiles), mt = tile / g.n_tiles;
+        if (mt >= m_tiles) return;
+        row0 = mt * BM;
+        rows = min(BM, g.M - row0);
+        n0 = (tile % g.n_tiles) * BM;
     }
     const TA* A = reinterpret_cast<const TA*>(g.A);
     const TA* B = reinterpret_cast<const TA*>(g.B);
@@ -216,22 +250,31 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     const TA* ca[2] = {nullptr, nullptr};      // the layer's operands
     const TA* cb[2] = {nullptr, nullptr};
     int total_k = k_end - k_begin;
+    bool fast = g.vec_a != 0 && g.vec_b != 0;  // (the layers' operands are only known by address here)
     auto settle = [&](int i) {                 // move past ended layers
         while (cr[i] >= ce[i] && cl[i] < g.n_layers) {
             const int over = cr[i] - ce[i];
             if (++cl[i] >= g.n_layers) break;
-            const int s = g.off_l[cl[i]][expert];
-            ce[i] = g.off_l[cl[i]][expert + 1];
-            cr[i] = s + over;
-            ca[i] = reinterpret_cast<const TA*>(g.a_l[cl[i]]);
-            cb[i] = reinterpret_cast<const TA*>(g.b_l[cl[i]]);
+            const Layer l = layers[cl[i]];
+            ce[i] = l.r1;
+            cr[i] = l.r0 + over;
+            ca[i] = l.a;
+            cb[i] = l.b;
         }
     };
     if constexpr (LAYERS) {
         if (g.n_layers > 0) {
+            for (int l = tid; l < g.n_layers; l += kThreads)
+                layers[l] = Layer{reinterpret_cast<const TA*>(g.a_l[l]), reinterpret_cast<const TA*>(g.b_l[l]),
+                                  g.off_l[l][expert], g.off_l[l][expert + 1]};
+            __syncthreads();
             total_k = 0;
-            for (int l = lane; l < g.n_layers; l += 64) total_k += g.off_l[l][expert + 1] - g.off_l[l][expert];
-            total_k = wave_sum_i(total_k);
+            for (int l = 0; l < g.n_layers; l++) {
+                total_k += layers[l].r1 - layers[l].r0;
+                fast = fast && (((size_t)layers[l].a | (size_t)layers[l].b) & (4 * sizeof(TA) - 1)) == 0;
+            }
+            A = layers[0].a;
+            B = layers[0].b;
             if (g.add && total_k == 0) return;
             settle(0);
             settle(1);
@@ -239,94 +282,123 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     }
     const int stages = (total_k + BK - 1) / BK;
 
-    f32x4 ra[2], rb[2];
-    auto fetch = [&](int s) {
-        const int k0 = k_begin + s * BK;
-#pragma unroll
-        for (int i = 0; i < 2; i++) {
-            const TA* pa = nullptr;
-            const TA* pb = nullptr;
-            int na = 0, nb = 0;
-            if constexpr (LAYERS) {
-                const int am = row0 + nq[i], bn = n0 + nq[i];
-                if (g.n_layers > 0) {
-                    if (cl[i] < g.n_layers) {
-                        pa = ca[i] + (size_t)cr[i] * g.lda + am;
-                        pb = cb[i] + (size_t)cr[i] * g.ldb + bn;
-                        na = g.M - am;
-                        nb = g.N - bn;
-                        cr[i] += BK;
-                        settle(i);
-                    }
-                } else if (k0 + kr[i] < k_end) {
-                    pa = A + (size_t)(k0 + kr[i]) * g.lda + am;
-                    pb = B + (size_t)(k0 + kr[i]) * g.ldb + bn;
-                    na = g.M - am;
-                    nb = g.N - bn;
-                }
-            } else {
-                static_assert(LAYERS || !ATR, "a strided first operand belongs to the weight gradients");
-                pa = arow[i] + k0 + kq[i];
-                na = arow[i] != nullptr ? k_end - k0 - kq[i] : 0;
-                if constexpr (BTR) {
-                    pb = B + (size_t)(k0 + kr[i]) * g.ldb + n0 + nq[i];
-                    nb = k0 + kr[i] < k_end ? g.N - n0 - nq[i] : 0;
-                } else {
-                    pb = brow[i] + k0 + kq[i];
-                    nb = brow[i] != nullptr ? k_end - k0 - kq[i] : 0;
-                }
-            }
-            // (the layers' operands are only known by address here: one that is not aligned goes value by value)
-            ra[i] = fetch4(pa, na, g.vec_a != 0 && (!LAYERS || ((size_t)pa & (4 * sizeof(TA) - 1)) == 0));
-            rb[i] = fetch4(pb, nb, g.vec_b != 0 && (!LAYERS || ((size_t)pb & (4 * sizeof(TA) - 1)) == 0));
-        }
-    };
-    // place of index k inside an LDS row: chunk, then the 4 x 4 transpose
-    auto place = [](int k) { return (k & ~15) + (k & 3) * 4 + ((k >> 2) & 3); };
-    auto put = [&](float* t, const f32x4& v, bool tr, int i) {
-        if (tr) {
-#pragma unroll
-            for (int j = 0; j < 4; j++) t[(nq[i] + j) * LD + place(kr[i])] = v[j];
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; j++) t[mq[i] * LD + place(kq[i] + j)] = v[j];
-        }
-    };
-
     f32x4 acc[NF][NF];
 #pragma unroll
     for (int a = 0; a < NF; a++)
 #pragma unroll
         for (int b = 0; b < NF; b++) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (stages > 0) fetch(0);
-    for (int s = 0; s < stages; s++) {
-        float* ta = lds[s & 1][0];
-        float* tb = lds[s & 1][1];
+    // Operands of the next two stages on their way, as they are in memory (a conversion here would wait for the load).
+    // FAST: four values at a time without a branch, so that the loads of two stages stay in flight; a group past an end is
+    // loaded from the operand's start and put down as zeros.  The general form goes value by value.
+    using Raw = typename std::conditional<std::is_same<TA, float>::value, f32x4, bf16x4>::type;
+    auto main_loop = [&](auto fast_c) __attribute__((always_inline)) {
+        constexpr bool FAST = decltype(fast_c)::value;
+        Raw ra[2][2], rb[2][2];
+        int oka[2] = {0, 0}, okb[2] = {0, 0};      // bit set: the set's group exists
+        auto fetch = [&](int s, auto set_c) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            const int k0 = k_begin + s * BK;
 #pragma unroll
-        for (int i = 0; i < 2; i++) {
-            put(ta, ra[i], ATR, i);
-            put(tb, rb[i], BTR, i);
+            for (int i = 0; i < 2; i++) {
+                const TA* pa = nullptr;
+                const TA* pb = nullptr;
+                int na = 0, nb = 0;
+                if constexpr (LAYERS) {
+                    const int am = row0 + nq[i], bn = n0 + nq[i];
+                    if (g.n_layers > 0) {
+                        if (cl[i] < g.n_layers) {
+                            pa = ca[i] + (size_t)cr[i] * g.lda + am;
+                            pb = cb[i] + (size_t)cr[i] * g.ldb + bn;
+                            na = g.M - am;
+                            nb = g.N - bn;
+                            cr[i] += BK;
+                            settle(i);
+                        }
+                    } else if (k0 + kr[i] < k_end) {
+                        pa = A + (size_t)(k0 + kr[i]) * g.lda + am;
+                        pb = B + (size_t)(k0 + kr[i]) * g.ldb + bn;
+                        na = g.M - am;
+                        nb = g.N - bn;
+                    }
+                } else {
+                    static_assert(LAYERS || !ATR, "a strided first operand belongs to the weight gradients");
+                    pa = arow[i] + k0 + kq[i];
+                    na = arow[i] != nullptr ? k_end - k0 - kq[i] : 0;
+                    if constexpr (BTR) {
+                        pb = B + (size_t)(k0 + kr[i]) * g.ldb + n0 + nq[i];
+                        nb = k0 + kr[i] < k_end ? g.N - n0 - nq[i] : 0;
+                    } else {
+                        pb = brow[i] + k0 + kq[i];
+                        nb = brow[i] != nullptr ? k_end - k0 - kq[i] : 0;
+                    }
+                }
+                if constexpr (FAST) {
+                    ra[set][i] = *reinterpret_cast<const Raw*>(na > 0 ? pa : A);
+                    rb[set][i] = *reinterpret_cast<const Raw*>(nb > 0 ? pb : B);
+                    oka[i] = (oka[i] & ~(1 << set)) | ((na > 0) << set);
+                    okb[i] = (okb[i] & ~(1 << set)) | ((nb > 0) << set);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        ra[set][i][q] = q < na ? pa[q] : (TA)0.f;
+                        rb[set][i][q] = q < nb ? pb[q] : (TA)0.f;
+                    }
+                }
+            }
+        };
+        auto put = [&](float* t, const Raw& v, bool ok, bool tr, int i) __attribute__((always_inline)) {
+            const f32x4 f = {(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+            *reinterpret_cast<f32x4*>(t + (tr ? kr[i] * LDT + nq[i] : mq[i] * LD + kq[i])) =
+                ok ? f : f32x4{0.f, 0.f, 0.f, 0.f};
+        };
+        // operands of the four instructions of chunk c: the lane's row (or column) at indices 4 q + lg
+        auto frag = [&](const float* t, bool tr, int r, int c) {
+            f32x4 v;
+#pragma unroll
+            for (int q = 0; q < 4; q++) v[q] = t[tr ? (c * 16 + 4 * q + lg) * LDT + r : r * LD + c * 16 + 4 * q + lg];
+            return v;
+        };
+
+        auto stage = [&](int s, auto set_c) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            float* ta = lds[set];
+            float* tb = ta + ABUF;
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                put(ta, ra[set][i], !FAST || (oka[i] >> set & 1), ATR, i);
+                put(tb, rb[set][i], !FAST || (okb[i] >> set & 1), BTR, i);
+            }
+            __syncthreads();                       // the other buffer is free: its readers passed the barrier before
+            if (s + 2 < stages) fetch(s + 2, set_c);
+#pragma unroll
+            for (int c = 0; c < CH; c++) {
+                f32x4 fa[NF], fb[NF];
+#pragma unroll
+                for (int a = 0; a < NF; a++) fa[a] = frag(ta, ATR, wm * WT + a * 16 + l16, c);
+#pragma unroll
+                for (int b = 0; b < NF; b++) fb[b] = frag(tb, BTR, wn * WT + b * 16 + l16, c);
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+#pragma unroll
+                    for (int a = 0; a < NF; a++)
+#pragma unroll
+                        for (int b = 0; b < NF; b++)
+                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][q], fa[a][q], acc[a][b], 0, 0, 0);
+            }
+        };
+        {
+            using Even = std::integral_constant<int, 0>;
+            using Odd = std::integral_constant<int, 1>;
+            if (stages > 0) fetch(0, Even{});
+            if (stages > 1) fetch(1, Odd{});
+            for (int s = 0; s < stages; s += 2) {
+                stage(s, Even{});
+                if (s + 1 < stages) stage(s + 1, Odd{});
+            }
         }
-        __syncthreads();                       // the other buffer is free: its readers passed the barrier before
-        if (s + 1 < stages) fetch(s + 1);
-#pragma unroll
-        for (int c = 0; c < CH; c++) {
-            f32x4 fa[NF], fb[NF];
-#pragma unroll
-            for (int a = 0; a < NF; a++)
-                fa[a] = *reinterpret_cast<const f32x4*>(ta + (wm * WT + a * 16 + l16) * LD + c * 16 + lg * 4);
-#pragma unroll
-            for (int b = 0; b < NF; b++)
-                fb[b] = *reinterpret_cast<const f32x4*>(tb + (wn * WT + b * 16 + l16) * LD + c * 16 + lg * 4);
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-#pragma unroll
-                for (int a = 0; a < NF; a++)
-#pragma unroll
-                    for (int b = 0; b < NF; b++)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][q], fa[a][q], acc[a][b], 0, 0, 0);
-        }
-    }
+    };
+    if (fast) main_loop(std::true_type{});
+    else main_loop(std::false_type{});
 
     // ---- epilogue: acc[a][b][r] = C[row wm WT + 16 a + l16][column wn WT + 16 b + 4 lg + r]
 #pragma unroll
@@ -396,7 +468,7 @@ hipError_t run_rows_wt(Args a, int n_cols, hipStream_t st) {
     constexpr int BM = 2 * WT;
     a.n_tiles = cdiv(n_cols, BM);
     const long long row_tiles = a.offsets ? (long long)a.M / BM + min(a.E, a.M) : cdiv(a.M, BM);
-    const long long grid = row_tiles * a.n_tiles;
+    const long long grid = (row_tiles * a.n_tiles + 7) / 8 * 8;          // a multiple of eight, see tile_of_block
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
     gemm_f32_kernel<TA, WT, false, BTR, EPI, false><<<(unsigned)grid, kThreads, 0, st>>>(a);
     return hipGetLastError();
@@ -412,7 +484,8 @@ template <typename TA, int WT>
 hipError_t run_layers_wt(Args a, int groups, hipStream_t st) {
     a.m_tiles = cdiv(a.M, 2 * WT);
     a.n_tiles = cdiv(a.N, 2 * WT);
-    const long long grid = (long long)groups * a.m_tiles * a.n_tiles;
+    a.E = groups;
+    const long long grid = ((long long)groups * a.m_tiles * a.n_tiles + 7) / 8 * 8;
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
     gemm_f32_kernel<TA, WT, true, true, kFloat, true><<<(unsigned)grid, kThreads, 0, st>>>(a);
     return hipGetLastError();
