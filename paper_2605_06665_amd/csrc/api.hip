@@ -218,7 +218,7 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
     void* dz = base + w.dz;
-    float* dsigma_part = (float*)(base + w.dsigma_part);
+    float* dsigma_part = (float*)(base + w.psum_part);     // and on into the area behind it
     const bool mfma = mfma_route_bwd_supported(*shape, x, w_router, dx);
     RouteBwdPrep prep = {};
     if (mfma) prep = mfma_route_bwd_prep(*shape, x, (int32_t*)(base + w.tile_meta), base + w.zeros);

@@ -1016,7 +1016,6 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // ---------------------------------------------------------------------------------------------
 // launch helpers
 // ---------------------------------------------------------------------------------------------
-constexpr int kFlatBM = 128;     // row tiles of ungrouped matrices (router): a token count of 128 per CU fills the chip
 constexpr int kBM = 256, kBN = 256, kBK = 64, kNS = 2;   // gemm_xw: 128-byte row segments per load
 constexpr int kPtqBK = 32, kPtqNS = 4, kPtqWaves = 8;       // gemm_ptq
 constexpr int kGemmLds = kNS * kBM * kBK * 2 + (kNS + 1) * kBN * kBK * 2;   // 2 X stages + 3 W stages = 160 KiB
@@ -1172,8 +1171,11 @@ hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, flo
     a.W = (const bf16*)w; a.w_stride = 0; a.ldw = s.d_model;
     a.K = s.d_model; a.N = s.E;
     a.tile_meta = tile_meta; a.out0 = z; a.ldo = s.E;
-    a.flat_rows = s.T; a.flat_bm = kFlatBM;
-    return run_xw<TILE_BIG, true, EPI_F32>(a, st);
+    a.flat_rows = s.T; a.flat_bm = kSmallBM;
+    // 128 columns where they hold the pool or where all tiles run at once, 256 otherwise, which read x half as often (all of
+    // the entry point, us, 256 / 128: 64 experts, 8192 tokens, d 832 26 / 23; 512, 1000, 320 43 / 34; 200, 20000, 832 42 / 45)
+    return s.E <= kSmallBN || cdiv(s.T, kSmallBM) * cdiv(s.E, kSmallBN) <= num_cus()
+               ? run_xw<TILE_SMALL, true, EPI_F32>(a, st) : run_xw<TILE_BIG, true, EPI_F32>(a, st);
 }
 
 hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
@@ -1269,9 +1271,12 @@ bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void*
 
 RouteBwdPrep mfma_route_bwd_prep(const unipool_shape& s, const void* x, int32_t* tile_meta, void* zeros) {
     // d_w_router = dz^T x: the token axis is cut into chunks whose partial products are summed in a fixed order;
-    // as many chunks as give every CU one output tile in a single round
+    // as many chunks as give every CU one output tile in a single round, of 256 tokens at least, or 128 where the partial
+    // products are small (all of the entry point, us, 256 / 128: 16 experts, d 768, 3001 tokens 24 / 22; 64 experts, d 768,
+    // 8192 tokens 32 / 34)
+    const int chunk_min = dz_stride(s) <= 32 ? 128 : 256;
     const int tiles_per_chunk = cdiv(dz_stride(s), 256) * cdiv(s.d_model, 256);
-    const int nchunks = max(1, min(min(kRouteBwdSplit, cdiv(s.T, 256)), num_cus() / tiles_per_chunk));
+    const int nchunks = max(1, min(min(kRouteBwdSplit, cdiv(s.T, chunk_min)), num_cus() / tiles_per_chunk));
     RouteBwdPrep p = {};
     p.chunk_rows = cdiv(cdiv(s.T, nchunks), 32) * 32;
     p.nchunks = cdiv(s.T, p.chunk_rows);
@@ -1299,7 +1304,7 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, c
     hipError_t e = run_ptq<false>(a, st);
     if (e != hipSuccess) return e;
     const size_t n = (size_t)E * d;                 // a multiple of 64, as d is
-    const int n_dsigma = cdiv(T, kRouterTokensPerBlock);
+    const int n_dsigma = cdiv(T, dz_tokens_per_block(s));
     if (((uintptr_t)dw & 15) == 0)
         reduce_partials_kernel<f32x4><<<(unsigned)((n / 4 + 255) / 256) + 1, 256, 0, st>>>(
             wpart, used, (size_t)ez * d, n, dw, dsigma_part, n_dsigma, d_sigma);
@@ -1308,16 +1313,18 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, c
             wpart, used, (size_t)ez * d, n, dw, dsigma_part, n_dsigma, d_sigma);
     // dx (+)= dz W   (W is [E][d]: reduction index strided)
     GemmArgs b = {};
-    // 256-row tiles where they still give every CU a tile: the short reduction (E indices) makes the pipeline
-    // fill of a tile as long as its loop, and a taller tile pays it once for twice the rows
-    b.flat_rows = T; b.flat_bm = (cdiv(T, kBM) * cdiv(d, kBN) >= num_cus()) ? kBM : kFlatBM;
+    // Small tiles: the reduction (E indices) is so short that a tile is mostly its start and its end, which two workgroups
+    // to a CU overlap (all of the entry point, us, 256 x 256 or 128 x 256 tiles / 128 x 128: 32768 tokens, 192 experts, d 1536
+    // 121 / 110; 8192, 64, 768: 33 / 32; 16384, 512, 1024: 84 / 86)
+    b.flat_rows = T; b.flat_bm = kSmallBM;
     b.X = (const bf16*)dz; b.ldx = ez;                 // (values between E and ez are zeros)
     b.W = (const bf16*)w; b.w_stride = 0; b.ldw = d;
     b.K = E; b.N = d;
     b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d; b.zeros = zeros;
     if (dx_accumulate)
-        return E % kBK != 0 ? run_xw<TILE_BIG, false, EPI_STORE, true, true>(b, st) : run_xw<TILE_BIG, false, EPI_STORE, false, true>(b, st);
-    return E % kBK != 0 ? run_xw<TILE_BIG, false, EPI_STORE, true>(b, st) : run_xw<TILE_BIG, false, EPI_STORE>(b, st);
+        return E % kBK != 0 ? run_xw<TILE_SMALL, false, EPI_STORE, true, true>(b, st)
+                            : run_xw<TILE_SMALL, false, EPI_STORE, false, true>(b, st);
+    return E % kBK != 0 ? run_xw<TILE_SMALL, false, EPI_STORE, true>(b, st) : run_xw<TILE_SMALL, false, EPI_STORE>(b, st);
 }
 
 }  // namespace unipool

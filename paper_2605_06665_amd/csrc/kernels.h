@@ -22,7 +22,9 @@ struct RouteBwdPrep {
     const void* x;
     uint32_t* zeros;             // 64 words
 };
-// d_sigma = nullptr: the partial sums stay in dsigma_part ([ceil(T / 64)]) for a later kernel
+// dsigma_part: one float per block of dz_tokens_per_block tokens.  d_sigma = nullptr: they stay there for a later kernel.
+// (The partial sums have the two areas of the router's block statistics, 2 E floats per 64 tokens.)
+inline int dz_tokens_per_block(const unipool_shape& s) { return s.E < 4 ? kRouterTokensPerBlock : s.E <= 256 ? 16 : 8; }
 hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, const int32_t* topk_idx,
                                const float* dgate, const float* aux_coef, void* dz,
                                float* dsigma_part, float* d_sigma, const RouteBwdPrep& prep, hipStream_t st);

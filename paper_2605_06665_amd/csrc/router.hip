@@ -148,13 +148,15 @@ __global__ __launch_bounds__(256) void route_finalize_kernel(
 // Backward of Eq. 7 per token, a group of GS lanes per token as in the forward selection:
 // ds = aux_coef + dgate on the selected experts; dz = J^T ds with J the Jacobian of
 // s = sigma c relu(z / (||z|| + eps)); d sigma = sum ds * s / sigma.  Rows of dz are ldz >= E values long, the
-// ones past E zero.
+// ones past E zero.  A wavefront takes one round of 64 / GS tokens (dz_tokens_per_block): the rounds of a block of 64 tokens
+// waited for their loads one after the other, on a quarter of the wavefronts (all of unipool_route_bwd, us: 5999 tokens of 90
+// experts, d 832 39 -> 35; 16384 of 512, 1024 94 -> 84; 4000 of 400, 640 62 -> 45; 32768 of 192, 1536 123 -> 121).
 template <typename TA, int GS, int VPL>
 __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ topk_idx,
     const float* __restrict__ dgate, const float* __restrict__ aux_coef, int T, int E, int k,
-    float sigma, float c, float eps, int softmax, TA* __restrict__ dz, int ldz, float* __restrict__ dsigma_part,
-    const RouteBwdPrep prep) {
+    float sigma, float c, float eps, int softmax, int tok_per_block, TA* __restrict__ dz, int ldz,
+    float* __restrict__ dsigma_part, const RouteBwdPrep prep) {
     constexpr int TPW = 64 / GS;
     if (blockIdx.x == 0 && prep.off != nullptr) {
         for (int i = threadIdx.x; i <= prep.nchunks; i += 256) prep.off[i] = min(T, i * prep.chunk_rows);
@@ -165,7 +167,6 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
             prep.table[2] = prep.off;
         }
     }
-    static_assert(kTokPerWave % TPW == 0, "whole rounds per wavefront");
     __shared__ float lds_ds[kWavesPerBlock];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -179,8 +180,9 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
         coef[i] = (aux_coef != nullptr && e < E) ? aux_coef[e] : 0.f;
     }
     float dsig = 0.f;
-    const int t0 = blockIdx.x * kRouterTokensPerBlock + wave * kTokPerWave + grp;
-    for (int tt = 0; tt < kTokPerWave; tt += TPW) {
+    const int per_wave = tok_per_block / kWavesPerBlock;
+    const int t0 = blockIdx.x * tok_per_block + wave * per_wave + grp;
+    for (int tt = 0; tt < per_wave; tt += TPW) {
         const int t = t0 + tt;
         const bool live = t < T;
         const int tc = min(t, T - 1);
@@ -205,6 +207,7 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
         }
 #pragma unroll
         for (int j = 0; j < kMaxK; j++) {
+            if (j >= k) break;
 #pragma unroll
             for (int i = 0; i < VPL; i++)
                 if (selv[j] == sl + GS * i) ds[i] += gdv[j];
@@ -343,10 +346,10 @@ hipError_t launch_route_finalize(const unipool_shape& s, const int32_t* cnt_part
 hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, const int32_t* topk_idx,
                                const float* dgate, const float* aux_coef, void* dz,
                                float* dsigma_part, float* d_sigma, const RouteBwdPrep& prep, hipStream_t st) {
-    const int nblocks = cdiv(s.T, kRouterTokensPerBlock);
+    const int tokens = dz_tokens_per_block(s), nblocks = cdiv(s.T, tokens);
 #define UNIPOOL_DZ(TA, GS, VPL)                                                                        \
     route_bwd_dz_kernel<TA, GS, VPL><<<nblocks, 256, 0, st>>>(logits, topk_idx, dgate, aux_coef, s.T, s.E, \
-                                                              s.k, s.sigma, s.c, s.eps, s.router, (TA*)dz, dz_stride(s), dsigma_part, prep)
+                                                              s.k, s.sigma, s.c, s.eps, s.router, tokens, (TA*)dz, dz_stride(s), dsigma_part, prep)
     if (s.dtype == UNIPOOL_BF16) {
         if (s.E <= 128) UNIPOOL_DZ(bf16, 16, 8);
         else if (s.E <= 256) UNIPOOL_DZ(bf16, 16, 16);

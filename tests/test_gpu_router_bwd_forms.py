@@ -119,3 +119,50 @@ def test_odd_pools_take_any_alignment(E, d, T, shifted):
     assert bool(torch.isfinite(ds).all())
     if around is not None:
         assert bool(torch.isnan(around[0])) and bool(torch.isnan(around[-1]))
+
+
+@pytest.mark.parametrize("E,T,k,d", [(1, 300, 1, 64), (3, 1000, 2, 64), (4, 1000, 2, 192), (5, 17, 1, 128), (32, 400, 2, 320),
+                                     (40, 129, 3, 64), (128, 400, 2, 192), (136, 70, 2, 320), (256, 15, 1, 64),
+                                     (257, 300, 3, 64), (264, 33, 8, 192), (512, 9, 8, 128), (512, 700, 8, 192),
+                                     (200, 17000, 1, 64)])
+@pytest.mark.parametrize("router", [0, 1])
+def test_blocks_of_tokens(E, T, k, d, router):
+    """Blocks of 8, 16 and 64 tokens with ends inside them, logits and dx in tiles of 128 x 128 and 128 x 256 whose rows
+    and columns end inside a tile, chunks of 128 and 256 tokens: logits, d_sigma, router gradient and dx in double."""
+    import torch
+    import paper_2605_06665_amd as U
+    g = torch.Generator().manual_seed(E + T)
+    x = torch.randn((T, d), generator=g).to(torch.bfloat16).cuda()
+    wr = (torch.randn((E, d), generator=g) * (1.0 if router == 0 else d ** -0.5)).to(torch.bfloat16).cuda()
+    sh = U.Shape(T=T, d_model=d, d_ff=64, E=E, k=k, L=1, dtype=U.BF16, sigma=0.9, c=2.0, eps=1e-6, alpha_pool=0.0, router=router)
+    i32, f32 = dict(dtype=torch.int32, device="cuda"), dict(device="cuda")
+    idx, gate, z = torch.empty((T, k), **i32), torch.empty((T, k), **f32), torch.full((T + 1, E), float("nan"), **f32)
+    cnt, ps = torch.empty(E, **i32), torch.empty(E, **f32)
+    ws = torch.full((U.workspace_bytes(sh),), 0xff, dtype=torch.uint8, device="cuda")
+    U.route(sh, x, wr, idx, gate, z, cnt, ps, ws)
+    assert torch.isnan(z[T]).all()
+    xd, wd = x.double().cpu(), wr.double().cpu()
+    assert rel_err(host(z[:T]), (xd @ wd.T).numpy()) <= 1e-5
+    dgate, coef = torch.randn((T, k), generator=g), torch.randn(E, generator=g) * 0.1
+    dw, dsg = torch.full((E, d), float("nan"), **f32), torch.full((1,), float("nan"), **f32)
+    dx = torch.full((T + 1, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    U.route_bwd(sh, x, wr, z, idx, dgate.cuda(), coef.cuda(), dw, dsg, dx, False, ws)
+    assert torch.isnan(dx[T].float()).all()
+    zd = z[:T].double().cpu()
+    ds = coef.double().expand(T, E).clone().scatter_add_(1, idx.long().cpu(), dgate.double())
+    if router == 0:
+        n = zd.norm(dim=1, keepdim=True)
+        s = 2.0 * (zd / (n + 1e-6)).clamp_min(0)
+        dzh = ds * 0.9 * 2.0 * (zd > 0)
+        dz = dzh / (n + 1e-6) - zd * (dzh * zd).sum(1, keepdim=True) / ((n + 1e-6) ** 2 * n)
+        # at most T E float terms, summed in a tree of wavefronts and blocks
+        assert abs(float(dsg) - float((ds * s).sum())) <= 1e-5 * float((ds * s).abs().sum()) + 1e-6
+    else:
+        p = torch.softmax(zd, 1)
+        dz = p * (ds - (ds * p).sum(1, keepdim=True))
+        assert float(dsg) == 0.0
+    # (one expert: dz cancels to rounding noise of its terms)
+    if E > 1:
+        assert rel_err(host(dw), (dz.T @ xd).numpy()) <= TOL["bf16"] and rel_err(host(dx[:T]), (dz @ wd).numpy()) <= TOL["bf16"]
+    else:
+        assert np.isfinite(host(dw)).all() and np.isfinite(host(dx[:T])).all()
