@@ -31,11 +31,6 @@ bool unfused_router() {
 constexpr bool unfused_router() { return false; }
 #endif
 
-__global__ void fill_zero_kernel(uint32_t* p, size_t words) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < words) p[i] = 0u;
-}
-
 __global__ void set_ptrs_kernel(void** table, const void* p0, const void* p1, const void* p2,
                                 const void* p3, const void* p4) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
@@ -61,13 +56,6 @@ int check_hip(hipError_t e, const char* what) {
     return set_error(UNIPOOL_ELAUNCH, "%s: %s", what, hipGetErrorString(e));
 }
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
-    const size_t words = bytes / 4;
-    if (words == 0) return hipSuccess;
-    fill_zero_kernel<<<(unsigned)((words + 255) / 256), 256, 0, st>>>((uint32_t*)p, words);
-    return hipGetLastError();
-}
-
 hipError_t launch_set_ptrs(void** table, const void* p0, const void* p1, const void* p2,
                            const void* p3, const void* p4, hipStream_t st) {
     set_ptrs_kernel<<<1, 64, 0, st>>>(table, p0, p1, p2, p3, p4);
@@ -81,7 +69,6 @@ WsLayout ws_layout(const unipool_shape& s) {
     const size_t rblocks = (T + kRouterTokensPerBlock - 1) / kRouterTokensPerBlock;
     const size_t act = s.dtype == UNIPOOL_BF16 ? 2 : 4, ez = (size_t)dz_stride(s);
     size_t o = 0;
-    w.zeros = o;       o += 256;
     w.tile_meta = o;   o += align_up((4096 + 4 * (S / 256 + 2 * E + T / 128 + 16)) * sizeof(int32_t));
     w.chunk_hist = o;  o += align_up(((T + 63) / 64) * E * sizeof(int32_t));
     w.psum_part = o;   o += align_up(rblocks * E * sizeof(float));
@@ -220,16 +207,14 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     void* dz = base + w.dz;
     float* dsigma_part = (float*)(base + w.psum_part);     // and on into the area behind it
     const bool mfma = mfma_route_bwd_supported(*shape, x, w_router, dx);
-    RouteBwdPrep prep = {};
-    if (mfma) prep = mfma_route_bwd_prep(*shape, x, (int32_t*)(base + w.tile_meta), base + w.zeros);
-    hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz, dsigma_part,
-                                       mfma ? nullptr : d_sigma, prep, st);
+    hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz, dsigma_part, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route_bwd: dz");
     if (mfma)
-        e = mfma_route_bwd_mm(*shape, prep, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
+        e = mfma_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
                               (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart), st);
     else
-        e = f32_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, (float*)(base + w.wpart), st);
+        e = f32_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
+                             (float*)(base + w.wpart), st);
     return check_hip(e, "unipool_route_bwd: contractions");
 }
 
@@ -340,16 +325,12 @@ int unipool_expert_ffn_bwd(const unipool_shape* shape, const void* dy_perm, cons
                             d_act, st);
     if (e != hipSuccess) return check_hip(e, "unipool_expert_ffn_bwd: dgrad");
     if (!d_w_gate_up) return UNIPOOL_OK;
-    void** tab = (void**)(base + w.ptr_tab);
-    e = launch_set_ptrs(tab, x_perm, d_act, act_h, dy_perm, expert_offsets, st);
-    if (e != hipSuccess) return check_hip(e, "unipool_expert_ffn_bwd: pointer table");
     if (mfma) {
-        e = launch_fill_zero(base + w.zeros, 256, st);
-        if (e != hipSuccess) return check_hip(e, "unipool_expert_ffn_bwd: zero page");
-        e = mfma_ffn_wgrad(*shape, 1, tab + 0, tab + 1, tab + 2, tab + 3,
-                           (const int32_t* const*)(tab + 4), d_w_gate_up, d_w_down, 1,
-                           base + w.zeros, st);
+        e = mfma_ffn_wgrad_layer(*shape, x_perm, d_act, act_h, dy_perm, expert_offsets, d_w_gate_up, d_w_down, st);
     } else {
+        void** tab = (void**)(base + w.ptr_tab);
+        e = launch_set_ptrs(tab, x_perm, d_act, act_h, dy_perm, expert_offsets, st);
+        if (e != hipSuccess) return check_hip(e, "unipool_expert_ffn_bwd: pointer table");
         e = f32_ffn_wgrad(*shape, 1, tab + 0, tab + 1, tab + 2, tab + 3,
                             (const int32_t* const*)(tab + 4), d_w_gate_up, d_w_down, 1, st);
     }
@@ -371,15 +352,12 @@ int unipool_expert_wgrad(const unipool_shape* shape, int n_layers, const void* c
     char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_ffn_supported(*shape)) {
-        e = launch_fill_zero(base + w.zeros, 256, st);
-        if (e != hipSuccess) return check_hip(e, "unipool_expert_wgrad: zero page");
+    if (mfma_ffn_supported(*shape))
         e = mfma_ffn_wgrad(*shape, n_layers, x_perm_l, d_act_l, act_h_l, dy_perm_l, expert_offsets_l,
-                           d_w_gate_up, d_w_down, accumulate, base + w.zeros, st);
-    } else {
+                           d_w_gate_up, d_w_down, accumulate, st);
+    else
         e = f32_ffn_wgrad(*shape, n_layers, x_perm_l, d_act_l, act_h_l, dy_perm_l, expert_offsets_l,
                             d_w_gate_up, d_w_down, accumulate, st);
-    }
     return check_hip(e, "unipool_expert_wgrad");
 }
 

@@ -25,7 +25,6 @@ struct GemmArgs {
     const bf16* aux_b;
     int up_rows;          // EPI_SWIGLU_FWD: row offset of the up projection inside W_e (= d_ff)
     int group_m;          // row tiles walked together
-    const void* zeros;    // >= 16 readable zero bytes (reduction tail of KTAIL kernels)
     // gathered rows: row r of the grouped order is row gather[r] / gather_div of X (null: row r itself)
     const int32_t* gather;
     int gather_div;

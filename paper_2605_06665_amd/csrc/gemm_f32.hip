@@ -58,6 +58,10 @@ struct Args {
     int m_tiles;
     long long out_stride;
     int chunk;                     // rows per partial sum (flat K ranges); 0: none
+    // a sum of floats that the first workgroup of the launch does on the way (null: none)
+    const float* sum_part;
+    int sum_n;
+    float* sum_out;
 };
 
 template <typename TA> __device__ __forceinline__ f32x4 fetch_vec(const TA* p);
@@ -178,6 +182,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     // ---- which tile
     int expert = 0, row0 = 0, rows = 0, n0, k_begin = 0, k_end = g.K;
     if constexpr (LAYERS) {
+        if (blockIdx.x == 0 && g.sum_part != nullptr) block_sum_256(g.sum_part, g.sum_n, g.sum_out);
         const int per = g.m_tiles * g.n_tiles;
         const int tile = tile_of_block(g.E * per);
         expert = tile / per;
@@ -578,7 +583,7 @@ namespace {
 
 template <typename TA>
 hipError_t route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw, void* dx,
-                        int dx_accumulate, float* wpart, hipStream_t st) {
+                        int dx_accumulate, const float* dsigma_part, float* d_sigma, float* wpart, hipStream_t st) {
     const int d = s.d_model, E = s.E, T = s.T, ez = dz_stride(s);
     const size_t el = sizeof(TA);
     // d_w_router = dz^T x.  The tokens are cut into chunks of at least 128 (two stages of a 32 x 32 tile) so that
@@ -589,6 +594,7 @@ hipError_t route_bwd_mm(const unipool_shape& s, const void* x, const void* w, co
     const int used = cdiv(T, chunk);
     Args a = {};
     a.A = dz; a.lda = ez; a.B = x; a.ldb = d; a.M = E; a.N = d; a.K = T; a.chunk = chunk;
+    a.sum_part = dsigma_part; a.sum_n = cdiv(T, dz_tokens_per_block(s)); a.sum_out = d_sigma;
     a.out0 = used > 1 ? wpart : dw; a.ldo = d; a.out_stride = (long long)E * d;
     a.vec_a = aligned(dz, ez, el); a.vec_b = aligned(x, d, el); a.vec_o = aligned(a.out0, d, 4);
     hipError_t e = run_layers<TA>(a, used, st);
@@ -609,9 +615,11 @@ hipError_t route_bwd_mm(const unipool_shape& s, const void* x, const void* w, co
 }  // namespace
 
 hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
-                            void* dx, int dx_accumulate, float* wpart, hipStream_t st) {
-    return s.dtype == UNIPOOL_BF16 ? route_bwd_mm<bf16>(s, x, w, dz, dw, dx, dx_accumulate, wpart, st)
-                                   : route_bwd_mm<float>(s, x, w, dz, dw, dx, dx_accumulate, wpart, st);
+                            void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma, float* wpart,
+                            hipStream_t st) {
+    return s.dtype == UNIPOOL_BF16
+               ? route_bwd_mm<bf16>(s, x, w, dz, dw, dx, dx_accumulate, dsigma_part, d_sigma, wpart, st)
+               : route_bwd_mm<float>(s, x, w, dz, dw, dx, dx_accumulate, dsigma_part, d_sigma, wpart, st);
 }
 
 }  // namespace unipool

@@ -78,6 +78,15 @@ __device__ __forceinline__ int scan512(int v, int* wsum) {
     return v;
 }
 
+// What reductions read past their end.  Never written.
+__device__ __align__(256) uint32_t g_zero_page[64];
+// Its address, once and for all: named in a loop it would be fetched from memory there each time.
+__device__ __forceinline__ const void* zero_page() {
+    const void* p = g_zero_page;
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // Size class of a row count, larger counts in later classes: steps of 16 rows below 2048, a sixteenth of a
 // power of two above.
 constexpr int kSizeClasses = 512;
@@ -344,6 +353,7 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
     // KTAIL: K is not a multiple of BK; chunks past K come from a page of zeros in both operands
     static_assert(!KTAIL || !WK, "the reduction tail is implemented for N-contiguous W only");
     int xk[KTAIL ? XI : 1], wk[KTAIL ? WI : 1];   // first reduction index of the lane's chunk / row
+    [[maybe_unused]] const void* const zeros = KTAIL ? zero_page() : nullptr;
     if constexpr (KTAIL) {
 #pragma unroll
         for (int i = 0; i < XI; i++) {
@@ -358,13 +368,13 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
         if (!xload[i]) return;
         const char* src = xsrc[i] + (size_t)kt * BK * 2;
         if constexpr (KTAIL)
-            if (kt * BK + xk[i] >= g.K) src = reinterpret_cast<const char*>(g.zeros);
+            if (kt * BK + xk[i] >= g.K) src = reinterpret_cast<const char*>(zeros);
         glds16(src, lds0 + xbuf(kb) * XBYTES + ((i * NW + wave) * 64) * 16);
     };
     auto issue_w = [&](int kt, int i, int kb) {
         const char* src = wsrc[i] + (size_t)kt * wstep;
         if constexpr (KTAIL)
-            if (kt * BK + wk[i] >= g.K) src = reinterpret_cast<const char*>(g.zeros);
+            if (kt * BK + wk[i] >= g.K) src = reinterpret_cast<const char*>(zeros);
         glds16(src, lds0 + WBASE + wbuf(kb) * WBYTES + ((i * NW + wave) * 64) * 16);
     };
     // One stage.  The wavefronts meet between the halves of the second slice: stage kt+1 has landed,
@@ -607,28 +617,37 @@ __global__ __launch_bounds__(2 * BN, 2) void gemm_xw_kernel(const GemmArgs g) {
 // gemm_ptq: out[e][i][j] (+)= sum_l sum_{row in group e of layer l} P_l[row][i] * Q_l[row][j]
 // ---------------------------------------------------------------------------------------------
 struct PtqArgs {
-    int n_layers;
-    const void* const* P;        // device arrays of device pointers
+    const void* const* P;        // device arrays of device pointers, one entry per layer
+// One weight gradient of all experts (or one matrix cut into chunks of rows, whose partial products are the "experts").
     const void* const* Q;
-    const int32_t* const* off;
-    int E, mdim, ndim;
+    const void* P1;              // the operands of a single layer or matrix (P, Q and off are null then)
+    const void* Q1;
+    int chunk_rows, total_rows;
+    int mdim, ndim;
     int m_tiles, n_tiles;
     float* out;
     long long out_stride;        // elements between experts
-    int accumulate;
-    const void* zeros;           // >= 16 readable zero bytes
+};
+// What a launch computes: the tiles of `first`, then those of `second` (none where it is not used).
+struct PtqLaunch {
+    PtqArgs first, second;
+    const int32_t* const* off;   // row offsets of the experts, one entry per layer; or
+    const int32_t* off1;         // those of a single layer; or none: chunks
+    int n_layers, E, accumulate;
 };
 
-template <int BK, int NS, int NW, bool STREAM>
-__global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
+template <int BK, int NS, int NW, bool STREAM, bool PAIR>
+__global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launch) {
     // 256 x 256 float tile, 2 x 4 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16 (at the card's power
     // limit it sustains about a sixth more than the 32x32x16 form): 8 x 4 accumulator blocks of 16 x 16.
-    constexpr int BM = 256, BN = 256;
+    // NW = 4: 128 x 128, 2 x 2 wavefronts of 64 x 64, several workgroups to a CU (see ptq_small).
+    constexpr int BM = NW == 8 ? 256 : 128, BN = BM;
     constexpr int NT = 64 * NW;               // threads
     constexpr int WNC = NW / 2;               // wavefronts along n (two along m)
-    constexpr int CW = BN / WNC;              // columns of a wavefront's block (128 rows)
-    constexpr int NA = 8, NB = CW / 16;       // 16-wide fragments of P and of Q per wavefront
-    static_assert(NW == 8 && BK == 32 && NB == 4, "one 32-deep slice per stage, 8 x 4 blocks per wavefront");
+    constexpr int CW = BN / WNC;              // columns of a wavefront's block
+    constexpr int RW = BM / 2;                // rows of a wavefront's block
+    constexpr int NA = RW / 16, NB = CW / 16; // 16-wide fragments of P and of Q per wavefront
+    static_assert((NW == 8 || NW == 4) && BK == 32 && NB == 4, "one 32-deep slice per stage, NA x 4 blocks per wavefront");
     constexpr int PBYTES = BK * BM * 2;
     constexpr int STAGE = 2 * PBYTES;
     constexpr int PI = BK * BM / 8 / NT;      // loads per wavefront per operand per stage
@@ -636,16 +655,21 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     using PT = NTile16<BM>;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-    const int per_e = g.m_tiles * g.n_tiles;
-    const int total = g.E * per_e;
+    const int total1 = launch.E * launch.first.m_tiles * launch.first.n_tiles;
+    const int total = total1 + (PAIR ? launch.E * launch.second.m_tiles * launch.second.n_tiles : 0);
     const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
     const int slot = blockIdx.x / kNumXcd;
     if (slot >= per_xcd) return;
-    const int lt = (blockIdx.x % kNumXcd) * per_xcd + slot;
+    int lt = (blockIdx.x % kNumXcd) * per_xcd + slot;
     if (lt >= total) return;
     const int e = lt / per_e;
     // The 32 workgroups of an XCD run 32 consecutive tiles side by side and share their operand blocks
     // through L2: with the shorter tile axis running fastest the 32 tiles form the squarest block
+    const PtqArgs g = PAIR && lt >= total1 ? launch.second : launch.first;
+    if (PAIR && lt >= total1) lt -= total1;
+    const int n_layers = launch.n_layers, accumulate = launch.accumulate;
+    const void* const zeros = zero_page();
+    const int per_e = g.m_tiles * g.n_tiles;
     // (about 6 x 5 instead of 2 x 16), which needs the fewest distinct operand blocks.
     const int idx = lt % per_e;
     const int m0 = (g.m_tiles <= g.n_tiles ? idx % g.m_tiles : idx / g.n_tiles) * BM;
@@ -665,22 +689,29 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     __shared__ int lds_r0[kMaxPtqLayers], lds_r1[kMaxPtqLayers];
     __shared__ const bf16* lds_p[kMaxPtqLayers];
     __shared__ const bf16* lds_q[kMaxPtqLayers];
-    for (int l = threadIdx.x; l < g.n_layers; l += NT) {
-        lds_r0[l] = g.off[l][e];
-        lds_r1[l] = g.off[l][e + 1];
-        lds_p[l] = reinterpret_cast<const bf16*>(g.P[l]);
-        lds_q[l] = reinterpret_cast<const bf16*>(g.Q[l]);
+    if (PAIR && g.P == nullptr) {
+        lds_r0[0] = launch.off1 ? launch.off1[e] : min(g.total_rows, e * g.chunk_rows);
+        lds_r1[0] = launch.off1 ? launch.off1[e + 1] : min(g.total_rows, (e + 1) * g.chunk_rows);
+        lds_p[0] = reinterpret_cast<const bf16*>(g.P1);
+        lds_q[0] = reinterpret_cast<const bf16*>(g.Q1);
+    } else {
+        for (int l = threadIdx.x; l < n_layers; l += NT) {
+            lds_r0[l] = launch.off[l][e];
+            lds_r1[l] = launch.off[l][e + 1];
+            lds_p[l] = reinterpret_cast<const bf16*>(g.P[l]);
+            lds_q[l] = reinterpret_cast<const bf16*>(g.Q[l]);
+        }
     }
     __syncthreads();
     // The rows of expert e in all the layers form one reduction, cut into K blocks of BK rows without
     // regard to the layers: a block may end one layer's range and begin the next one's, and only the
     // very last block is filled up with zero rows.
     int k_total = 0;
-    for (int l = 0; l < g.n_layers; l++) k_total += max(0, __builtin_amdgcn_readfirstlane(lds_r1[l] - lds_r0[l]));
+    for (int l = 0; l < n_layers; l++) k_total += max(0, __builtin_amdgcn_readfirstlane(lds_r1[l] - lds_r0[l]));
     const int nb = (k_total + BK - 1) / BK;
     float* otile = g.out + (long long)e * g.out_stride;
     if (nb == 0) {
-        if (!g.accumulate) {
+        if (!accumulate) {
             for (int i = threadIdx.x; i < BM * BN; i += NT) {
                 const int r = m0 + i / BN, c = n0 + i % BN;
                 if (r < g.mdim && c < g.ndim) otile[(size_t)r * g.ndim + c] = 0.f;
@@ -690,12 +721,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     }
 
     // lane geometry of the direct-to-LDS loads: load i of a wavefront fills LDS slots
-    // (i*NW + wave)*64 + lane, i.e. K row 2*NW*i + 2*wave + lane/32, chunk position lane%32.  The
+    // (i*NW + wave)*64 + lane, i.e. K row 16 i + RPL wave + lane / CPR, chunk position lane % CPR.  The
     // swizzle depends on bits 0, 1 and 3 of the K row, which are the same for all i.
-    static_assert((2 * NW) % 16 == 0, "the K rows of a lane's loads differ by multiples of 16");
+    constexpr int RPL = 64 / PT::CPR;         // K rows of one load
+    static_assert(RPL * NW == 16, "the K rows of a lane's loads differ by multiples of 16");
     static_assert(2 * PI == 4, "four loads per K block");
-    const int krow0 = 2 * wave + (lane >> 5);
-    const int cc = (lane & 31) ^ PT::swz(krow0);
+    const int krow0 = RPL * wave + lane / PT::CPR;
+    const int cc = (lane % PT::CPR) ^ PT::swz(krow0);
     const int pcol = min(m0 + cc * 8, g.mdim - 8);
     const int qcol = min(n0 + cc * 8, g.ndim - 8);
 
@@ -722,7 +754,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     const bf16* nx_q = nullptr;
     auto fetch_next = [&]() {
         nx_r = nx_end = 0;
-        while (++nx_layer < g.n_layers) {
+        while (++nx_layer < n_layers) {
             nx_r = __builtin_amdgcn_readfirstlane(lds_r0[nx_layer]);
             nx_end = __builtin_amdgcn_readfirstlane(lds_r1[nx_layer]);
             if (nx_end > nx_r) {
@@ -731,12 +763,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
                 return;
             }
         }
-        nx_layer = g.n_layers;
+        nx_layer = n_layers;
         nx_r = nx_end = 0;
     };
     fetch_next();
     auto next_layer = [&]() {     // the cursor moves to the next layer with rows (wave-uniform); false past the last
-        if (nx_layer >= g.n_layers) return false;
+        if (nx_layer >= n_layers) return false;
         ld_layer = nx_layer;
         ld_r = nx_r;
         ld_end = nx_end;
@@ -745,30 +777,31 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         fetch_next();
         return true;
     };
-    auto next_block = [&]() {     // put the cursor on the first row of the next K block
-        while (ld_r >= ld_end)
-            if (!next_layer()) break;
-    };
+    // The cursor is always on a row, as long as there is one: it moves to the next layer as soon as one ends.
     auto advance_block = [&]() {  // move the cursor BK rows on, from layer to layer
-        int need = BK;
+        ld_r += BK;
+        if (__builtin_expect(ld_r < ld_end, 1)) return;
+        int over = ld_r - ld_end;
         for (;;) {
-            const int n = min(ld_end - ld_r, need);
-            if (n > 0) {
-                ld_r += n;
-                need -= n;
+            if (!next_layer()) {
+                ld_r = ld_end;
+                return;
             }
-            if (need == 0 || !next_layer()) break;
+            if (over < ld_end - ld_r) break;
+            over -= ld_end - ld_r;
         }
     };
     // Per-lane source addresses of the LPS loads of the K block at the cursor (P rows for i < PI, Q
     // rows after), worked out in one place per block so that the load slots between the MFMAs hold
+        ld_r += over;
     // nothing but the load.
+    next_layer();
     const void* blk_src[2 * PI];
     auto block_sources = [&]() {
         if (__builtin_expect(ld_r + BK <= ld_end, 1)) {
 #pragma unroll
             for (int i = 0; i < 2 * PI; i++) {
-                const int rb = ld_r + 2 * NW * (i < PI ? i : i - PI);         // wave-uniform
+                const int rb = ld_r + 16 * (i < PI ? i : i - PI);         // wave-uniform
                 blk_src[i] = i < PI ? reinterpret_cast<const char*>(ld_p + (size_t)rb * g.mdim) + voff_p
                                     : reinterpret_cast<const char*>(ld_q + (size_t)rb * g.ndim) + voff_q;
             }
@@ -778,13 +811,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
             const int rem = ld_end - ld_r, nrows = nx_end - nx_r;
 #pragma unroll
             for (int i = 0; i < 2 * PI; i++) {
-                const int j = 2 * NW * (i < PI ? i : i - PI) + krow0;
+                const int j = 16 * (i < PI ? i : i - PI) + krow0;
                 const int dim = i < PI ? g.mdim : g.ndim, col = i < PI ? pcol : qcol;
-                const void* src = g.zeros;
+                const void* src = zeros;
                 if (j < rem) src = (i < PI ? ld_p : ld_q) + (size_t)(ld_r + j) * dim + col;
                 else if (j - rem < nrows) src = (i < PI ? nx_p : nx_q) + (size_t)(nx_r + j - rem) * dim + col;
                 int j0 = rem + nrows;
-                for (int lay = nx_layer + 1; j0 < BK && lay < g.n_layers; lay++) {
+                for (int lay = nx_layer + 1; j0 < BK && lay < n_layers; lay++) {
                     const int r = __builtin_amdgcn_readfirstlane(lds_r0[lay]);
                     const int n = min(__builtin_amdgcn_readfirstlane(lds_r1[lay]) - r, BK - j0);
                     if (n <= 0) continue;
@@ -808,15 +841,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         for (int b = 0; b < NB; b++) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Fragments: P block a (rows of the output) and Q block b (columns), one register set each.  A
-    // stage is 32 MFMA slots, slot 4b + a in each half (a = 0..3 in the first half, 4..7 in the
-    // second), so P[0..3] and Q[0..2] become free for the next stage's data during the second half,
-    // Q[3] and P[4..7] at its end; the wavefronts meet in the middle, where the next stage's data has
+    // stage is NA * NB MFMA slots, slot HA b + a in each half (a < HA in the first half, the others in the
+    // second), so P[0 .. HA) and Q[0..2] become free for the next stage's data during the second half,
+    // Q[3] and the other P at its end; the wavefronts meet in the middle, where the next stage's data has
     // landed.
     static_assert(NS >= 2 && (NS - 1) * LPS < 64, "outstanding loads must fit the wait counter");
     bf16x8 pfr[NA], qfr[NB];
     int foff_p[NA], foff_q[NB];
 #pragma unroll
-    for (int a = 0; a < NA; a++) foff_p[a] = PT::frag_off(wm * 128 + a * 16, lane);
+    for (int a = 0; a < NA; a++) foff_p[a] = PT::frag_off(wm * RW + a * 16, lane);
 #pragma unroll
     for (int b = 0; b < NB; b++) foff_q[b] = PBYTES + PT::frag_off(wn * CW + b * 16, lane);
     constexpr int SECOND = 4 * PT::CPR * 16;          // bytes between the two reads of a fragment
@@ -842,16 +875,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         const int stage = kb % NS, nstage = (kb + 1) % NS;
         static_assert(LPS == 4, "load slots below");
         if constexpr (ISSUE) {
-            next_block();
             block_sources();
+        constexpr int HA = NA / 2, HS = HA * NB;          // slots of a half
+        constexpr int GAP = HS == 16 ? 3 : 1;
         }
 #pragma unroll
-        for (int s = 0; s < 16; s++) {
-            mfma_one(s & 3, s >> 2);
+        for (int s = 0; s < HS; s++) {
+            mfma_one(s % HA, s / HA);
             if (s == 0) load_q(stage, 3);                       // what the previous stage still held
-            if (s >= 1 && s <= 4) load_p(stage, 3 + s);
+            if (s >= 1 && s <= HA) load_p(stage, HA - 1 + s);
             if constexpr (ISSUE) {
-                if (s >= 5 && (s - 5) % 3 == 0) issue_one((kb + NS - 1) % NS, (s - 5) / 3);
+                constexpr int S0 = HS - 3 * GAP - (HS == 16 ? 2 : 1);
+                if (s >= S0 && (s - S0) % GAP == 0 && (s - S0) / GAP < 4) issue_one((kb + NS - 1) % NS, (s - S0) / GAP);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -870,17 +905,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         pc_bar += clock64() - pw1;
 #endif
 #pragma unroll
-        for (int s = 0; s < 16; s++) {
-            mfma_one(4 + (s & 3), s >> 2);
-            if (s < 4) load_p(nstage, s);                       // after the last stage: unused, in bounds
-            else if ((s & 3) == 0) load_q(nstage, (s >> 2) - 1);
+        for (int s = 0; s < HS; s++) {
+            mfma_one(HA + s % HA, s / HA);
+            if (s < HA) load_p(nstage, s);                      // after the last stage: unused, in bounds
+            else if (s % HA == 0) load_q(nstage, s / HA - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 #pragma unroll
     for (int s = 0; s < NS; s++)
         if (s < nb) {
-            next_block();
             block_sources();
 #pragma unroll
             for (int i = 0; i < LPS; i++) issue_one(s, i);
@@ -893,7 +927,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     const long long pt_filled = wall_clock64(), pc_filled = clock64();
 #endif
 #pragma unroll
-    for (int a = 0; a < 4; a++) load_p(0, a);
+    for (int a = 0; a < NA / 2; a++) load_p(0, a);
 #pragma unroll
     for (int b = 0; b < 3; b++) load_q(0, b);
     {
@@ -906,8 +940,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
     const long long pt_looped = wall_clock64(), pc_looped = clock64();
 #endif
 
-    // acc[a][b][r] = out[i = m0 + wm*128 + a*16 + 4*(lane/16) + r][j = n0 + wn*CW + b*16 + lane%16]
-    // The 128 x CW block of a wavefront leaves in four passes of 32 rows through a wave-private LDS
+    // acc[a][b][r] = out[i = m0 + wm*RW + a*16 + 4*(lane/16) + r][j = n0 + wn*CW + b*16 + lane%16]
+    // The block of a wavefront leaves in passes of 32 rows through a wave-private LDS
     // area (rows of CW floats + 4 of padding), so that every lane stores 16 bytes and a wavefront
     // instruction covers whole row segments of 4*CW bytes; when accumulating, the old values are
     // fetched in the same layout.
@@ -927,13 +961,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
         // 852 -> 780 us).  A choice at run time would not do: the compiler merges the two forms of an access into the
         // plain one.
         constexpr int ITS = 32 / RPI;
-        const bool add_vec = vec_ok && g.accumulate;
+        const bool add_vec = vec_ok && accumulate;
         const int c4 = (lane % LPR) * 4, j = jw + c4;
         f32x4 old[2][ITS];
         auto fetch_old = [&](int a2) {
 #pragma unroll
             for (int it = 0; it < ITS; it++) {
-                const int i = m0 + wm * 128 + a2 * 32 + it * RPI + lane / LPR;
+                const int i = m0 + wm * RW + a2 * 32 + it * RPI + lane / LPR;
                 if (i < g.mdim && j < g.ndim) {
                     const f32x4* src = reinterpret_cast<const f32x4*>(otile + (size_t)i * g.ndim + j);
                     if constexpr (STREAM) old[a2 & 1][it] = __builtin_nontemporal_load(src);
@@ -952,7 +986,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
 #pragma unroll
                     for (int r = 0; r < 4; r++)
                         stg[(16 * ah + 4 * (lane >> 4) + r) * SLD + b * 16 + (lane & 15)] = acc[2 * a2 + ah][b][r];
-            const int i_blk = m0 + wm * 128 + a2 * 32;
+            const int i_blk = m0 + wm * RW + a2 * 32;
 #pragma unroll
             for (int it = 0; it < ITS; it++) {
                 const int row = it * RPI + lane / LPR;
@@ -967,7 +1001,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqArgs g) {
                 } else {
                     const float vv[4] = {v[0], v[1], v[2], v[3]};
                     for (int q = 0; q < 4; q++)
-                        if (j + q < g.ndim) dst[q] = (g.accumulate ? dst[q] : 0.f) + vv[q];
+                        if (j + q < g.ndim) dst[q] = (accumulate ? dst[q] : 0.f) + vv[q];
                 }
             }
         }
@@ -1049,25 +1083,72 @@ hipError_t run_xw(GemmArgs a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <bool STREAM>
-hipError_t run_ptq(const PtqArgs& a, hipStream_t st) {
-    auto kern = gemm_ptq_kernel<kPtqBK, kPtqNS, kPtqWaves, STREAM>;
+constexpr int kPtqSmallNS = 3, kPtqSmallLds = kPtqSmallNS * 2 * kPtqBK * 128 * 2;   // 48 KiB
+
+template <int NW, bool STREAM, bool PAIR>
+hipError_t run_ptq_form(PtqLaunch a, hipStream_t st) {
+    constexpr int BM = NW == 8 ? 256 : 128, NS = NW == 8 ? kPtqNS : kPtqSmallNS, LDS = NW == 8 ? kPtqLds : kPtqSmallLds;
+    auto kern = gemm_ptq_kernel<kPtqBK, NS, NW, STREAM, PAIR>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kPtqLds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int total = a.E * a.m_tiles * a.n_tiles;
+    for (PtqArgs* p : {&a.first, &a.second}) {
+        p->m_tiles = cdiv(p->mdim, BM);
+        p->n_tiles = cdiv(p->ndim, BM);
+    }
+    const int total = a.E * (a.first.m_tiles * a.first.n_tiles + a.second.m_tiles * a.second.n_tiles);
     const int grid = cdiv(total, kNumXcd) * kNumXcd;
-    kern<<<grid, 64 * kPtqWaves, kPtqLds, st>>>(a);
+    kern<<<grid, 64 * NW, LDS, st>>>(a);
     return hipGetLastError();
 }
 
 // the meeting counters live behind the largest possible tile table (total_rows / 256 + 2 E entries)
 int32_t* pair_counters(int32_t* meta, int E, int total_rows) {
     return meta + kTileBase + 4 * (total_rows / kBM + 2 * E);
+template <int NW, bool PAIR> hipError_t run_ptq_nw(const PtqLaunch& a, bool stream, hipStream_t st) {
+    return stream ? run_ptq_form<NW, true, PAIR>(a, st) : run_ptq_form<NW, false, PAIR>(a, st);
+}
+
+// Weight gradients of the experts, `rows` rows each in all layers on average.  A 256 x 256 tile takes its CU 0.0235 us per
+// row, and then 11 us for its floats, 24 when they are added to old ones; in four 128 x 128 tiles, which read twice as many
+// operand bytes but of which a CU runs two at a time, so that one stores while the other multiplies, 0.034 us per row and
+// 10.2 or 17.7 us (fitted to 64 experts of 768 x 2048 with 512 and 2048 rows; short of a whole tile the floats count).
+// The 18 shapes this was checked on follow it to 10 %, hence the margins (us, big / small tiles, added: 90 experts of
+// 832 x 1472 with 200 rows 711 / 522, with 400 825 / 663; 96 of 1024 x 2816 with 682 rows 1974 / 2072; written: 60 of
+// 320 x 320 with 400 rows 60 / 42, 90 of 832 x 1472 483 / 513).
+// Both gradients go out in one launch, the second's tiles in the wake of the first's (16 of 576 x 320, 1500 rows: two
+// launches 93, one 52; 200 of 640 x 1024, 28 rows: 336 / 320), except where each is many rounds of long tiles: then tiles of
+// both kinds side by side share less in L2 (192 of 1536 x 4096, 2728 rows: 17.1 / 17.4 ms).
+hipError_t run_ptq(const PtqLaunch& a, bool stream, double rows, hipStream_t st) {
+    const double cus = num_cus();
+    auto tiles = [&](int bm) {
+        return (double)a.E * ((double)cdiv(a.first.mdim, bm) * cdiv(a.first.ndim, bm) +
+                              (double)cdiv(a.second.mdim, bm) * cdiv(a.second.ndim, bm));
+    };
+    const double nb = tiles(256), ns = tiles(128);
+    const double whole = (double)a.E * ((double)a.first.mdim * a.first.ndim + (double)a.second.mdim * a.second.ndim) / 65536;
+    const double big = std::ceil(nb / cus) * (0.0235 * rows + (a.accumulate ? 24.0 : 11.0) * whole / nb);
+    const double small = std::ceil(ns / (2 * cus)) * 0.5 * (0.034 * rows + (a.accumulate ? 17.7 : 10.2) * 4 * whole / ns);
+    bool take_small = small < (a.accumulate ? 0.98 : 0.9) * big;
+#ifdef UNIPOOL_DEBUG_SWITCHES
+    if (const char* e = getenv("UNIPOOL_PTQ")) take_small = e[0] == '1';
+#endif
+    if (take_small) return run_ptq_nw<4, true>(a, stream, st);
+    if (rows > 448 && nb > 8 * cus && a.off != nullptr) {
+        PtqLaunch one = a;
+        one.second = PtqArgs{};
+        hipError_t e = run_ptq_nw<8, false>(one, stream, st);
+        if (e != hipSuccess) return e;
+        one.first = a.second;
+        return run_ptq_nw<8, false>(one, stream, st);
+    }
+    return run_ptq_nw<8, true>(a, stream, st);
+}
+
 }
 
 // Timing aid of debugging builds: UNIPOOL_W0=1 makes every expert read the weights of expert 0, so that the
@@ -1235,28 +1316,41 @@ hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_
     return run_grouped<false, EPI_STORE>(b, tile1, st);
 }
 
-hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
-                          const void* const* d_act_l, const void* const* h_l,
-                          const void* const* dy_l, const int32_t* const* offsets_l,
-                          float* dwgu, float* dwd, int accumulate, const void* zeros,
-                          hipStream_t st) {
+static hipError_t ffn_wgrad(const unipool_shape& s, PtqLaunch a, float* dwgu, float* dwd, hipStream_t st) {
     const int d = s.d_model, f = s.d_ff;
     // Smaller gradients are still in the last-level cache (256 MB) when the next layer adds to them.  One layer's whole
     // backward call, k = 2, plain / streamed, us: 16 experts of 768 x 1024 (151 MB), 256 tokens 106 / 124, 4096 tokens
     // 214 / 207; 14 experts of 1024 x 1024 (176 MB) 147 / 138 and 224 / 208; 64 experts of 768 x 2048 (1.2 GB) 669 / 608
     // and 770 / 712.
     const bool stream = 12ll * s.E * d * f > (160ll << 20);
-    PtqArgs a = {};    // d_w_gate_up[e][n][c] = sum d_act[row][n] * x_perm[row][c]
-    a.n_layers = n_layers; a.P = d_act_l; a.Q = x_perm_l; a.off = offsets_l;
-    a.E = s.E; a.mdim = 2 * f; a.ndim = d; a.m_tiles = cdiv(2 * f, 256); a.n_tiles = cdiv(d, 256);
-    a.out = dwgu; a.out_stride = 2LL * f * d; a.accumulate = accumulate; a.zeros = zeros;
-    hipError_t e = stream ? run_ptq<true>(a, st) : run_ptq<false>(a, st);
-    if (e != hipSuccess) return e;
-    PtqArgs b = {};    // d_w_down[e][c][n] = sum dy[row][c] * h[row][n]
-    b.n_layers = n_layers; b.P = dy_l; b.Q = h_l; b.off = offsets_l;
-    b.E = s.E; b.mdim = d; b.ndim = f; b.m_tiles = cdiv(d, 256); b.n_tiles = cdiv(f, 256);
-    b.out = dwd; b.out_stride = (long long)d * f; b.accumulate = accumulate; b.zeros = zeros;
-    return stream ? run_ptq<true>(b, st) : run_ptq<false>(b, st);
+    a.E = s.E;
+    PtqArgs& gu = a.first;     // d_w_gate_up[e][n][c] = sum d_act[row][n] * x_perm[row][c]
+    gu.mdim = 2 * f; gu.ndim = d;
+    gu.out = dwgu; gu.out_stride = 2LL * f * d;
+    PtqArgs& dn = a.second;    // d_w_down[e][c][n] = sum dy[row][c] * h[row][n]
+    dn.mdim = d; dn.ndim = f;
+    dn.out = dwd; dn.out_stride = (long long)d * f;
+    return run_ptq(a, stream, (double)a.n_layers * s.T * s.k / s.E, st);
+}
+
+hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
+                          const void* const* d_act_l, const void* const* h_l,
+                          const void* const* dy_l, const int32_t* const* offsets_l,
+                          float* dwgu, float* dwd, int accumulate, hipStream_t st) {
+    PtqLaunch a = {};
+    a.off = offsets_l; a.n_layers = n_layers; a.accumulate = accumulate;
+    a.first.P = d_act_l; a.first.Q = x_perm_l;
+    a.second.P = dy_l; a.second.Q = h_l;
+    return ffn_wgrad(s, a, dwgu, dwd, st);
+}
+
+hipError_t mfma_ffn_wgrad_layer(const unipool_shape& s, const void* x_perm, const void* d_act, const void* h, const void* dy,
+                                const int32_t* offsets, float* dwgu, float* dwd, hipStream_t st) {
+    PtqLaunch a = {};
+    a.off1 = offsets; a.n_layers = 1; a.accumulate = 1;
+    a.first.P1 = d_act; a.first.Q1 = x_perm;
+    a.second.P1 = dy; a.second.Q1 = h;
+    return ffn_wgrad(s, a, dwgu, dwd, st);
 }
 
 bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx) {
@@ -1269,39 +1363,30 @@ bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void*
     return s.T > 256 && (((uintptr_t)x | (uintptr_t)w | (uintptr_t)dx) & 15) == 0;
 }
 
-RouteBwdPrep mfma_route_bwd_prep(const unipool_shape& s, const void* x, int32_t* tile_meta, void* zeros) {
+hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
+                             float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,
+                             int32_t* tile_meta, float* wpart, hipStream_t st) {
+    const int d = s.d_model, E = s.E, T = s.T, ez = dz_stride(s);
     // d_w_router = dz^T x: the token axis is cut into chunks whose partial products are summed in a fixed order;
     // as many chunks as give every CU one output tile in a single round, of 256 tokens at least, or 128 where the partial
     // products are small (all of the entry point, us, 256 / 128: 16 experts, d 768, 3001 tokens 24 / 22; 64 experts, d 768,
     // 8192 tokens 32 / 34)
-    const int chunk_min = dz_stride(s) <= 32 ? 128 : 256;
-    const int tiles_per_chunk = cdiv(dz_stride(s), 256) * cdiv(s.d_model, 256);
-    const int nchunks = max(1, min(min(kRouteBwdSplit, cdiv(s.T, chunk_min)), num_cus() / tiles_per_chunk));
-    RouteBwdPrep p = {};
-    p.chunk_rows = cdiv(cdiv(s.T, nchunks), 32) * 32;
-    p.nchunks = cdiv(s.T, p.chunk_rows);
-    // the pointer table and the chunk offsets live where other entry points keep the tile table
-    p.off = tile_meta;                              // [nchunks + 1]
-    p.table = reinterpret_cast<void**>(tile_meta + 1024);
-    p.x = x;
-    p.zeros = static_cast<uint32_t*>(zeros);
-    return p;
-}
-
-hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, const void* w, const void* dz,
-                             float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,
-                             int32_t* tile_meta, float* wpart, hipStream_t st) {
-    const int d = s.d_model, E = s.E, T = s.T, ez = dz_stride(s);
-    const int used = prep.nchunks;
-    void** tab = prep.table;
-    const void* zeros = prep.zeros;
-    PtqArgs a = {};
+    const int chunk_min = ez <= 32 ? 128 : 256;
+    const int tiles_per_chunk = cdiv(ez, 256) * cdiv(d, 256);
+    const int nchunks = max(1, min(min(kRouteBwdSplit, cdiv(T, chunk_min)), num_cus() / tiles_per_chunk));
+    PtqLaunch a = {};
     a.n_layers = 1;
-    a.P = (const void* const*)(tab + 0); a.Q = (const void* const*)(tab + 1);
-    a.off = (const int32_t* const*)(tab + 2);
-    a.E = used; a.mdim = ez; a.ndim = d; a.m_tiles = cdiv(ez, 256); a.n_tiles = cdiv(d, 256);
-    a.out = wpart; a.out_stride = (long long)ez * d; a.accumulate = 0; a.zeros = zeros;
-    hipError_t e = run_ptq<false>(a, st);
+    PtqArgs& p = a.first;
+    p.P1 = dz; p.Q1 = x;
+    p.chunk_rows = cdiv(cdiv(T, nchunks), 32) * 32;
+    p.total_rows = T;
+    const int used = cdiv(T, p.chunk_rows);
+    a.E = used;
+    p.mdim = ez; p.ndim = d;
+    p.out = wpart; p.out_stride = (long long)ez * d;
+    // 128 x 128 tiles for pools that they do not cut and for short calls (all of the entry point, us, 256 / 128: 64 experts,
+    // d 768, 8192 tokens 32 / 28; 512, 320, 1000 32 / 25; 192, 1536, 32768 115 / 122)
+    hipError_t e = ez <= 128 || T <= 4096 ? run_ptq_form<4, false, true>(a, st) : run_ptq_form<8, false, true>(a, st);
     if (e != hipSuccess) return e;
     const size_t n = (size_t)E * d;                 // a multiple of 64, as d is
     const int n_dsigma = cdiv(T, dz_tokens_per_block(s));
@@ -1320,7 +1405,7 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, c
     b.X = (const bf16*)dz; b.ldx = ez;                 // (values between E and ez are zeros)
     b.W = (const bf16*)w; b.w_stride = 0; b.ldw = d;
     b.K = E; b.N = d;
-    b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d; b.zeros = zeros;
+    b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d;
     if (dx_accumulate)
         return E % kBK != 0 ? run_xw<TILE_SMALL, false, EPI_STORE, true, true>(b, st)
                             : run_xw<TILE_SMALL, false, EPI_STORE, false, true>(b, st);

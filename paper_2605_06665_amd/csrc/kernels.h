@@ -13,21 +13,12 @@ hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, 
 // Per-token backward of the score: writes dz (act dtype) and d_sigma.
 hipError_t launch_route_finalize(const unipool_shape& s, const int32_t* cnt_part, const float* psum_part,
                                  int32_t* counts, float* psum, hipStream_t st);
-// Set-up of the router weight gradient (gemm_mfma.hip) that the first workgroup of the dz kernel does on the way: row
-// offsets of the token chunks, the pointer table of the reduction and the page of zeros.
-struct RouteBwdPrep {
-    int32_t* off;                // [nchunks + 1], or null: nothing to do
-    int chunk_rows, nchunks;
-    void** table;                // dz, x, off
-    const void* x;
-    uint32_t* zeros;             // 64 words
-};
-// dsigma_part: one float per block of dz_tokens_per_block tokens.  d_sigma = nullptr: they stay there for a later kernel.
+// dsigma_part: one float per block of dz_tokens_per_block tokens, added up by the kernels of the contractions.
 // (The partial sums have the two areas of the router's block statistics, 2 E floats per 64 tokens.)
 inline int dz_tokens_per_block(const unipool_shape& s) { return s.E < 4 ? kRouterTokensPerBlock : s.E <= 256 ? 16 : 8; }
 hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, const int32_t* topk_idx,
                                const float* dgate, const float* aux_coef, void* dz,
-                               float* dsigma_part, float* d_sigma, const RouteBwdPrep& prep, hipStream_t st);
+                               float* dsigma_part, hipStream_t st);
 
 // ---- permute.hip ------------------------------------------------------------------
 hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* topk_idx,
@@ -78,7 +69,8 @@ hipError_t f32_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const
                          const void* const* d_act_l, const void* const* h_l, const void* const* dy_l,
                          const int32_t* const* offsets_l, float* dwgu, float* dwd, int accumulate, hipStream_t st);
 hipError_t f32_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz, float* dw,
-                            void* dx, int dx_accumulate, float* wpart, hipStream_t st);
+                            void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma, float* wpart,
+                            hipStream_t st);
 
 int num_cus();
 
@@ -99,11 +91,11 @@ hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a,
 hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,
                           const void* const* d_act_l, const void* const* h_l,
                           const void* const* dy_l, const int32_t* const* offsets_l,
-                          float* dwgu, float* dwd, int accumulate, const void* zeros,
-                          hipStream_t st);
+                          float* dwgu, float* dwd, int accumulate, hipStream_t st);
+hipError_t mfma_ffn_wgrad_layer(const unipool_shape& s, const void* x_perm, const void* d_act, const void* h, const void* dy,
+                                const int32_t* offsets, float* dwgu, float* dwd, hipStream_t st);     // added to dwgu, dwd
 bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx);
-RouteBwdPrep mfma_route_bwd_prep(const unipool_shape& s, const void* x, int32_t* tile_meta, void* zeros);
-hipError_t mfma_route_bwd_mm(const unipool_shape& s, const RouteBwdPrep& prep, const void* w, const void* dz,
+hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
                              float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,
                              int32_t* tile_meta, float* wpart, hipStream_t st);
 
@@ -116,7 +108,6 @@ hipError_t few_ffn_fwd(const unipool_shape& s, const void* x, const int32_t* off
                        const int32_t* slot_of_row = nullptr);
 
 // ---- small utilities (api.hip) ---------------------------------------------------------
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_set_ptrs(void** table, const void* p0, const void* p1, const void* p2,
                            const void* p3, const void* p4, hipStream_t st);
 

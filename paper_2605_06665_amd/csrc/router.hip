@@ -156,17 +156,8 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ topk_idx,
     const float* __restrict__ dgate, const float* __restrict__ aux_coef, int T, int E, int k,
     float sigma, float c, float eps, int softmax, int tok_per_block, TA* __restrict__ dz, int ldz,
-    float* __restrict__ dsigma_part, const RouteBwdPrep prep) {
+    float* __restrict__ dsigma_part) {
     constexpr int TPW = 64 / GS;
-    if (blockIdx.x == 0 && prep.off != nullptr) {
-        for (int i = threadIdx.x; i <= prep.nchunks; i += 256) prep.off[i] = min(T, i * prep.chunk_rows);
-        if (threadIdx.x < 64) prep.zeros[threadIdx.x] = 0u;
-        if (threadIdx.x == 0) {
-            prep.table[0] = dz;
-            prep.table[1] = const_cast<void*>(prep.x);
-            prep.table[2] = prep.off;
-        }
-    }
     __shared__ float lds_ds[kWavesPerBlock];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -275,11 +266,6 @@ __global__ __launch_bounds__(256) void route_bwd_dz_kernel(
         dsigma_part[blockIdx.x] = ((lds_ds[0] + lds_ds[1]) + lds_ds[2]) + lds_ds[3];
 }
 
-__global__ __launch_bounds__(256) void dsigma_finalize_kernel(const float* __restrict__ part, int n,
-                                                              float* __restrict__ out) {
-    block_sum_256(part, n, out);
-}
-
 }  // namespace
 
 namespace {
@@ -345,11 +331,11 @@ hipError_t launch_route_finalize(const unipool_shape& s, const int32_t* cnt_part
 
 hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, const int32_t* topk_idx,
                                const float* dgate, const float* aux_coef, void* dz,
-                               float* dsigma_part, float* d_sigma, const RouteBwdPrep& prep, hipStream_t st) {
+                               float* dsigma_part, hipStream_t st) {
     const int tokens = dz_tokens_per_block(s), nblocks = cdiv(s.T, tokens);
 #define UNIPOOL_DZ(TA, GS, VPL)                                                                        \
     route_bwd_dz_kernel<TA, GS, VPL><<<nblocks, 256, 0, st>>>(logits, topk_idx, dgate, aux_coef, s.T, s.E, \
-                                                              s.k, s.sigma, s.c, s.eps, s.router, tokens, (TA*)dz, dz_stride(s), dsigma_part, prep)
+                                                              s.k, s.sigma, s.c, s.eps, s.router, tokens, (TA*)dz, dz_stride(s), dsigma_part)
     if (s.dtype == UNIPOOL_BF16) {
         if (s.E <= 128) UNIPOOL_DZ(bf16, 16, 8);
         else if (s.E <= 256) UNIPOOL_DZ(bf16, 16, 16);
@@ -360,7 +346,6 @@ hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, cons
         else UNIPOOL_DZ(float, 32, 16);
     }
 #undef UNIPOOL_DZ
-    if (d_sigma) dsigma_finalize_kernel<<<1, 256, 0, st>>>(dsigma_part, nblocks, d_sigma);
     return hipGetLastError();
 }
 
