@@ -308,9 +308,10 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
     // Stage kt of this tile lives in X buffer (g0 + kt) mod 2 and W buffer (g0 + kt) mod 3: the
     // buffers rotate on from tile to tile, so the first stages of the next tile can be requested
     // while this tile's last stage and epilogue still hold theirs.
-    const int x0 = g0 & 1, w0 = g0 % 3;
-    auto xbuf = [&](int kt) { return (kt + x0) & 1; };
-    auto wbuf = [&](int kt) { return (kt + w0) % 3; };
+    // The loop carries their LDS offsets, of stage kt: xo (the other one: xo ^ XBYTES), and of W(kt), W(kt+1), W(kt+2).
+    static_assert((XBYTES & (XBYTES - 1)) == 0, "the other X buffer by an exclusive or");
+    unsigned xo = (g0 & 1) * XBYTES;
+    unsigned wo0 = WBASE + g0 % 3 * WBYTES, wo1 = WBASE + (g0 + 1) % 3 * WBYTES, wo2 = WBASE + (g0 + 2) % 3 * WBYTES;
     // Fragments of one slice: W block nb (16 columns x 32 indices, the MFMA A operand) and X fragment
     // a (16 rows x 32 indices, the B operand: a < MTV the upper rows of strip a, a >= MTV the lower rows
     // of strip a - MTV), one register set each.  A slice is two halves; slot nb * MTV + tm of the first
@@ -332,8 +333,8 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
         for (int nb = 0; nb < 4; nb++) noff[nb] = WTN::frag_off(wpos[nb >> 1] + 16 * (nb & 1), lane);
     }
     constexpr int ROWB = BK * 2;                                           // bytes per K-contiguous row
-    auto load_w = [&](int kt, int ks, int nb) {
-        const char* wb = smem + WBASE + wbuf(kt) * WBYTES;
+    auto load_w = [&](unsigned buf, int ks, int nb) {
+        const char* wb = smem + buf;
         if constexpr (WK) {
             wfr[nb] = lds_read16(wb + (wpos[nb >> 1] + 16 * (nb & 1)) * ROWB + (ks ? koff1 : koff0));
         } else {
@@ -341,9 +342,9 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
             wfr[nb] = lds_read_tr8(p, p + 4 * WTN::CPR * 16);
         }
     };
-    auto load_x = [&](int kt, int ks, int a) {
+    auto load_x = [&](unsigned buf, int ks, int a) {
         const int tm = a < MTV ? a : a - MTV, mh = a < MTV ? 0 : 1;
-        const char* xb = smem + xbuf(kt) * XBYTES;
+        const char* xb = smem + buf;
         xfr[a] = lds_read16(xb + ((wm + 2 * tm) * 32 + 16 * mh) * ROWB + (ks ? koff1 : koff0));
     };
     auto mfma_one = [&](int a, int nb) {
@@ -352,8 +353,8 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
     };
     // KTAIL: K is not a multiple of BK; chunks past K come from a page of zeros in both operands
     static_assert(!KTAIL || !WK, "the reduction tail is implemented for N-contiguous W only");
-    int xk[KTAIL ? XI : 1], wk[KTAIL ? WI : 1];   // first reduction index of the lane's chunk / row
     [[maybe_unused]] const void* const zeros = KTAIL ? zero_page() : nullptr;
+    int xk[KTAIL ? XI : 1], wk[KTAIL ? WI : 1];   // first reduction index of the lane's chunk / row
     if constexpr (KTAIL) {
 #pragma unroll
         for (int i = 0; i < XI; i++) {
@@ -363,19 +364,19 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
 #pragma unroll
         for (int i = 0; i < WI; i++) wk[i] = ((i * NW + wave) * 64 + lane) / WTN::CPR;
     }
-    // load i of stage kt of the tile the sources point at, into the buffer of stage kb of this tile
-    auto issue_x = [&](int kt, int i, int kb) {
+    // load i of stage kt of the tile the sources point at, into the given buffer
+    auto issue_x = [&](int kt, int i, unsigned buf) {
         if (!xload[i]) return;
         const char* src = xsrc[i] + (size_t)kt * BK * 2;
         if constexpr (KTAIL)
             if (kt * BK + xk[i] >= g.K) src = reinterpret_cast<const char*>(zeros);
-        glds16(src, lds0 + xbuf(kb) * XBYTES + ((i * NW + wave) * 64) * 16);
+        glds16(src, lds0 + buf + ((i * NW + wave) * 64) * 16);
     };
-    auto issue_w = [&](int kt, int i, int kb) {
+    auto issue_w = [&](int kt, int i, unsigned buf) {
         const char* src = wsrc[i] + (size_t)kt * wstep;
         if constexpr (KTAIL)
             if (kt * BK + wk[i] >= g.K) src = reinterpret_cast<const char*>(zeros);
-        glds16(src, lds0 + WBASE + wbuf(kb) * WBYTES + ((i * NW + wave) * 64) * 16);
+        glds16(src, lds0 + buf + ((i * NW + wave) * 64) * 16);
     };
     // One stage.  The wavefronts meet between the halves of the second slice: stage kt+1 has landed,
     // nobody reads stage kt any more, and the second half, whose operands are in registers, covers the
@@ -393,41 +394,41 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
             if constexpr (IW) {
 #pragma unroll
                 for (int u = 0; u < WI; u++)
-                    if (u * SL / WI == slot) issue_w(kt + 2, u, kt + 2);
+                    if (u * SL / WI == slot) issue_w(kt + 2, u, wo2);
             }
         };
         auto x_loads = [&](int slot) {
 #pragma unroll
             for (int u = 0; u < XI; u++)
-                if (u * HM2 / XI == slot && ix) issue_x(kt + 2, u, kt + 2);
+                if (u * HM2 / XI == slot && ix) issue_x(kt + 2, u, xo);
         };
         if constexpr (SL == 0 && IW) {
 #pragma unroll
-            for (int u = 0; u < WI; u++) issue_w(kt + 2, u, kt + 2);
+            for (int u = 0; u < WI; u++) issue_w(kt + 2, u, wo2);
         }
-        auto first_half = [&](int ks, int slot0) {
+        auto first_half = [&](int ks, int slot0) {         // of stage kt
 #pragma unroll
             for (int sl = 0; sl < HM1; sl++) {
                 mfma_one(sl % MTV, sl / MTV);
-                if (sl == 0) load_w(kt, ks, 3);                        // what the previous slice still held
-                if (sl >= 1 && sl <= M2) load_x(kt, ks, MTV + sl - 1);
+                if (sl == 0) load_w(wo0, ks, 3);                       // what the previous slice still held
+                if (sl >= 1 && sl <= M2) load_x(xo, ks, MTV + sl - 1);
                 w_loads(slot0 + sl);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto second_half = [&](int nkt, int nks, int slot0) {       // (nkt, nks): the slice that follows
+        auto second_half = [&](unsigned nxo, unsigned nwo, int nks, int slot0) {       // where the slice that follows is
 #pragma unroll
             for (int sl = 0; sl < HM2; sl++) {
                 mfma_one(MTV + sl % M2, sl / M2);
-                if (sl < MTV) load_x(nkt, nks, sl);
-                if (sl >= M2 && sl % M2 == 0) load_w(nkt, nks, sl / M2 - 1);
+                if (sl < MTV) load_x(nxo, nks, sl);
+                if (sl >= M2 && sl % M2 == 0) load_w(nwo, nks, sl / M2 - 1);
                 if (slot0 >= 0) w_loads(slot0 + sl);
                 else x_loads(sl);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
         first_half(0, 0);
-        second_half(kt, 1, HM1);
+        second_half(xo, wo0, 1, HM1);
         first_half(1, HM1 + HM2);
         // X(kt+1) and W(kt+1) must have landed.  Loads complete in issue order, and the only ones
         // issued after those two batches are the W loads of stage kt+2.
@@ -448,29 +449,32 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
         if constexpr (HM2 == 0) {
             if (ix) {
 #pragma unroll
-                for (int u = 0; u < XI; u++) issue_x(kt + 2, u, kt + 2);
+                for (int u = 0; u < XI; u++) issue_x(kt + 2, u, xo);
             }
         }
-        second_half(kt + 1, 0, -1);                   // after the last stage: unused, in bounds
+        second_half(xo ^ XBYTES, wo1, 0, -1);         // after the last stage: unused, in bounds
+        const unsigned w = wo0;
+        wo0 = wo1; wo1 = wo2; wo2 = w;
+        xo ^= XBYTES;
     };
     // prologue: X(0) W(0) X(1) W(1) W(2), less what the previous tile has requested already
     if (!(pre & 1)) {
 #pragma unroll
-        for (int i = 0; i < XI; i++) issue_x(0, i, 0);
+        for (int i = 0; i < XI; i++) issue_x(0, i, xo);
 #pragma unroll
-        for (int i = 0; i < WI; i++) issue_w(0, i, 0);
+        for (int i = 0; i < WI; i++) issue_w(0, i, wo0);
     }
     if (nk > 1) {
 #pragma unroll
-        for (int i = 0; i < XI; i++) issue_x(1, i, 1);
+        for (int i = 0; i < XI; i++) issue_x(1, i, xo ^ XBYTES);
         if (!(pre & 2)) {
 #pragma unroll
-            for (int i = 0; i < WI; i++) issue_w(1, i, 1);
+            for (int i = 0; i < WI; i++) issue_w(1, i, wo1);
         }
     }
     if (nk > 2) {
 #pragma unroll
-        for (int i = 0; i < WI; i++) issue_w(2, i, 2);
+        for (int i = 0; i < WI; i++) issue_w(2, i, wo2);
     }
     // stage 0 has landed when at most the two W batches of stages 1 and 2 are outstanding (the X
     // batch of stage 1, which may be shorter than XI loads, then has landed too: stricter than needed)
@@ -482,10 +486,10 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
     PHASE_CLOCK(cl0_);
 #endif
 #pragma unroll
-    for (int a = 0; a < MTV; a++) load_x(0, 0, a);
+    for (int a = 0; a < MTV; a++) load_x(xo, 0, a);
     if constexpr (MTV > 0) {
 #pragma unroll
-        for (int nb = 0; nb < 3; nb++) load_w(0, 0, nb);
+        for (int nb = 0; nb < 3; nb++) load_w(wo0, 0, nb);
     }
     {
         using T = std::integral_constant<bool, true>;
@@ -505,12 +509,12 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
         if (nxt.valid) {
             set_sources(nxt.expert, nxt.row0, nxt.rows, nxt.nt);
 #pragma unroll
-            for (int i = 0; i < XI; i++) issue_x(0, i, nk);
+            for (int i = 0; i < XI; i++) issue_x(0, i, xo);
 #pragma unroll
-            for (int i = 0; i < WI; i++) issue_w(0, i, nk);
+            for (int i = 0; i < WI; i++) issue_w(0, i, wo0);
             if (PREW1 && nk > 1) {
 #pragma unroll
-                for (int i = 0; i < WI; i++) issue_w(1, i, nk + 1);
+                for (int i = 0; i < WI; i++) issue_w(1, i, wo1);
             }
         }
     }
@@ -547,13 +551,12 @@ __device__ __forceinline__ void xw_tile(const GemmArgs& g, char* smem, TileRef c
         // buffer, region 2 (SwiGLU backward only) the W buffer that would otherwise hold W(1) of the
         // next tile.
         const int region = wave / SG::RW;
-        const int rbase = region == 0 ? xbuf(nk - 1) * XBYTES
-                                      : WBASE + (region == 1 ? wbuf(nk - 1) : wbuf(nk + 1)) * WBYTES;
+        // (by now the offsets are those of stage nk: the last stage's are xo ^ XBYTES and wo2)
+        const unsigned rbase = region == 0 ? xo ^ XBYTES : region == 1 ? wo2 : wo1;
         char* stg = smem + rbase + (wave % SG::RW) * SG::WSTG;
         char* stg2 = nullptr;
         if constexpr (SG::SPLIT)       // second areas: buffer 2, the rest behind the first areas in buffer 1
-            stg2 = smem + WBASE + (wave < SG::RW ? wbuf(nk + 1) * WBYTES + wave * SG::AREA
-                                                 : wbuf(nk - 1) * WBYTES + (NW - SG::RW + wave - SG::RW) * SG::AREA);
+            stg2 = smem + (wave < SG::RW ? wo1 + wave * SG::AREA : wo2 + (NW - SG::RW + wave - SG::RW) * SG::AREA);
         xw_staged_epilogue<EPI, NW, MTV, LH, ADD>(epi_args(g), AccArray<MTV>{acc}, stg, stg2, rows, row0, n0, f0, wm, 2, wn,
                                                   lane);
     }
@@ -616,9 +619,9 @@ __global__ __launch_bounds__(2 * BN, 2) void gemm_xw_kernel(const GemmArgs g) {
 // ---------------------------------------------------------------------------------------------
 // gemm_ptq: out[e][i][j] (+)= sum_l sum_{row in group e of layer l} P_l[row][i] * Q_l[row][j]
 // ---------------------------------------------------------------------------------------------
+// One weight gradient of all experts (or one matrix cut into chunks of rows, whose partial products are the "experts").
 struct PtqArgs {
     const void* const* P;        // device arrays of device pointers, one entry per layer
-// One weight gradient of all experts (or one matrix cut into chunks of rows, whose partial products are the "experts").
     const void* const* Q;
     const void* P1;              // the operands of a single layer or matrix (P, Q and off are null then)
     const void* Q1;
@@ -662,14 +665,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
     if (slot >= per_xcd) return;
     int lt = (blockIdx.x % kNumXcd) * per_xcd + slot;
     if (lt >= total) return;
-    const int e = lt / per_e;
-    // The 32 workgroups of an XCD run 32 consecutive tiles side by side and share their operand blocks
-    // through L2: with the shorter tile axis running fastest the 32 tiles form the squarest block
     const PtqArgs g = PAIR && lt >= total1 ? launch.second : launch.first;
     if (PAIR && lt >= total1) lt -= total1;
     const int n_layers = launch.n_layers, accumulate = launch.accumulate;
     const void* const zeros = zero_page();
     const int per_e = g.m_tiles * g.n_tiles;
+    const int e = lt / per_e;
+    // The 32 workgroups of an XCD run 32 consecutive tiles side by side and share their operand blocks
+    // through L2: with the shorter tile axis running fastest the 32 tiles form the squarest block
     // (about 6 x 5 instead of 2 x 16), which needs the fewest distinct operand blocks.
     const int idx = lt % per_e;
     const int m0 = (g.m_tiles <= g.n_tiles ? idx % g.m_tiles : idx / g.n_tiles) * BM;
@@ -790,12 +793,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
             if (over < ld_end - ld_r) break;
             over -= ld_end - ld_r;
         }
+        ld_r += over;
     };
+    next_layer();
     // Per-lane source addresses of the LPS loads of the K block at the cursor (P rows for i < PI, Q
     // rows after), worked out in one place per block so that the load slots between the MFMAs hold
-        ld_r += over;
     // nothing but the load.
-    next_layer();
     const void* blk_src[2 * PI];
     auto block_sources = [&]() {
         if (__builtin_expect(ld_r + BK <= ld_end, 1)) {
@@ -874,10 +877,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
         constexpr bool ISSUE = decltype(issue_c)::value;
         const int stage = kb % NS, nstage = (kb + 1) % NS;
         static_assert(LPS == 4, "load slots below");
-        if constexpr (ISSUE) {
-            block_sources();
         constexpr int HA = NA / 2, HS = HA * NB;          // slots of a half
         constexpr int GAP = HS == 16 ? 3 : 1;
+        if constexpr (ISSUE) {
+            block_sources();
         }
 #pragma unroll
         for (int s = 0; s < HS; s++) {
@@ -1106,9 +1109,6 @@ hipError_t run_ptq_form(PtqLaunch a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// the meeting counters live behind the largest possible tile table (total_rows / 256 + 2 E entries)
-int32_t* pair_counters(int32_t* meta, int E, int total_rows) {
-    return meta + kTileBase + 4 * (total_rows / kBM + 2 * E);
 template <int NW, bool PAIR> hipError_t run_ptq_nw(const PtqLaunch& a, bool stream, hipStream_t st) {
     return stream ? run_ptq_form<NW, true, PAIR>(a, st) : run_ptq_form<NW, false, PAIR>(a, st);
 }
@@ -1149,6 +1149,9 @@ hipError_t run_ptq(const PtqLaunch& a, bool stream, double rows, hipStream_t st)
     return run_ptq_nw<8, true>(a, stream, st);
 }
 
+// the meeting counters live behind the largest possible tile table (total_rows / 256 + 2 E entries)
+int32_t* pair_counters(int32_t* meta, int E, int total_rows) {
+    return meta + kTileBase + 4 * (total_rows / kBM + 2 * E);
 }
 
 // Timing aid of debugging builds: UNIPOOL_W0=1 makes every expert read the weights of expert 0, so that the
