@@ -138,9 +138,8 @@ class PoolStep:
         return -(-self.L // -(-self.L // most))          # as even as the number of accumulations allows
 
     def shape(self, sigma: float, L=None) -> B.Shape:
-        return B.Shape(T=self.T, d_model=self.d, d_ff=self.f, E=self.E, k=self.k, L=self.L if L is None else L,
-                       dtype=self.dtype, sigma=float(sigma), c=self.c, eps=self.eps,
-                       alpha_pool=self.alpha, router=self.router)
+        return B.Shape(self.T, self.d, self.f, self.E, self.k, self.L if L is None else L, self.dtype, float(sigma),
+                       self.c, self.eps, self.alpha, self.router)
 
     def _call(self, fn, *args):
         if not self.timing:
