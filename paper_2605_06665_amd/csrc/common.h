@@ -88,7 +88,7 @@ __device__ __forceinline__ void block_sum_256(const float* part, int n, float* o
 // ---- workspace layout ---------------------------------------------------------
 // The workspace is cut into fixed regions, all 256-byte aligned, sized from the shape.
 struct WsLayout {
-    size_t tile_meta;      // int32: [0] number of row tiles, then 3 ints per tile
+    size_t tile_meta;      // int32: [0] number of row tiles, 4 ints per tile from [64] on, then the meeting counters
     size_t chunk_hist;     // int32 [ceil(T/64)][E]   permute: per-64-token histograms/bases
     size_t psum_part;      // float [router blocks][E] partial score sums
     size_t dsigma_part;    // float [router blocks]

@@ -1149,9 +1149,9 @@ hipError_t run_ptq(const PtqLaunch& a, bool stream, double rows, hipStream_t st)
     return run_ptq_nw<8, true>(a, stream, st);
 }
 
-// the meeting counters live behind the largest possible tile table (total_rows / 256 + 2 E entries)
+// the meeting counters live behind the largest possible tile table (total_rows / 128 + 2 E entries)
 int32_t* pair_counters(int32_t* meta, int E, int total_rows) {
-    return meta + kTileBase + 4 * (total_rows / kBM + 2 * E);
+    return meta + kTileBase + 4 * ((size_t)total_rows / kSmallBM + 2 * E);
 }
 
 // Timing aid of debugging builds: UNIPOOL_W0=1 makes every expert read the weights of expert 0, so that the
