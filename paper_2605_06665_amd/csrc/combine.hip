@@ -1,5 +1,5 @@
 // Gate-weighted combine of the expert outputs (paper Eq. 2) and its backward.
-// One wavefront per token; rows move in 16-byte chunks; sums are taken in float in slot order.
+// One wavefront per token (the combine of few tokens: one per 64 chunks of a row); rows move in 16-byte chunks; sums are taken in float in slot order.
 #include "kernels.h"
 
 namespace unipool {
@@ -33,12 +33,13 @@ __device__ __forceinline__ void store_chunk(TA* p, const float (&v)[N]) {
 template <typename TA, int K>
 __global__ __launch_bounds__(256) void combine_kernel(const TA* __restrict__ y_perm,
                                                       const int32_t* __restrict__ row_of_slot,
-                                                      const float* __restrict__ gate, int T, int d,
+                                                      const float* __restrict__ gate, int T, int d, int parts,
                                                       TA* __restrict__ out) {
     constexpr int N = Vec<TA>::n;
-    const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    const int t = wave / parts;
     if (t >= T) return;
+    const int lane = (wave % parts) * 64 + (threadIdx.x & 63), lanes = parts * 64;      // of the token
     int rows[K];
     float g[K];
 #pragma unroll
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const TA* __restrict__ y_p
         g[j] = gate ? gate[(size_t)t * K + j] : 1.0f;
     }
     const int chunks = (d % N == 0) ? d / N : 0;   // misaligned rows take the scalar path
-    for (int c = lane; c < chunks; c += 64) {
+    for (int c = lane; c < chunks; c += lanes) {
         float v[K][N];
 #pragma unroll
         for (int j = 0; j < K; j++) load_chunk<TA, N>(y_perm + (size_t)rows[j] * d + (size_t)c * N, v[j]);
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const TA* __restrict__ y_p
         store_chunk<TA, N>(out + (size_t)t * d + (size_t)c * N, acc);
     }
     // tail elements when d is not a multiple of the chunk width
-    for (int c = chunks * N + lane; c < d; c += 64) {
+    for (int c = chunks * N + lane; c < d; c += lanes) {
         float acc = 0.f;
 #pragma unroll
         for (int j = 0; j < K; j++) acc += g[j] * to_f32(y_perm[(size_t)rows[j] * d + c]);
@@ -119,19 +120,28 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
     }
 }
 
+// Wavefronts that share a token's row in the combine: one per round of loads while the tokens alone do not fill the card,
+// so that the rounds do not wait for one another (launches back to back in a graph, one wavefront per token / this, us:
+// 48 tokens, k = 2, d_model 1536 2.3 / 2.0; k = 8, 1024 3.0 / 2.3; 1001 tokens 5.6 / 5.4; float, k = 2, 1536, 300 tokens
+// 4.0 / 2.7, 1001 6.1 / 4.8; but 3001 tokens, k = 2, 1536 6.6 / 6.9).
+int combine_parts(const unipool_shape& s) {
+    const int rounds = cdiv(s.d_model, 64 * (s.dtype == UNIPOOL_BF16 ? 8 : 4));
+    return s.T <= 2048 ? rounds : 1;
+}
+
 }  // namespace
 
 hipError_t launch_combine(const unipool_shape& s, const void* y_perm, const int32_t* row_of_slot,
                           const float* gate, void* out, hipStream_t st) {
-    const int nblocks = cdiv(s.T, 4);
+    const int parts = combine_parts(s), nblocks = cdiv(s.T * parts, 4);
     with_top_k(s.k, [&](auto kc) {
         constexpr int K = decltype(kc)::value;
         if (s.dtype == UNIPOOL_BF16)
             combine_kernel<bf16, K><<<nblocks, 256, 0, st>>>((const bf16*)y_perm, row_of_slot, gate, s.T, s.d_model,
-                                                             (bf16*)out);
+                                                             parts, (bf16*)out);
         else
             combine_kernel<float, K><<<nblocks, 256, 0, st>>>((const float*)y_perm, row_of_slot, gate, s.T, s.d_model,
-                                                              (float*)out);
+                                                              parts, (float*)out);
     });
     return hipGetLastError();
 }
