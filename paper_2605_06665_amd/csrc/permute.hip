@@ -1,7 +1,7 @@
 // Dispatch: builds the expert-contiguous row order and copies the token rows.
 //
 // The order is unique (expert-major, ascending token inside an expert), so it is computed
-// without order-dependent atomics:
+// without order-dependent atomics (up to 256 tokens and up to 4096 in one launch: see the kernels further down):
 //   1. hist    : one wavefront per chunk of 64 tokens builds, in LDS, a 64-bit token mask per
 //                expert (atomic OR, order-free) and writes the per-chunk histogram;
 //   2. scan    : one block per expert: its offset (sum of the counts of the experts before it) and
@@ -308,6 +308,78 @@ __global__ __launch_bounds__(256) void permute_small_kernel(const V* __restrict_
     }
 }
 
+// Up to 4096 tokens in one launch, while counting is shorter than two more launches: a workgroup of 16 tokens counts the
+// picks of all tokens before its own for itself, in LDS.  Three launches / this one (back to back in a graph, with the copy
+// and without), us: 300 tokens, k = 2, 24 experts of d_model 320 7.0 / 3.4, 6.7 / 2.6; 3001, 1, 16, 768 8.0 / 4.2,
+// 7.0 / 3.0; 4001, 2, 192, 1536 11.5 / 8.5, 7.9 / 3.5; 4096, 8, 512, 1024 23 / 17, 12.6 / 6.6.  The adds to one counter go one
+// after the other, at most one per token, which draws the line: with all tokens on one expert 3001 take 7.9 / 6.1, 6144
+// 8.9 / 10.9 (evenly spread 8.7 / 5.8); and every workgroup reads the picks: 32768 tokens, k = 2 55 / 68.
+constexpr int kCountTokens = 16, kCountThreads = 512;
+constexpr int kCountMaxTokens = 4096;
+
+template <typename V, int K>
+__global__ __launch_bounds__(kCountThreads) void permute_count_kernel(
+    const V* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ counts, int T, int E,
+    int row_words, V* __restrict__ x_perm, int32_t* __restrict__ expert_offsets, int32_t* __restrict__ row_of_slot,
+    int32_t* __restrict__ slot_of_row) {
+    constexpr int kWaves = kCountThreads / 64;
+    constexpr int kAhead = 8;                        // loads in flight per thread
+    __shared__ int before[kMaxE];                    // picks of the expert by the tokens before this workgroup's
+    __shared__ unsigned mask[kMaxE];                 // own tokens that picked the expert
+    __shared__ int base[kMaxE];                      // first row of the expert
+    __shared__ int wsum[kWaves];
+    __shared__ int own_row[kCountTokens * K];
+    static_assert(kMaxE == kCountThreads && kCountTokens <= 32, "an expert per thread, a bit per token");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t0 = blockIdx.x * kCountTokens;
+    const int own = tid < kCountTokens * K ? tid / K : kCountTokens;      // own token whose pick this thread places
+    const int own_e = own < kCountTokens && t0 + own < T ? topk_idx[(size_t)t0 * K + tid] : -1;
+    const int c = tid < E ? counts[tid] : 0;
+    before[tid] = 0;
+    mask[tid] = 0u;
+    int incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves - 1; w++)
+        if (w < wave) incl += wsum[w];
+    base[tid] = incl - c;
+    if (blockIdx.x == 0) {
+        if (tid < E) expert_offsets[tid] = incl - c;
+        if (tid == kCountThreads - 1) expert_offsets[E] = incl;
+    }
+    if (own_e >= 0) atomicOr(&mask[own_e], 1u << own);
+    const int n = t0 * K;
+    for (int i0 = tid; i0 < n; i0 += kAhead * kCountThreads) {
+        int e[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) e[u] = topk_idx[min(i0 + u * kCountThreads, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++)
+            if (i0 + u * kCountThreads < n) atomicAdd(&before[e[u]], 1);
+    }
+    __syncthreads();
+    if (own_e >= 0) {
+        const int r = base[own_e] + before[own_e] + __popc(mask[own_e] & ((1u << own) - 1u));
+        row_of_slot[(size_t)t0 * K + tid] = r;
+        slot_of_row[r] = t0 * K + tid;
+        own_row[tid] = r;
+    }
+    if (x_perm == nullptr) return;                   // index maps only
+    __syncthreads();
+    for (int i = wave; i < kCountTokens && t0 + i < T; i += kWaves)
+        for (int w = lane; w < row_words; w += 64) {
+            const V v = x[(size_t)(t0 + i) * row_words + w];
+#pragma unroll
+            for (int j = 0; j < K; j++) x_perm[(size_t)own_row[i * K + j] * row_words + w] = v;
+        }
+}
+
 }  // namespace
 
 hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* topk_idx,
@@ -327,6 +399,21 @@ hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* 
                 permute_small_kernel<uint32_t, K><<<nblocks, 256, 0, st>>>((const uint32_t*)x, topk_idx, counts, s.T, s.E,
                                                                            (int)(row_bytes / 4), (uint32_t*)x_perm,
                                                                            expert_offsets, row_of_slot, slot_of_row);
+        });
+        return hipGetLastError();
+    }
+    if (s.T <= kCountMaxTokens) {
+        const int nblocks = cdiv(s.T, kCountTokens);
+        with_top_k(s.k, [&](auto kc) {
+            constexpr int K = decltype(kc)::value;
+            if (row_bytes % 16 == 0)
+                permute_count_kernel<uint4, K><<<nblocks, kCountThreads, 0, st>>>(
+                    (const uint4*)x, topk_idx, counts, s.T, s.E, (int)(row_bytes / 16), (uint4*)x_perm, expert_offsets,
+                    row_of_slot, slot_of_row);
+            else
+                permute_count_kernel<uint32_t, K><<<nblocks, kCountThreads, 0, st>>>(
+                    (const uint32_t*)x, topk_idx, counts, s.T, s.E, (int)(row_bytes / 4), (uint32_t*)x_perm, expert_offsets,
+                    row_of_slot, slot_of_row);
         });
         return hipGetLastError();
     }
