@@ -1,5 +1,5 @@
-"""GPU: float products over pools of any size (batches of 64 experts in the search for a row tile, the list of tiles cut
-into eight parts, one tile and less than eight), widths that are a multiple of four and not, and weight gradients over
+"""GPU: float products over pools of any size (the search for a row tile by wavefronts up to 64 experts and by the workgroup
+beyond, the list of tiles cut into eight parts, one tile and less than eight), widths that are a multiple of four and not, and weight gradients over
 layers of which one is not aligned to 16 bytes."""
 import numpy as np
 import pytest
@@ -12,6 +12,8 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not has_gpu(), reason="needs a
 @pytest.mark.parametrize("E,d,f,rows", [(1, 20, 12, [5]), (3, 64, 68, [0, 1, 130]), (7, 33, 40, [64, 0, 65, 3, 0, 32, 31]),
                                         (64, 24, 21, [i % 5 for i in range(64)]), (65, 36, 32, [0] * 64 + [70]),
                                         (130, 16, 20, [(7 * i) % 67 for i in range(130)]),
+                                        (511, 12, 8, [i % 3 for i in range(511)]),
+                                        (512, 8, 16, [33] + [0] * 509 + [1, 66]), (66, 20, 12, [1] + [0] * 64 + [129]),
                                         (12, 252, 500, [40 + 9 * i for i in range(12)])])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_products(E, d, f, rows, shift):
