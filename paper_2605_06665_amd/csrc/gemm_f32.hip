@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     const TA* ca[2] = {nullptr, nullptr};      // the layer's operands
     const TA* cb[2] = {nullptr, nullptr};
     int total_k = k_end - k_begin;
-    bool fast = g.vec_a != 0 && g.vec_b != 0;  // (the layers' operands are only known by address here)
+    bool vec_a = g.vec_a != 0, vec_b = g.vec_b != 0;     // (the layers' operands are only known by address here)
     auto settle = [&](int i) {                 // move past ended layers
         while (cr[i] >= ce[i] && cl[i] < g.n_layers) {
             const int over = cr[i] - ce[i];
@@ -290,7 +290,8 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
             total_k = 0;
             for (int l = 0; l < g.n_layers; l++) {
                 total_k += layers[l].r1 - layers[l].r0;
-                fast = fast && (((size_t)layers[l].a | (size_t)layers[l].b) & (4 * sizeof(TA) - 1)) == 0;
+                vec_a = vec_a && ((size_t)layers[l].a & (4 * sizeof(TA) - 1)) == 0;
+                vec_b = vec_b && ((size_t)layers[l].b & (4 * sizeof(TA) - 1)) == 0;
             }
             A = layers[0].a;
             B = layers[0].b;
@@ -307,11 +308,14 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
 #pragma unroll
         for (int b = 0; b < NF; b++) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     // Operands of the next two stages on their way, as they are in memory (a conversion here would wait for the load).
-    // FAST: four values at a time without a branch, so that the loads of two stages stay in flight; a group past an end is
-    // loaded from the operand's start and put down as zeros.  The general form goes value by value.
+    // FA / FB: four values of the operand at a time without a branch, so that the loads of two stages stay in flight; a group
+    // past an end is loaded from the operand's start and put down as zeros.  An operand whose rows are not aligned to four
+    // values goes value by value, and the other one keeps its wide loads (12 experts, 3003 rows, us, one form for both / a form
+    // each: d 252, f 501 both backward products 83 / 67, weight gradients of two layers 103 / 86; d 250, f 500 77 / 61, 103 / 86;
+    // router backward, 4000 tokens of 90 experts, d 832 52 / 44).
     using Raw = typename std::conditional<std::is_same<TA, float>::value, f32x4, bf16x4>::type;
-    auto main_loop = [&](auto fast_c) __attribute__((always_inline)) {
-        constexpr bool FAST = decltype(fast_c)::value;
+    auto main_loop = [&](auto fa_c, auto fb_c) __attribute__((always_inline)) {
+        constexpr bool FA = decltype(fa_c)::value, FB = decltype(fb_c)::value;
         Raw ra[2][2], rb[2][2];
         int oka[2] = {0, 0}, okb[2] = {0, 0};      // bit set: the set's group exists
         auto fetch = [&](int s, auto set_c) __attribute__((always_inline)) {
@@ -351,17 +355,19 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
                         nb = brow[i] != nullptr ? k_end - k0 - kq[i] : 0;
                     }
                 }
-                if constexpr (FAST) {
+                if constexpr (FA) {
                     ra[set][i] = *reinterpret_cast<const Raw*>(na > 0 ? pa : A);
-                    rb[set][i] = *reinterpret_cast<const Raw*>(nb > 0 ? pb : B);
                     oka[i] = (oka[i] & ~(1 << set)) | ((na > 0) << set);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; q++) ra[set][i][q] = q < na ? pa[q] : (TA)0.f;
+                }
+                if constexpr (FB) {
+                    rb[set][i] = *reinterpret_cast<const Raw*>(nb > 0 ? pb : B);
                     okb[i] = (okb[i] & ~(1 << set)) | ((nb > 0) << set);
                 } else {
 #pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        ra[set][i][q] = q < na ? pa[q] : (TA)0.f;
-                        rb[set][i][q] = q < nb ? pb[q] : (TA)0.f;
-                    }
+                    for (int q = 0; q < 4; q++) rb[set][i][q] = q < nb ? pb[q] : (TA)0.f;
                 }
             }
         };
@@ -384,8 +390,8 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
             float* tb = ta + ABUF;
 #pragma unroll
             for (int i = 0; i < 2; i++) {
-                put(ta, ra[set][i], !FAST || (oka[i] >> set & 1), ATR, i);
-                put(tb, rb[set][i], !FAST || (okb[i] >> set & 1), BTR, i);
+                put(ta, ra[set][i], !FA || (oka[i] >> set & 1), ATR, i);
+                put(tb, rb[set][i], !FB || (okb[i] >> set & 1), BTR, i);
             }
             __syncthreads();                       // the other buffer is free: its readers passed the barrier before
             if (s + 2 < stages) fetch(s + 2, set_c);
@@ -416,8 +422,10 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
             }
         }
     };
-    if (fast) main_loop(std::true_type{});
-    else main_loop(std::false_type{});
+    if (vec_a && vec_b) main_loop(std::true_type{}, std::true_type{});
+    else if (vec_a) main_loop(std::true_type{}, std::false_type{});
+    else if (vec_b) main_loop(std::false_type{}, std::true_type{});
+    else main_loop(std::false_type{}, std::false_type{});
 
     // ---- epilogue: acc[a][b][r] = C[row wm WT + 16 a + l16][column wn WT + 16 b + 4 lg + r]
 #pragma unroll
