@@ -110,6 +110,15 @@ __device__ __forceinline__ int tile_of_block(int total) {
     return slot < per_xcd ? (blockIdx.x % 8) * per_xcd + slot : total;
 }
 
+// The same for weight gradients, whose tiles are as long as their expert has rows: the list is dealt to the XCDs in turn, a row
+// of n_tiles tiles at a time, which share an operand, so that the experts with many rows, wherever they are in the pool, are
+// spread over all of them (in eight parts / dealt, us: 32 experts of 320 x 640, 4500 rows of two layers, about half of them on
+// the first six 332 / 151, on six others 239 / 170, on all alike 155 / 154; whole experts in turn 162, 221, 159).
+__device__ __forceinline__ int dealt_tile_of_block(int n_tiles) {
+    const int slot = blockIdx.x / 8;
+    return (slot / n_tiles * 8 + blockIdx.x % 8) * n_tiles + slot % n_tiles;
+}
+
 // Row tile of the row groups, BM rows a tile, that this workgroup works on with which of n_tiles column tiles.  Up to 64
 // experts every wavefront finds it by itself; of larger pools a thread counts the tiles of two experts, so that the offsets
 // are waited for once.  (Batches of 64 experts one after the other, which every wavefront went through twice, once for the
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     if constexpr (LAYERS) {
         if (blockIdx.x == 0 && g.sum_part != nullptr) block_sum_256(g.sum_part, g.sum_n, g.sum_out);
         const int per = g.m_tiles * g.n_tiles;
-        const int tile = tile_of_block(g.E * per);
+        const int tile = dealt_tile_of_block(g.n_tiles);
         expert = tile / per;
         if (expert >= g.E) return;
         const int r = tile % per;
@@ -512,7 +521,7 @@ hipError_t run_layers_wt(Args a, int groups, hipStream_t st) {
     a.m_tiles = cdiv(a.M, 2 * WT);
     a.n_tiles = cdiv(a.N, 2 * WT);
     a.E = groups;
-    const long long grid = ((long long)groups * a.m_tiles * a.n_tiles + 7) / 8 * 8;
+    const long long grid = ((long long)groups * a.m_tiles + 7) / 8 * 8 * a.n_tiles;     // see dealt_tile_of_block
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
     gemm_f32_kernel<TA, WT, true, true, kFloat, true><<<(unsigned)grid, kThreads, 0, st>>>(a);
     return hipGetLastError();

@@ -63,3 +63,34 @@ def test_products(E, d, f, rows, shift):
         want = np.concatenate([dh * b[r] * sg * (1 + a[r] * (1 - sg)), dh * a[r] * sg], axis=1)
         for got, w in ((a[r], z[:, :f]), (b[r], z[:, f:]), (y[r], h[r] @ wd[e].T), (dact[r], want), (dx[r], dact[r] @ wgu[e])):
             assert rel_err(got, w) <= TOL["f32"], e
+
+
+def test_weight_gradients_of_skewed_pools_use_the_whole_card():
+    """As many rows take about as long whether they are spread evenly or half of them are with the first six experts of 32 (4500
+    rows, 320 x 640, two layers: 155 us both; 332 for the second where the experts were cut into eight parts in order)."""
+    import torch
+    import paper_2605_06665_amd as U
+    E, d, f, S, L = 32, 320, 640, 4500, 2
+    sh = U.Shape(T=S, d_model=d, d_ff=f, E=E, k=1, L=L, dtype=U.F32, sigma=1.0, c=1.0, eps=1e-6, alpha_pool=0.0, router=0)
+    ws = torch.empty(U.workspace_bytes(sh), dtype=torch.uint8, device="cuda:0")
+    x, dy, h, dact = (torch.randn((S, n), device="cuda:0") for n in (d, d, f, 2 * f))
+    dwgu, dwd = torch.empty((E, 2 * f, d), device="cuda:0"), torch.empty((E, d, f), device="cuda:0")
+
+    def best_time(rows):
+        off = torch.from_numpy(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)).cuda()
+        tabs = [torch.tensor([t.data_ptr()] * L, dtype=torch.int64, device="cuda:0") for t in (x, dact, h, dy, off)]
+        times = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                U.expert_wgrad(sh, L, *tabs, dwgu, dwd, False, ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    even = [S // E + (i < S % E) for i in range(E)]
+    skewed = [375] * 6 + [86] * 25 + [100]
+    assert sum(skewed) == S
+    assert best_time(skewed) <= 1.5 * best_time(even)
