@@ -1,5 +1,7 @@
 // Gate-weighted combine of the expert outputs (paper Eq. 2) and its backward.
 // One wavefront per token (the combine of few tokens: one per 64 chunks of a row); rows move in 16-byte chunks; sums are taken in float in slot order.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace unipool {
@@ -33,13 +35,12 @@ __device__ __forceinline__ void store_chunk(TA* p, const float (&v)[N]) {
 template <typename TA, int K>
 __global__ __launch_bounds__(256) void combine_kernel(const TA* __restrict__ y_perm,
                                                       const int32_t* __restrict__ row_of_slot,
-                                                      const float* __restrict__ gate, int T, int d, int parts,
+                                                      const float* __restrict__ gate, int T, int d,
                                                       TA* __restrict__ out) {
     constexpr int N = Vec<TA>::n;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    const int t = wave / parts;
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
-    const int lane = (wave % parts) * 64 + (threadIdx.x & 63), lanes = parts * 64;      // of the token
+    const int lane = blockIdx.y * 64 + (threadIdx.x & 63), lanes = gridDim.y * 64;      // of the token
     int rows[K];
     float g[K];
 #pragma unroll
@@ -120,28 +121,31 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
     }
 }
 
-// Wavefronts that share a token's row in the combine: one per round of loads while the tokens alone do not fill the card,
-// so that the rounds do not wait for one another (launches back to back in a graph, one wavefront per token / this, us:
-// 48 tokens, k = 2, d_model 1536 2.3 / 2.0; k = 8, 1024 3.0 / 2.3; 1001 tokens 5.6 / 5.4; float, k = 2, 1536, 300 tokens
-// 4.0 / 2.7, 1001 6.1 / 4.8; but 3001 tokens, k = 2, 1536 6.6 / 6.9).
+// Wavefronts that share a token's row in the combine (the second dimension of the grid): one per round of loads while the
+// tokens alone do not fill the card, so that the rounds do not wait for one another (launches back to back in a graph, rows in
+// the caches, one wavefront per token / this, us: 48 tokens, k = 2, d_model 1536 2.36 / 2.02; k = 8, 1024 2.68 / 2.22; 1001
+// tokens, k = 2, 1536 2.74 / 2.47; 2048 3.33 / 3.20; but 6000 tokens, k = 3, 832 5.97 / 6.36, and at 32768 46.5 / 49; float,
+// 300 tokens, 1536 2.83 / 2.25, 3001 tokens, k = 3, 1000 8.0 / 9.1).  A list of wavefronts that each found its token by a
+// division cost the many short rows of the largest calls more than it gave the few (20600 tokens, k = 2, d_model 64
+// 5.54, now 4.23).
 int combine_parts(const unipool_shape& s) {
     const int rounds = cdiv(s.d_model, 64 * (s.dtype == UNIPOOL_BF16 ? 8 : 4));
-    return s.T <= 2048 ? rounds : 1;
+    return s.T <= 2048 ? std::min(rounds, 64) : 1;
 }
 
 }  // namespace
 
 hipError_t launch_combine(const unipool_shape& s, const void* y_perm, const int32_t* row_of_slot,
                           const float* gate, void* out, hipStream_t st) {
-    const int parts = combine_parts(s), nblocks = cdiv(s.T * parts, 4);
+    const dim3 grid(cdiv(s.T, 4), combine_parts(s));
     with_top_k(s.k, [&](auto kc) {
         constexpr int K = decltype(kc)::value;
         if (s.dtype == UNIPOOL_BF16)
-            combine_kernel<bf16, K><<<nblocks, 256, 0, st>>>((const bf16*)y_perm, row_of_slot, gate, s.T, s.d_model,
-                                                             parts, (bf16*)out);
+            combine_kernel<bf16, K><<<grid, 256, 0, st>>>((const bf16*)y_perm, row_of_slot, gate, s.T, s.d_model,
+                                                          (bf16*)out);
         else
-            combine_kernel<float, K><<<nblocks, 256, 0, st>>>((const float*)y_perm, row_of_slot, gate, s.T, s.d_model,
-                                                              parts, (float*)out);
+            combine_kernel<float, K><<<grid, 256, 0, st>>>((const float*)y_perm, row_of_slot, gate, s.T, s.d_model,
+                                                           (float*)out);
     });
     return hipGetLastError();
 }
