@@ -124,7 +124,9 @@ def test_odd_pools_take_any_alignment(E, d, T, shifted):
 @pytest.mark.parametrize("E,T,k,d", [(1, 300, 1, 64), (3, 1000, 2, 64), (4, 1000, 2, 192), (5, 17, 1, 128), (32, 400, 2, 320),
                                      (40, 129, 3, 64), (128, 400, 2, 192), (136, 70, 2, 320), (256, 15, 1, 64),
                                      (257, 300, 3, 64), (264, 33, 8, 192), (512, 9, 8, 128), (512, 700, 8, 192),
-                                     (200, 17000, 1, 64)])
+                                     (200, 17000, 1, 64),
+                                     # 2048, 2049 and 4125 partial sums of d_sigma: whole and cut rounds of its loads
+                                     (8, 32768, 1, 64), (8, 32784, 1, 64), (264, 33000, 1, 64)])
 @pytest.mark.parametrize("router", [0, 1])
 def test_blocks_of_tokens(E, T, k, d, router):
     """Blocks of 8, 16 and 64 tokens with ends inside them, logits and dx in tiles of 128 x 128 and 128 x 256 whose rows
