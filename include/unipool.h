@@ -101,6 +101,22 @@ int unipool_version(void);
 int unipool_fast_path(const unipool_shape* shape);
 
 /*
+ * Which forms of the bfloat16 kernels the expert products and weight gradients of a shape take: for tests and
+ * measurements, as the form changes no bit of a result.  n_layers and accumulate are those of unipool_expert_wgrad
+ * (1 and 1: the gradients of unipool_expert_ffn_bwd).
+ * Returns a bit mask, 0 in float mode; negative on invalid arguments.
+ */
+#define UNIPOOL_SMALL_GATE_UP       1   /* tiles of 128 x 128 instead of 256 x 256: the product of w_gate_up in the forward pass, */
+#define UNIPOOL_SMALL_DOWN          2   /* of w_down in the forward pass, */
+#define UNIPOOL_SMALL_DH            4   /* of w_down in the backward pass, */
+#define UNIPOOL_SMALL_DX            8   /* of w_gate_up in the backward pass, */
+#define UNIPOOL_SMALL_WGRAD        16   /* the weight gradients */
+#define UNIPOOL_WGRAD_TWO_LAUNCHES 32   /* the weight gradients of unipool_expert_wgrad in a launch each */
+#define UNIPOOL_WGRAD_STREAMED     64   /* gradients read and written past the caches */
+#define UNIPOOL_FEW_ROWS          128   /* the forward products take neither tile but stream the weights to registers */
+int unipool_tile_forms(const unipool_shape* shape, int n_layers, int accumulate);
+
+/*
  * Router of one layer (Sec. 4.3, Eq. 7 and the top-k paragraph).
  *   z = x W^T (float accumulate);  n = ||z||_2;  s_i = sigma c max(0, z_i/(n+eps));
  *   topk_idx[t, :] = the k experts with the largest logits, in descending order,

@@ -28,7 +28,7 @@ class Shape(ctypes.Structure):
                 ("eps", ctypes.c_float), ("alpha_pool", ctypes.c_float), ("router", ctypes.c_int32)]
 
 
-ENTRY_POINTS = ("unipool_workspace_bytes", "unipool_last_error", "unipool_version", "unipool_fast_path", "unipool_route",
+ENTRY_POINTS = ("unipool_workspace_bytes", "unipool_last_error", "unipool_version", "unipool_fast_path", "unipool_tile_forms", "unipool_route",
                 "unipool_route_bwd", "unipool_permute", "unipool_permute_static", "unipool_expert_ffn_fwd", "unipool_expert_ffn_fwd_gather",
                 "unipool_expert_ffn_recompute", "unipool_expert_ffn_bwd", "unipool_expert_wgrad", "unipool_combine",
                 "unipool_combine_bwd", "unipool_pool_aux_loss", "unipool_estimate_c",
@@ -58,6 +58,8 @@ def load_library():
         lib.unipool_version.argtypes = []
         lib.unipool_fast_path.restype = I
         lib.unipool_fast_path.argtypes = [SP]
+        lib.unipool_tile_forms.restype = I
+        lib.unipool_tile_forms.argtypes = [SP, I, I]
         sigs = {
             "unipool_route": [SP] + [P] * 7 + [P, Z, P],
             "unipool_route_bwd": [SP] + [P] * 9 + [I, P, Z, P],
@@ -95,6 +97,17 @@ def fast_path(shape: Shape) -> int:
     MFMA, bit 2 fused router kernel)."""
     rc = load_library().unipool_fast_path(ctypes.byref(shape))
     _check(rc if rc < 0 else 0, "unipool_fast_path")
+    return rc
+
+
+# bits of tile_forms
+SMALL_GATE_UP, SMALL_DOWN, SMALL_DH, SMALL_DX, SMALL_WGRAD, WGRAD_TWO_LAUNCHES, WGRAD_STREAMED, FEW_ROWS = (1 << i for i in range(8))
+
+
+def tile_forms(shape: Shape, n_layers: int = 1, accumulate: bool = True) -> int:
+    """Bit mask of the kernel forms that the expert products and the weight gradients of n_layers layers take."""
+    rc = load_library().unipool_tile_forms(ctypes.byref(shape), int(n_layers), int(bool(accumulate)))
+    _check(rc if rc < 0 else 0, "unipool_tile_forms")
     return rc
 
 

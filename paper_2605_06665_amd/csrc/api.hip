@@ -117,9 +117,11 @@ int need_ws(const unipool_shape* s, void* ws, size_t ws_bytes, const char* fn) {
 
 // Second tile table of an FFN entry point, in the area of the router gradient's partial products (which no FFN entry point uses), or
 // null where it does not fit there.
+bool extra_table_fits(const unipool_shape& s, const WsLayout& w) {
+    return (64 + 4 * ((size_t)s.T * s.k / 128 + 2 * (size_t)s.E)) * sizeof(int32_t) <= w.total - w.wpart;
+}
 int32_t* extra_table(const unipool_shape& s, const WsLayout& w, void* ws) {
-    const size_t need = (64 + 4 * ((size_t)s.T * s.k / 128 + 2 * (size_t)s.E)) * sizeof(int32_t);
-    return need <= w.total - w.wpart ? (int32_t*)((char*)ws + w.wpart) : nullptr;
+    return extra_table_fits(s, w) ? (int32_t*)((char*)ws + w.wpart) : nullptr;
 }
 
 #define REQUIRE_PTR(p)                                                                  \
@@ -155,6 +157,15 @@ int unipool_fast_path(const unipool_shape* shape) {
     PROLOGUE();
     return (mfma_ffn_supported(*shape) ? UNIPOOL_FAST_EXPERTS : 0) | (mfma_router_supported(*shape) ? UNIPOOL_FAST_ROUTER : 0) |
            (router_fused_supported(*shape) ? UNIPOOL_FAST_ROUTER_FUSED : 0);
+}
+
+int unipool_tile_forms(const unipool_shape* shape, int n_layers, int accumulate) {
+    PROLOGUE();
+    if (n_layers < 1 || n_layers > 256)
+        return set_error(UNIPOOL_EINVAL, "%s: n_layers=%d outside [1, 256]", __func__, n_layers);
+    if (!mfma_ffn_supported(*shape)) return 0;
+    return mfma_tile_forms(*shape, extra_table_fits(*shape, ws_layout(*shape)), n_layers, accumulate != 0) |
+           (few_rows_supported(*shape) ? UNIPOOL_FEW_ROWS : 0);
 }
 
 int unipool_route(const unipool_shape* shape, const void* x, const void* w_router,

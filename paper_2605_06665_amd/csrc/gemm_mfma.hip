@@ -1123,7 +1123,10 @@ template <int NW, bool PAIR> hipError_t run_ptq_nw(const PtqLaunch& a, bool stre
 // Both gradients go out in one launch, the second's tiles in the wake of the first's (16 of 576 x 320, 1500 rows: two
 // launches 93, one 52; 200 of 640 x 1024, 28 rows: 336 / 320), except where each is many rounds of long tiles: then tiles of
 // both kinds side by side share less in L2 (192 of 1536 x 4096, 2728 rows: 17.1 / 17.4 ms).
-hipError_t run_ptq(const PtqLaunch& a, bool stream, double rows, hipStream_t st) {
+struct PtqForm {
+    bool small, two_launches, stream;
+};
+PtqForm ptq_form(const PtqLaunch& a, double rows, bool stream) {
     const double cus = num_cus();
     auto tiles = [&](int bm) {
         return (double)a.E * ((double)cdiv(a.first.mdim, bm) * cdiv(a.first.ndim, bm) +
@@ -1137,16 +1140,19 @@ hipError_t run_ptq(const PtqLaunch& a, bool stream, double rows, hipStream_t st)
 #ifdef UNIPOOL_DEBUG_SWITCHES
     if (const char* e = getenv("UNIPOOL_PTQ")) take_small = e[0] == '1';
 #endif
-    if (take_small) return run_ptq_nw<4, true>(a, stream, st);
-    if (rows > 448 && nb > 8 * cus && a.off != nullptr) {
+    return PtqForm{take_small, !take_small && rows > 448 && nb > 8 * cus, stream};
+}
+hipError_t run_ptq(const PtqLaunch& a, const PtqForm& form, hipStream_t st) {
+    if (form.small) return run_ptq_nw<4, true>(a, form.stream, st);
+    if (form.two_launches && a.off != nullptr) {          // (a single layer's operands only come in one launch)
         PtqLaunch one = a;
         one.second = PtqArgs{};
-        hipError_t e = run_ptq_nw<8, false>(one, stream, st);
+        hipError_t e = run_ptq_nw<8, false>(one, form.stream, st);
         if (e != hipSuccess) return e;
         one.first = a.second;
-        return run_ptq_nw<8, false>(one, stream, st);
+        return run_ptq_nw<8, false>(one, form.stream, st);
     }
-    return run_ptq_nw<8, true>(a, stream, st);
+    return run_ptq_nw<8, true>(a, form.stream, st);
 }
 
 // the meeting counters live behind the largest possible tile table (total_rows / 128 + 2 E entries)
@@ -1192,8 +1198,8 @@ hipError_t run_grouped(const GemmArgs& a, int tile, hipStream_t st) {
 // below a multiple of the tile already gives part of the experts one tile more.
 double row_tiles(double r, int bm) {
     const double s = 0.5 * sqrt(r);
-    double m = 1.0;
-    for (int j = 1; bm * j < r + s; j++) m += std::min(1.0, (r + s - bm * j) / (2.0 * s));
+    double m = std::max(1.0, std::floor((r - s) / bm) + 1.0);          // tiles that every expert takes
+    for (double j = m; bm * j < r + s; j++) m += std::min(1.0, (r + s - bm * j) / (2.0 * s));
     return m;
 }
 
@@ -1209,8 +1215,8 @@ double row_tiles(double r, int bm) {
 // together are 10 % shorter than with big tiles alone (small tiles alone: 9 %), the worst shape 2 % longer and the best 26 %
 // shorter.  One layer, us, big / small: down projection of 16 experts of 768 x 2048, 188 rows each (48 tiles / 192) 41 / 27,
 // dX of these 67 / 39, dH 34 / 27; but gate and up of 192 experts of 1536 x 4096, 341 rows each 1880 / 2700.
-int tile_form(const unipool_shape& s, int N, int which, const int32_t* extra) {
-    if (extra == nullptr) return TILE_BIG;
+int tile_form(const unipool_shape& s, int N, int which, bool extra) {
+    if (!extra) return TILE_BIG;                       // there is no room for a second table
 #ifdef UNIPOOL_DEBUG_SWITCHES
     if (const char* e = getenv("UNIPOOL_TILES")) return (atoi(e) >> (4 * which)) & 15;    // a digit per product
 #endif
@@ -1266,8 +1272,8 @@ hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const in
                            const void* wgu, void* a_out, void* b_out, void* h_out, int32_t* tile_meta,
                            int32_t* extra, hipStream_t st, const int32_t* slot_of_row) {
     const int d = s.d_model, f = s.d_ff;
-    const int tile = tile_form(s, 2 * f, 0, extra);
-    hipError_t e = build_tiles(s, offsets, tile, tile_form(s, d, 1, extra), tile_meta, extra, st);
+    const int tile = tile_form(s, 2 * f, 0, extra != nullptr);
+    hipError_t e = build_tiles(s, offsets, tile, tile_form(s, d, 1, extra != nullptr), tile_meta, extra, st);
     if (e != hipSuccess) return e;
     GemmArgs a = {};
     a.X = (const bf16*)x_perm; a.ldx = d;
@@ -1289,8 +1295,8 @@ hipError_t mfma_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_
     b.X = (const bf16*)h_out; b.ldx = f;
     b.W = (const bf16*)wd; b.w_stride = debug_w_stride((long long)d * f); b.ldw = f;
     b.K = f; b.N = d;
-    const int tile = tile_form(s, d, 1, extra);
-    b.tile_meta = tile == tile_form(s, 2 * f, 0, extra) ? tile_meta : extra; b.launch_slot = 1; b.out0 = y; b.ldo = d;
+    const int tile = tile_form(s, d, 1, extra != nullptr);
+    b.tile_meta = tile == tile_form(s, 2 * f, 0, extra != nullptr) ? tile_meta : extra; b.launch_slot = 1; b.out0 = y; b.ldo = d;
     if (b.K >= kPairMinK) { b.pair_cnt = pair_counters(tile_meta, s.E, S); b.pair_cap = kPairCap; }
     return run_grouped<true, EPI_STORE>(b, tile, st);
 }
@@ -1299,7 +1305,7 @@ hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_
                           const int32_t* offsets, const void* wgu, const void* wd, void* dx,
                           void* d_act, int32_t* tile_meta, int32_t* extra, hipStream_t st) {
     const int S = s.T * s.k, d = s.d_model, f = s.d_ff;
-    const int tile0 = tile_form(s, f, 2, extra), tile1 = tile_form(s, d, 3, extra);
+    const int tile0 = tile_form(s, f, 2, extra != nullptr), tile1 = tile_form(s, d, 3, extra != nullptr);
     hipError_t e = build_tiles(s, offsets, tile0, tile1, tile_meta, extra, st);
     if (e != hipSuccess) return e;
     GemmArgs a = {};   // dH = dY W_down (W_down[e] is [d][f]: reduction index strided), then SwiGLU backward
@@ -1319,21 +1325,39 @@ hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_
     return run_grouped<false, EPI_STORE>(b, tile1, st);
 }
 
-static hipError_t ffn_wgrad(const unipool_shape& s, PtqLaunch a, float* dwgu, float* dwd, hipStream_t st) {
+// Sizes of both gradients of a.n_layers layers, and the form of their launch.
+static PtqForm set_wgrad_sizes(const unipool_shape& s, PtqLaunch& a) {
     const int d = s.d_model, f = s.d_ff;
+    a.E = s.E;
+    a.first.mdim = 2 * f; a.first.ndim = d;            // d_w_gate_up[e][n][c] = sum d_act[row][n] * x_perm[row][c]
+    a.first.out_stride = 2LL * f * d;
+    a.second.mdim = d; a.second.ndim = f;              // d_w_down[e][c][n] = sum dy[row][c] * h[row][n]
+    a.second.out_stride = (long long)d * f;
     // Smaller gradients are still in the last-level cache (256 MB) when the next layer adds to them.  One layer's whole
     // backward call, k = 2, plain / streamed, us: 16 experts of 768 x 1024 (151 MB), 256 tokens 106 / 124, 4096 tokens
     // 214 / 207; 14 experts of 1024 x 1024 (176 MB) 147 / 138 and 224 / 208; 64 experts of 768 x 2048 (1.2 GB) 669 / 608
     // and 770 / 712.
     const bool stream = 12ll * s.E * d * f > (160ll << 20);
-    a.E = s.E;
-    PtqArgs& gu = a.first;     // d_w_gate_up[e][n][c] = sum d_act[row][n] * x_perm[row][c]
-    gu.mdim = 2 * f; gu.ndim = d;
-    gu.out = dwgu; gu.out_stride = 2LL * f * d;
-    PtqArgs& dn = a.second;    // d_w_down[e][c][n] = sum dy[row][c] * h[row][n]
-    dn.mdim = d; dn.ndim = f;
-    dn.out = dwd; dn.out_stride = (long long)d * f;
-    return run_ptq(a, stream, (double)a.n_layers * s.T * s.k / s.E, st);
+    return ptq_form(a, (double)a.n_layers * s.T * s.k / s.E, stream);
+}
+
+static hipError_t ffn_wgrad(const unipool_shape& s, PtqLaunch a, float* dwgu, float* dwd, hipStream_t st) {
+    const PtqForm form = set_wgrad_sizes(s, a);
+    a.first.out = dwgu;
+    a.second.out = dwd;
+    return run_ptq(a, form, st);
+}
+
+int mfma_tile_forms(const unipool_shape& s, bool extra, int n_layers, int accumulate) {
+    const int N[4] = {2 * s.d_ff, s.d_model, s.d_ff, s.d_model};
+    int forms = 0;
+    for (int which = 0; which < 4; which++)
+        if (tile_form(s, N[which], which, extra) == TILE_SMALL) forms |= UNIPOOL_SMALL_GATE_UP << which;
+    PtqLaunch a = {};
+    a.n_layers = n_layers; a.accumulate = accumulate;
+    const PtqForm form = set_wgrad_sizes(s, a);
+    return forms | (form.small ? UNIPOOL_SMALL_WGRAD : 0) | (form.two_launches ? UNIPOOL_WGRAD_TWO_LAUNCHES : 0) |
+           (form.stream ? UNIPOOL_WGRAD_STREAMED : 0);
 }
 
 hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* const* x_perm_l,

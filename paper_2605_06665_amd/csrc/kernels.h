@@ -94,6 +94,7 @@ hipError_t mfma_ffn_wgrad(const unipool_shape& s, int n_layers, const void* cons
                           float* dwgu, float* dwd, int accumulate, hipStream_t st);
 hipError_t mfma_ffn_wgrad_layer(const unipool_shape& s, const void* x_perm, const void* d_act, const void* h, const void* dy,
                                 const int32_t* offsets, float* dwgu, float* dwd, hipStream_t st);     // added to dwgu, dwd
+int mfma_tile_forms(const unipool_shape& s, bool extra, int n_layers, int accumulate);
 bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx);
 hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
                              float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,

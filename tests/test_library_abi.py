@@ -77,3 +77,23 @@ def test_fast_path_reports_the_kernel_families(U):
     assert U.fast_path(sh(dtype=U.F32)) == 0            # float mode: plain kernels throughout
     with pytest.raises(U.UniPoolError, match="k=9"):
         U.fast_path(sh(k=9))
+
+
+def test_tile_forms_are_found_at_any_number_of_rows(U):
+    """The choice is made on the host in every call: its time may not grow with the rows (134 million rows of one expert are
+    1.5 million tiles of both sizes; loops over them took 10 ms)."""
+    import time
+    sh = U.Shape(T=134_000_000, d_model=8192, d_ff=64, E=1, k=1, L=1, dtype=U.BF16, sigma=1.0, c=2.5, eps=1e-6, alpha_pool=0.01)
+    best = 1.0
+    for _ in range(3):
+        t0 = time.perf_counter()
+        forms = U.tile_forms(sh)
+        best = min(best, time.perf_counter() - t0)
+    assert best < 1e-3
+    # 64 columns (dH) are half a small tile and a quarter of a large one, 8192 whole tiles of both
+    from paper_2605_06665_amd import binding as B
+    assert forms & (B.SMALL_DH | B.SMALL_DX) == B.SMALL_DH
+    with pytest.raises(U.UniPoolError, match="n_layers=0"):
+        U.tile_forms(sh, 0, False)
+    sh.dtype = U.F32
+    assert U.tile_forms(sh) == 0
