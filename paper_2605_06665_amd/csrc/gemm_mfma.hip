@@ -1210,10 +1210,13 @@ double row_tiles(double r, int bm) {
 //   small: ceil(tiles / 512) rounds, two tiles to a CU, of 2 (128 + 0.4 rows), times 0.9 (gate and up 0.95, whose rows of 64
 //          + 64 columns are stored in shorter pieces) since one workgroup's epilogue runs beside the other's loop; up to 256
 //          tiles every workgroup has a CU to itself, which takes 0.6 of that.
-// So small tiles are taken where big ones leave CUs without work or columns without use.  Over 90 shapes (8 to 380
-// experts, d_model 256 to 1472, d_ff 256 to 4096, 2 to 18700 rows per expert, all ways of routing) both FFN entry points
-// together are 10 % shorter than with big tiles alone (small tiles alone: 9 %), the worst shape 2 % longer and the best 26 %
-// shorter.  One layer, us, big / small: down projection of 16 experts of 768 x 2048, 188 rows each (48 tiles / 192) 41 / 27,
+// So small tiles are taken where big ones leave CUs without work or columns without use.  Where big tiles all run at once and
+// small ones two to a CU, the longest CU gets 256 columns either way, and with few rows there is little epilogue to overlap: big
+// ones then (dX of 31 experts, 1280 columns, 6 rows each, share of both backward products: 5.7 to 7.9 % longer in small
+// tiles; 29 of 1600, 44 rows 3 to 4 %; 33 of 1088, 53 rows 3.6 %; 97 of 320, 56 rows 2 %; but 30 of 1152, 61 rows 4 to 5 %
+// shorter, 23 of 1856, 64 rows 1 %).  Over 218 shapes (4 to 512 experts, d_model 64 to 1664, d_ff 64 to 4096, 1 to 37000
+// rows per expert, even and skewed routing) both FFN entry points together are 11 % shorter than with big tiles alone, the
+// worst shape 2 % longer and the best 46 % shorter; the worst single entry point is 4 % longer.  One layer, us, big / small: down projection of 16 experts of 768 x 2048, 188 rows each (48 tiles / 192) 41 / 27,
 // dX of these 67 / 39, dH 34 / 27; but gate and up of 192 experts of 1536 x 4096, 341 rows each 1880 / 2700.
 int tile_form(const unipool_shape& s, int N, int which, bool extra) {
     if (!extra) return TILE_BIG;                       // there is no room for a second table
@@ -1225,6 +1228,7 @@ int tile_form(const unipool_shape& s, int N, int which, bool extra) {
     const double nb = s.E * mb * cdiv(N, kBN), ns = s.E * ms * cdiv(N, kSmallBN);
     const int cus = num_cus();
     const double big = std::ceil(nb / cus) * (kBN + 0.4 * r / mb);
+    if (nb <= cus && ns > cus && r < 60) return TILE_BIG;
     const double small = (ns <= cus ? 0.6 : std::ceil(ns / (2 * cus))) * (which == 0 ? 0.95 : 0.9) * 2 * (kSmallBN + 0.4 * r / ms);
     return small < big ? TILE_SMALL : TILE_BIG;
 }

@@ -97,3 +97,19 @@ def test_tile_forms_are_found_at_any_number_of_rows(U):
         U.tile_forms(sh, 0, False)
     sh.dtype = U.F32
     assert U.tile_forms(sh) == 0
+
+
+def test_tile_forms_of_few_rows(U):
+    """Where large tiles all run at once and small ones do not get a compute unit each, few rows per expert keep the large ones
+    (256 compute units, as on a host without a device)."""
+    from paper_2605_06665_amd import binding as B
+
+    def small(T, k, E, d, f, bit):
+        return bool(U.tile_forms(U.Shape(T=T, d_model=d, d_ff=f, E=E, k=k, L=1, dtype=U.BF16, sigma=1.0, c=2.5, eps=1e-6,
+                                         alpha_pool=0.01)) & bit)
+    assert not small(141, 2, 9, 640, 2176, B.SMALL_GATE_UP)        # 31 rows, 153 large tiles or 306 small ones
+    assert not small(95, 2, 31, 1280, 1536, B.SMALL_DX)            # 6 rows, 155 or 310
+    assert not small(1749, 1, 33, 1088, 960, B.SMALL_DH)           # 53 rows, 132 or 264
+    assert small(230, 8, 30, 1152, 192, B.SMALL_DX)                # 61 rows, 150 or 270
+    assert small(95, 2, 31, 1280, 1536, B.SMALL_GATE_UP)           # 372 large tiles: two rounds
+    assert small(567, 8, 23, 192, 1856, B.SMALL_DOWN)              # 46 small tiles: one each
