@@ -1122,7 +1122,11 @@ template <int NW, bool PAIR> hipError_t run_ptq_nw(const PtqLaunch& a, bool stre
 // 320 x 320 with 400 rows 60 / 42, 90 of 832 x 1472 483 / 513).
 // Both gradients go out in one launch, the second's tiles in the wake of the first's (16 of 576 x 320, 1500 rows: two
 // launches 93, one 52; 200 of 640 x 1024, 28 rows: 336 / 320), except where each is many rounds of long tiles: then tiles of
-// both kinds side by side share less in L2 (192 of 1536 x 4096, 2728 rows: 17.1 / 17.4 ms).
+// both kinds side by side share less in L2 (written, ms, two / one, rounds of 256 tiles: 96 of 1024 x 2816, 50 rounds, 5460 rows
+// 7.88 / 7.96, 8190 rows 11.60 / 11.75; 512 of 1024 x 704, 72 rounds, 4096 rows 8.90 / 8.96; 90 of 832 x 1472, 25 rounds, 4800
+// rows 3.52 / 3.57).  With fewer rows or rounds one launch is the shorter or they are alike (96 of 1024 x 2816, 2730 rows
+// 4.03 / 4.01, 682 rows 1.45 / 1.43, added 2.02 / 1.97; 64 of 768 x 2048, 18 rounds, 4096 rows 2.26 / 2.22, 1024 rows 0.69 / 0.67,
+// added 0.89 / 0.86; 192 of 1536 x 4096, 216 rounds, 2728 rows 18.14 / 18.19).
 struct PtqForm {
     bool small, two_launches, stream;
 };
@@ -1140,7 +1144,7 @@ PtqForm ptq_form(const PtqLaunch& a, double rows, bool stream) {
 #ifdef UNIPOOL_DEBUG_SWITCHES
     if (const char* e = getenv("UNIPOOL_PTQ")) take_small = e[0] == '1';
 #endif
-    return PtqForm{take_small, !take_small && rows > 448 && nb > 8 * cus, stream};
+    return PtqForm{take_small, !take_small && rows > 4000 && nb > 20 * cus, stream};
 }
 hipError_t run_ptq(const PtqLaunch& a, const PtqForm& form, hipStream_t st) {
     if (form.small) return run_ptq_nw<4, true>(a, form.stream, st);

@@ -113,3 +113,14 @@ def test_tile_forms_of_few_rows(U):
     assert small(230, 8, 30, 1152, 192, B.SMALL_DX)                # 61 rows, 150 or 270
     assert small(95, 2, 31, 1280, 1536, B.SMALL_GATE_UP)           # 372 large tiles: two rounds
     assert small(567, 8, 23, 192, 1856, B.SMALL_DOWN)              # 46 small tiles: one each
+
+
+def test_weight_gradients_in_two_launches_are_long(U):
+    from paper_2605_06665_amd import binding as B
+
+    def two(E, d, f, rows, n_layers=1):
+        return bool(U.tile_forms(U.Shape(T=E * rows // n_layers, d_model=d, d_ff=f, E=E, k=1, L=1, dtype=U.BF16, sigma=1.0, c=2.5,
+                                         eps=1e-6, alpha_pool=0.01), n_layers, False) & B.WGRAD_TWO_LAUNCHES)
+    assert two(96, 1024, 2816, 5460) and two(90, 832, 1472, 4800, 8)
+    assert not two(64, 768, 2048, 1024) and not two(96, 1024, 2816, 682)       # few rows
+    assert not two(64, 768, 2048, 8192)                                        # 18 rounds of tiles
