@@ -1433,14 +1433,23 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* 
             wpart, used, (size_t)ez * d, n, dw, dsigma_part, n_dsigma, d_sigma);
     // dx (+)= dz W   (W is [E][d]: reduction index strided)
     GemmArgs b = {};
-    // Small tiles: the reduction (E indices) is so short that a tile is mostly its start and its end, which two workgroups
-    // to a CU overlap (all of the entry point, us, 256 x 256 or 128 x 256 tiles / 128 x 128: 32768 tokens, 192 experts, d 1536
-    // 121 / 110; 8192, 64, 768: 33 / 32; 16384, 512, 1024: 84 / 86)
-    b.flat_rows = T; b.flat_bm = kSmallBM;
+    b.flat_rows = T;
     b.X = (const bf16*)dz; b.ldx = ez;                 // (values between E and ez are zeros)
     b.W = (const bf16*)w; b.w_stride = 0; b.ldw = d;
     b.K = E; b.N = d;
     b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d;
+    // Small tiles: the reduction (E indices) is so short that a tile is mostly its start and its end, which two workgroups
+    // to a CU overlap (all of the entry point, us, 256 x 256 / 128 x 128 tiles: 32768 tokens, 192 experts, d 1536 117 / 110;
+    // 65536, 192, 1536 223 / 211; 32768, 512, 1024 135 / 131; 131072, 384, 576 320 / 303; 4096, 512, 1024 46 / 38).  Many rounds
+    // of wide rows of a large pool are bound by reading dz once per column tile, half as often in large ones: 131072 tokens, 512
+    // experts, d 1024 444 / 458; 262144 844 / 870; 131072, 512, 1536 590 / 607; 65536, 448, 2048 368 / 375; but 131072, 256, 1024
+    // 312 / 305, 65536, 512, 1024 (4 rounds) 237 / 235, 524288, 512, 256 888 / 873.
+    const bool big = E >= 448 && E % kBK == 0 && d >= 1024 && (long long)cdiv(T, kBM) * cdiv(d, kBN) >= 8ll * num_cus();
+    if (big) {
+        b.flat_bm = kBM;
+        return dx_accumulate ? run_xw<TILE_BIG, false, EPI_STORE, false, true>(b, st) : run_xw<TILE_BIG, false, EPI_STORE>(b, st);
+    }
+    b.flat_bm = kSmallBM;
     if (dx_accumulate)
         return E % kBK != 0 ? run_xw<TILE_SMALL, false, EPI_STORE, true, true>(b, st)
                             : run_xw<TILE_SMALL, false, EPI_STORE, false, true>(b, st);

@@ -168,3 +168,27 @@ def test_blocks_of_tokens(E, T, k, d, router):
         assert rel_err(host(dw), (dz.T @ xd).numpy()) <= TOL["bf16"] and rel_err(host(dx[:T]), (dz @ wd).numpy()) <= TOL["bf16"]
     else:
         assert np.isfinite(host(dw)).all() and np.isfinite(host(dx[:T])).all()
+
+
+@pytest.mark.parametrize("T", [130816, 130817, 131072])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_dx_of_many_tokens_of_a_large_pool(T, accumulate):
+    """Both sides of the line from which dx goes in tiles of 256 x 256 (eight rounds of them on 256 compute units: 512 row tiles of
+    d_model 1024), the last one of a single row or full: sampled rows in double, and the bits of the first tokens alone, in tiles of 128 x 128."""
+    import torch
+    import paper_2605_06665_amd as U
+    E, d = 448, 1024
+    sh, x, wr, z, idx, dgate, ws, dz = _route_bwd_inputs(T, E, d, 2, 7)
+    f32 = dict(device="cuda")
+    dw, ds = torch.empty((E, d), **f32), torch.empty(1, **f32)
+    dx = torch.full((T + 1, d), 0.5 if accumulate else float("nan"), dtype=torch.bfloat16, device="cuda")
+    U.route_bwd(sh, x, wr, z, idx, dgate, None, dw, ds, dx, accumulate, ws)
+    assert bool((dx[T] == 0.5).all() if accumulate else torch.isnan(dx[T]).all())
+    few = 1000
+    sh2 = U.Shape(T=few, d_model=d, d_ff=64, E=E, k=2, L=1, dtype=U.BF16, sigma=0.9, c=2.0, eps=1e-6, alpha_pool=0.0, router=0)
+    dx2 = torch.full((few, d), 0.5, dtype=torch.bfloat16, device="cuda")
+    U.route_bwd(sh2, x[:few], wr, z[:few], idx[:few], dgate[:few], None, dw, ds, dx2, accumulate, ws)
+    assert torch.equal(dx[:few], dx2)
+    rows = torch.tensor([0, 127, 128, 255, 256, 65535, T - 257, T - 256, T - 255, T - 1], device="cuda")
+    want = dz[rows] @ wr.double() + (0.5 if accumulate else 0.0)
+    assert rel_err(host(dx[rows]), host(want)) <= TOL["bf16"]
