@@ -44,7 +44,8 @@ class PoolStep:
 
     wgrad     "pool": one weight-gradient pass over all layers at the end of the backward pass;
               "layer": accumulate into the float gradients as the backward pass goes: backward_layer layer by layer,
-              step() a few layers at a time (see _layers_per_wgrad).
+              step() a few layers at a time: wgrad_layers of them, or as many as _layers_per_wgrad says.  The dy / d_act
+              buffers of the layers beyond the first are made by the first step(); wgrad_layers=1 needs none.
     recompute keep one shared pair of A / B buffers instead of one per layer and rebuild a layer's
               A and B (unipool_expert_ffn_recompute) right before its backward pass (App. D (hyperparameter details):
               activation checkpointing with MoE recompute).  Results are bit-identical.
@@ -58,7 +59,8 @@ class PoolStep:
               device buffers used in turn and is part of state_dict()."""
 
     def __init__(self, T, d_model, d_ff, E, k, L, dtype, c, eps, alpha_pool, device="cuda:0",
-                 wgrad="pool", recompute=False, lagged=False, aux="pool", router="norm"):
+                 wgrad="pool", recompute=False, lagged=False, aux="pool", router="norm", wgrad_layers=None):
+        assert wgrad_layers is None or (wgrad == "layer" and wgrad_layers >= 1)
         assert wgrad in ("pool", "layer") and aux in ("pool", "layer") and router in ("norm", "softmax")
         self.router = B.ROUTER_SOFTMAX if router == "softmax" else B.ROUTER_NORM
         assert not (lagged and aux == "layer"), "the lagged statistic belongs to the pool loss"
@@ -108,31 +110,51 @@ class PoolStep:
             st.d_w_router = torch.empty((E, d), **f32)
             st.d_sigma = torch.empty(1, **f32)
             self.layers.append(st)
-        # backward buffers: per layer when the weight gradient is deferred, for the layers of one accumulation otherwise
-        per = L if wgrad == "pool" else self._layers_per_wgrad()
-        self._dy = [torch.empty((S, d), **act) for _ in range(per)]
-        self._dact = [torch.empty((S, 2 * f), **act) for _ in range(per)]
+        # backward buffers: per layer when the weight gradient is deferred, otherwise for one layer until the first step()
+        self._dy, self._dact = [], []
         self._dxp = torch.empty((S, d), **act)
         self.d_w_gate_up = torch.zeros((E, 2 * f, d), **f32)
         self.d_w_down = torch.zeros((E, d, f), **f32)
+        self._tables = []            # pointer tables, all kept: a recorded step may hold any of them
+        self._take_layers(L if wgrad == "pool" else 1)
+        self._wgrad_layers = L if wgrad == "pool" else min(L, wgrad_layers or self._layers_per_wgrad())
 
-        # pointer tables of the layers that share an accumulation, in the order of the backward pass; layer l uses the
-        # buffers l mod per
-        groups = [range(max(0, hi - per), hi) for hi in range(L, 0, -per)]
+    def _take_layers(self, per):
+        """Backward buffers and pointer tables for `per` layers in one weight gradient."""
+        act = dict(dtype=self.act, device=self.dev)
+        more = [(torch.empty((self.S, self.d), **act), torch.empty((self.S, 2 * self.f), **act))
+                for _ in range(per - len(self._dy))]
+        dy, dact = self._dy + [m[0] for m in more], self._dact + [m[1] for m in more]
+        # the layers that share an accumulation, in the order of the backward pass; layer l uses the buffers l mod per
+        groups = [range(max(0, hi - per), hi) for hi in range(self.L, 0, -per)]
         ptrs = []
         for ls in groups:
-            for ts in ([self.layers[l].x_perm for l in ls], [self._dact[l % per] for l in ls],
-                       [self.layers[l].act_h for l in ls], [self._dy[l % per] for l in ls],
+            for ts in ([self.layers[l].x_perm for l in ls], [dact[l % per] for l in ls],
+                       [self.layers[l].act_h for l in ls], [dy[l % per] for l in ls],
                        [self.layers[l].offsets for l in ls]):
                 ptrs += [t.data_ptr() for t in ts]
-        table = iter(torch.tensor(ptrs, dtype=torch.int64, device=self.dev).split([len(ls) for ls in groups for _ in range(5)]))
-        self._wgrad_groups = [(ls, [next(table) for _ in range(5)]) for ls in groups]
+        table = torch.tensor(ptrs, dtype=torch.int64, device=self.dev)
+        parts = iter(table.split([len(ls) for ls in groups for _ in range(5)]))
+        self._dy, self._dact = dy, dact
+        self._tables.append(table)
+        self._wgrad_groups = [(ls, [next(parts) for _ in range(5)]) for ls in groups]
+
+    def _take_more_layers(self):
+        """Before a step: buffers for _wgrad_layers layers at a time.  Where there is no memory for them, and in a recording,
+        which is no place to make buffers, the layers go on one by one."""
+        if len(self._dy) >= self._wgrad_layers or torch.cuda.is_current_stream_capturing():
+            return
+        try:
+            self._take_layers(self._wgrad_layers)
+        except torch.OutOfMemoryError:
+            self._wgrad_layers = len(self._dy)
 
     def _layers_per_wgrad(self):
-        """Layers that step() takes together into the float gradients with wgrad="layer".  Reading and writing the
-        gradients in every layer is most of a backward pass over few tokens; what it costs to take n layers at once are
-        n - 1 more pairs of dy / d_act buffers, which get up to a quarter of the gradients' own bytes (4 layers of 90
-        experts of 832 x 1472, 5999 tokens, k = 3, two layers at a time and no zeroing: 5.95 -> 4.20 ms a step)."""
+        """Layers that step() takes together into the float gradients with wgrad="layer", unless the caller says how many.
+        Reading and writing the gradients in every layer is most of a backward pass over few tokens; what it costs to take n
+        layers at once are n - 1 more pairs of dy / d_act buffers, which get up to a quarter of the gradients' own bytes (4
+        layers of 90 experts of 832 x 1472, 5999 tokens, k = 3, ms a step: added layer by layer to cleared gradients 5.03,
+        wgrad_layers=1 4.73, two layers at a time, as here, 3.90, all four 3.45)."""
         pair = self.S * (self.d + 2 * self.f) * (2 if self.dtype == B.BF16 else 4)
         most = min(self.L, 8, 1 + (3 * self.E * self.d * self.f) // pair)
         return -(-self.L // -(-self.L // most))          # as even as the number of accumulations allows
@@ -241,6 +263,7 @@ class PoolStep:
         for l in range(self.L):
             self.forward_layer(l, xs[l], w_routers[l], sigmas[l], w_gate_up, w_down)
         self.aux_loss(fbar_in)
+        self._take_more_layers()
         # the first accumulation writes every gradient, so nothing is cleared before it
         for g, (layers, _) in enumerate(self._wgrad_groups):
             for l in reversed(layers):

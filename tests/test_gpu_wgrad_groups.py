@@ -27,8 +27,8 @@ def test_groups(dtype, T, L, recompute, per):
     sig = [1.0] * L
     ps = PoolStep(T, d, f, E, k, L, U.BF16 if dtype == "bf16" else U.F32, 2.6, 1e-6, 0.01, device="cuda:0", wgrad="layer",
                   recompute=recompute)
-    assert len(ps._dy) == per
     ps.step(xs, wrs, sig, wgu, wd, gs)                       # leaves the forward pass's state of every layer
+    assert len(ps._dy) == per
     ps.begin_backward()
     for l in reversed(range(L)):
         ps.backward_layer(l, xs[l], wrs[l], sig[l], wgu, wd, gs[l])
@@ -43,3 +43,69 @@ def test_groups(dtype, T, L, recompute, per):
         # the same products in another order of float sums: about sqrt(n) 2^-24 of terms of the size of the result; n up to
         # T L, a few hundred per expert
         assert (a - b).norm() <= 2e-6 * b.norm() and torch.isfinite(a).all()
+
+
+def _small_step(dev="cuda:0", **kw):
+    import torch
+    import paper_2605_06665_amd as U
+    from paper_2605_06665_amd.pipeline import PoolStep
+    T, L, E, d, f, k = 30, 4, 16, 64, 64, 2
+    g = torch.Generator().manual_seed(T)
+
+    def rnd(*shape, std=1.0):
+        return (torch.randn(shape, generator=g) * std).to(torch.bfloat16).to(dev)
+
+    args = ([rnd(T, d) for _ in range(L)], [rnd(E, d) for _ in range(L)], [1.0] * L, rnd(E, 2 * f, d, std=0.1),
+            rnd(E, d, f, std=0.1), [rnd(T, d) for _ in range(L)])
+    return PoolStep(T, d, f, E, k, L, U.BF16, 2.6, 1e-6, 0.01, device=dev, wgrad="layer", **kw), args
+
+
+def _gradients(ps, args):
+    ps.step(*args)
+    return [t.clone() for t in (ps.d_w_gate_up, ps.d_w_down)]
+
+
+def _agree(a, b):
+    return all((p - q).norm() <= 2e-6 * q.norm() for p, q in zip(a, b))           # as above
+
+
+def test_the_caller_says_how_many_layers(monkeypatch):
+    """Buffers of further layers are made by the first step() and not by a caller's own loop over the layers; wgrad_layers
+    sets their number; without memory for them, and in a recording that is the first step, layers go one by one."""
+    import torch
+    ps, args = _small_step()
+    for l in range(4):
+        ps.forward_layer(l, args[0][l], args[1][l], 1.0, args[3], args[4])
+    ps.aux_loss()
+    ps.begin_backward()
+    for l in reversed(range(4)):
+        ps.backward_layer(l, args[0][l], args[1][l], 1.0, args[3], args[4], args[5][l])
+    ps.end_backward()
+    want = [t.clone() for t in (ps.d_w_gate_up, ps.d_w_down)]
+    assert len(ps._dy) == len(ps._dact) == 1
+    assert _agree(_gradients(ps, args), want) and len(ps._dy) == 4
+    for n in (1, 3, 9):
+        ps, args = _small_step(wgrad_layers=n)
+        assert _agree(_gradients(ps, args), want) and len(ps._dy) == min(n, 4)
+    ps, args = _small_step()
+
+    def no_memory(per):
+        raise torch.OutOfMemoryError("none left")
+
+    monkeypatch.setattr(ps, "_take_layers", no_memory)
+    assert _agree(_gradients(ps, args), want) and len(ps._dy) == 1
+    # the kernels have run, this object has not
+    ps, args = _small_step()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        ps.step(*args)
+    assert len(ps._dy) == 1
+    assert _agree(_gradients(ps, args), want) and len(ps._dy) == 4       # an eager step makes them, the recording keeps its own
+    for _ in range(3):
+        ps.d_w_gate_up.fill_(float("nan"))
+        ps.d_w_down.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _agree((ps.d_w_gate_up, ps.d_w_down), want)
+        assert _agree(_gradients(ps, args), want)
