@@ -27,6 +27,7 @@ def test_both_sides_of_the_line(aligned):
     got = []
     for E in (few, few + 2):
         sh = U.Shape(T=T, d_model=D, d_ff=F, E=E, k=K, L=1, dtype=U.BF16, sigma=1.0, c=1.0, eps=1e-6, alpha_pool=0.0, router=0)
+        assert bool(U.tile_forms(sh) & U.binding.WGRAD_STREAMED) == (E > few)
         offsets = torch.cat([off, off[-1:].repeat(E - few)]).cuda()
         wgu, wd = (torch.zeros(n, dtype=torch.bfloat16, device="cuda") for n in ((E, 2 * F, D), (E, D, F)))
         pad = 0 if aligned else 1                    # the other form of the stores

@@ -1,6 +1,7 @@
 """GPU: the tile table of the grouped GEMMs over pool sizes and row counts at its edges: short last laps of the
 dealing (E mod 8 in both directions), empty experts, all experts of one size class, counts on both sides of the
-2048-row change of class width, one expert with nearly all rows."""
+2048-row change of class width, one expert with nearly all rows.  At these widths all products run in tiles of 128 x 128
+(test_gpu_tile_forms.py has the tables of 256-row tiles)."""
 import numpy as np
 import pytest
 
@@ -35,6 +36,7 @@ def test_every_row_meets_its_expert(name):
     wd = (torch.randn((E, d, f), generator=g) * 0.1).to(torch.bfloat16)
     sh = U.Shape(T=S, d_model=d, d_ff=f, E=E, k=1, L=1, dtype=U.BF16, sigma=1.0, c=1.0, eps=1e-6, alpha_pool=0.0,
                  router=0)
+    assert U.tile_forms(sh) & 15 == 15
     ws = torch.empty(U.workspace_bytes(sh), dtype=torch.uint8, device="cuda:0")
     a, b, h = (torch.full((S, f), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(3))
     y = torch.full((S, d), float("nan"), dtype=torch.bfloat16, device="cuda:0")
