@@ -73,7 +73,7 @@ WsLayout ws_layout(const unipool_shape& s) {
     w.tile_meta = o;   o += align_up((4096 + 4 * (std::max(S / 128, S / 256 + T / 128) + 2 * E + 16)) * sizeof(int32_t));
     w.chunk_hist = o;  o += align_up(((T + 63) / 64) * E * sizeof(int32_t));
     w.psum_part = o;   o += align_up(rblocks * E * sizeof(float));
-    w.dsigma_part = o; o += align_up(rblocks * E * sizeof(int32_t));   // also holds count partials
+    w.cnt_part = o;    o += align_up(rblocks * E * sizeof(int32_t));
     w.dz = o;          o += align_up(std::max(T * E * 4, T * ez * act));   // logits (float) or dz
     w.ptr_tab = o;     o += 256;
     w.wpart = o;       o += align_up((size_t)kRouteBwdSplit * ez * d * sizeof(float));
@@ -184,7 +184,7 @@ int unipool_route(const unipool_shape* shape, const void* x, const void* w_route
     if (!few && router_fused_supported(*shape) && !unfused_router()) {
         // logits, scores, top-k and block statistics in one kernel; then the sum over the blocks
         const bool one_block = shape->T <= kRouterTokensPerBlock;     // then its statistics are the layer's
-        int32_t* cnt_part = one_block ? counts : (int32_t*)(base + w.dsigma_part);
+        int32_t* cnt_part = one_block ? counts : (int32_t*)(base + w.cnt_part);
         float* psum_part = one_block ? psum : (float*)(base + w.psum_part);
         e = router_fused(*shape, x, w_router, z, topk_idx, topk_gate, cnt_part, psum_part, st);
         if (e != hipSuccess) return check_hip(e, "unipool_route: fused router");
@@ -195,12 +195,12 @@ int unipool_route(const unipool_shape* shape, const void* x, const void* w_route
     if (few)
         e = router_few_logits(*shape, x, w_router, z, st);
     else if (mfma_router_supported(*shape))
-        e = mfma_logits(*shape, x, w_router, z, (int32_t*)(base + w.tile_meta), st);
+        e = mfma_logits(*shape, x, w_router, z, st);
     else
         e = f32_logits(*shape, x, w_router, z, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route: logits");
     e = launch_route_score_topk(*shape, z, topk_idx, topk_gate, counts, psum,
-                                (int32_t*)(base + w.dsigma_part), (float*)(base + w.psum_part),
+                                (int32_t*)(base + w.cnt_part), (float*)(base + w.psum_part),
                                 (float*)(base + w.wpart), st);
     return check_hip(e, "unipool_route: score/top-k");
 }
@@ -217,13 +217,13 @@ int unipool_route_bwd(const unipool_shape* shape, const void* x, const void* w_r
     char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
     void* dz = base + w.dz;
-    float* dsigma_part = (float*)(base + w.psum_part);     // and on into the area behind it
+    float* dsigma_part = (float*)(base + w.psum_part);
     const bool mfma = mfma_route_bwd_supported(*shape, x, w_router, dx);
     hipError_t e = launch_route_bwd_dz(*shape, logits, topk_idx, dgate, aux_coef, dz, dsigma_part, st);
     if (e != hipSuccess) return check_hip(e, "unipool_route_bwd: dz");
     if (mfma)
         e = mfma_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
-                              (int32_t*)(base + w.tile_meta), (float*)(base + w.wpart), st);
+                              (float*)(base + w.wpart), st);
     else
         e = f32_route_bwd_mm(*shape, x, w_router, dz, d_w_router, dx, dx_accumulate, dsigma_part, d_sigma,
                              (float*)(base + w.wpart), st);
@@ -360,8 +360,6 @@ int unipool_expert_wgrad(const unipool_shape* shape, int n_layers, const void* c
     REQUIRE_PTR(x_perm_l); REQUIRE_PTR(d_act_l); REQUIRE_PTR(act_h_l); REQUIRE_PTR(dy_perm_l);
     REQUIRE_PTR(expert_offsets_l); REQUIRE_PTR(d_w_gate_up); REQUIRE_PTR(d_w_down);
     NEED_WS();
-    const WsLayout w = ws_layout(*shape);
-    char* base = (char*)ws;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     if (mfma_ffn_supported(*shape))

@@ -100,8 +100,8 @@ __device__ __forceinline__ void block_sum_256(const float* part, int n, float* o
 struct WsLayout {
     size_t tile_meta;      // int32: [0] number of row tiles, 4 ints per tile from [64] on, then the meeting counters
     size_t chunk_hist;     // int32 [ceil(T/64)][E]   permute: per-64-token histograms/bases
-    size_t psum_part;      // float [router blocks][E] partial score sums
-    size_t dsigma_part;    // float [router blocks]
+    size_t psum_part;      // float [ceil(T/64)][E] partial score sums; in the backward pass the partial sums of d_sigma
+    size_t cnt_part;       // int32 [ceil(T/64)][E] partial counts
     size_t dz;             // act   [T][dz_stride]  router backward logits gradient; float [T][E] logits
     size_t ptr_tab;        // 5 device pointers for the single-layer weight gradient
     size_t wpart;          // float [split][dz_stride][d]  router weight gradient partials

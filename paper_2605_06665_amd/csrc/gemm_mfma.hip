@@ -58,10 +58,6 @@ __device__ unsigned long long g_phase_times[1024][8];
 #define PHASE_COMMIT(t0, t1, t2, t3)
 #endif
 
-
-
-
-
 // Inclusive prefix sum over the 512 threads of a workgroup; wsum: eight words of LDS that nobody else uses.
 __device__ __forceinline__ int scan512(int v, int* wsum) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -639,11 +635,13 @@ struct PtqLaunch {
     int n_layers, E, accumulate;
 };
 
-template <int BK, int NS, int NW, bool STREAM, bool PAIR>
+// BOTH: the tiles of launch.second follow those of launch.first (if it has any), and the operands of a single layer or matrix may
+// come by pointer; without it launch.first alone, by table.  STREAM: see the epilogue.
+template <int BK, int NS, int NW, bool STREAM, bool BOTH>
 __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launch) {
     // 256 x 256 float tile, 2 x 4 wavefronts of 128 x 64, v_mfma_f32_16x16x32_bf16 (at the card's power
     // limit it sustains about a sixth more than the 32x32x16 form): 8 x 4 accumulator blocks of 16 x 16.
-    // NW = 4: 128 x 128, 2 x 2 wavefronts of 64 x 64, several workgroups to a CU (see ptq_small).
+    // NW = 4: 128 x 128, 2 x 2 wavefronts of 64 x 64, several workgroups to a CU (see ptq_form).
     constexpr int BM = NW == 8 ? 256 : 128, BN = BM;
     constexpr int NT = 64 * NW;               // threads
     constexpr int WNC = NW / 2;               // wavefronts along n (two along m)
@@ -659,14 +657,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int total1 = launch.E * launch.first.m_tiles * launch.first.n_tiles;
-    const int total = total1 + (PAIR ? launch.E * launch.second.m_tiles * launch.second.n_tiles : 0);
+    const int total = total1 + (BOTH ? launch.E * launch.second.m_tiles * launch.second.n_tiles : 0);
     const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
     const int slot = blockIdx.x / kNumXcd;
     if (slot >= per_xcd) return;
     int lt = (blockIdx.x % kNumXcd) * per_xcd + slot;
     if (lt >= total) return;
-    const PtqArgs g = PAIR && lt >= total1 ? launch.second : launch.first;
-    if (PAIR && lt >= total1) lt -= total1;
+    const PtqArgs g = BOTH && lt >= total1 ? launch.second : launch.first;
+    if (BOTH && lt >= total1) lt -= total1;
     const int n_layers = launch.n_layers, accumulate = launch.accumulate;
     const void* const zeros = zero_page();
     const int per_e = g.m_tiles * g.n_tiles;
@@ -692,7 +690,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
     __shared__ int lds_r0[kMaxPtqLayers], lds_r1[kMaxPtqLayers];
     __shared__ const bf16* lds_p[kMaxPtqLayers];
     __shared__ const bf16* lds_q[kMaxPtqLayers];
-    if (PAIR && g.P == nullptr) {
+    if (BOTH && g.P == nullptr) {
         lds_r0[0] = launch.off1 ? launch.off1[e] : min(g.total_rows, e * g.chunk_rows);
         lds_r1[0] = launch.off1 ? launch.off1[e + 1] : min(g.total_rows, (e + 1) * g.chunk_rows);
         lds_p[0] = reinterpret_cast<const bf16*>(g.P1);
@@ -741,7 +739,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
     const unsigned voff_q = ((unsigned)krow0 * (unsigned)g.ndim + (unsigned)qcol) * 2u;
 
     // load cursor over the rows of expert e, layer after layer
-    int ld_layer = -1, ld_r = 0, ld_end = 0;
+    int ld_r = 0, ld_end = 0;
     const bf16* ld_p = nullptr;
     const bf16* ld_q = nullptr;
     auto uniform_ptr = [](const bf16* p) {
@@ -772,7 +770,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_ptq_kernel(const PtqLaunch launc
     fetch_next();
     auto next_layer = [&]() {     // the cursor moves to the next layer with rows (wave-uniform); false past the last
         if (nx_layer >= n_layers) return false;
-        ld_layer = nx_layer;
         ld_r = nx_r;
         ld_end = nx_end;
         ld_p = nx_p;
@@ -1054,7 +1051,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // launch helpers
 // ---------------------------------------------------------------------------------------------
 constexpr int kBM = 256, kBN = 256, kBK = 64, kNS = 2;   // gemm_xw: 128-byte row segments per load
-constexpr int kPtqBK = 32, kPtqNS = 4, kPtqWaves = 8;       // gemm_ptq
+constexpr int kPtqBK = 32, kPtqNS = 4;       // gemm_ptq
 constexpr int kGemmLds = kNS * kBM * kBK * 2 + (kNS + 1) * kBN * kBK * 2;   // 2 X stages + 3 W stages = 160 KiB
 constexpr int kPtqLds = kPtqNS * 2 * kPtqBK * 256 * 2;            // 128 KiB
 
@@ -1088,10 +1085,10 @@ hipError_t run_xw(GemmArgs a, hipStream_t st) {
 
 constexpr int kPtqSmallNS = 3, kPtqSmallLds = kPtqSmallNS * 2 * kPtqBK * 128 * 2;   // 48 KiB
 
-template <int NW, bool STREAM, bool PAIR>
+template <int NW, bool STREAM, bool BOTH>
 hipError_t run_ptq_form(PtqLaunch a, hipStream_t st) {
     constexpr int BM = NW == 8 ? 256 : 128, NS = NW == 8 ? kPtqNS : kPtqSmallNS, LDS = NW == 8 ? kPtqLds : kPtqSmallLds;
-    auto kern = gemm_ptq_kernel<kPtqBK, NS, NW, STREAM, PAIR>;
+    auto kern = gemm_ptq_kernel<kPtqBK, NS, NW, STREAM, BOTH>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1109,8 +1106,8 @@ hipError_t run_ptq_form(PtqLaunch a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int NW, bool PAIR> hipError_t run_ptq_nw(const PtqLaunch& a, bool stream, hipStream_t st) {
-    return stream ? run_ptq_form<NW, true, PAIR>(a, st) : run_ptq_form<NW, false, PAIR>(a, st);
+template <int NW, bool BOTH> hipError_t run_ptq_nw(const PtqLaunch& a, bool stream, hipStream_t st) {
+    return stream ? run_ptq_form<NW, true, BOTH>(a, st) : run_ptq_form<NW, false, BOTH>(a, st);
 }
 
 // Weight gradients of the experts, `rows` rows each in all layers on average.  A 256 x 256 tile takes its CU 0.0235 us per
@@ -1262,13 +1259,12 @@ bool mfma_router_supported(const unipool_shape& s) {
     return s.dtype == UNIPOOL_BF16 && s.d_model % 64 == 0 && s.E % 8 == 0;
 }
 
-hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, float* z,
-                       int32_t* tile_meta, hipStream_t st) {
+hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st) {
     GemmArgs a = {};
     a.X = (const bf16*)x; a.ldx = s.d_model;
     a.W = (const bf16*)w; a.w_stride = 0; a.ldw = s.d_model;
     a.K = s.d_model; a.N = s.E;
-    a.tile_meta = tile_meta; a.out0 = z; a.ldo = s.E;
+    a.out0 = z; a.ldo = s.E;
     a.flat_rows = s.T; a.flat_bm = kSmallBM;
     // 128 columns where they hold the pool or where all tiles run at once, 256 otherwise, which read x half as often (all of
     // the entry point, us, 256 / 128: 64 experts, 8192 tokens, d 832 26 / 23; 512, 1000, 320 43 / 34; 200, 20000, 832 42 / 45)
@@ -1276,12 +1272,12 @@ hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, flo
                ? run_xw<TILE_SMALL, true, EPI_F32>(a, st) : run_xw<TILE_BIG, true, EPI_F32>(a, st);
 }
 
-hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
-                           const void* wgu, void* a_out, void* b_out, void* h_out, int32_t* tile_meta,
-                           int32_t* extra, hipStream_t st, const int32_t* slot_of_row) {
+// Gate and up projections in tiles of form `tile`; the table of `down` is built along with theirs.
+static hipError_t ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets, const void* wgu, void* a_out,
+                              void* b_out, void* h_out, int32_t* tile_meta, int32_t* extra, int tile, int down, hipStream_t st,
+                              const int32_t* slot_of_row) {
     const int d = s.d_model, f = s.d_ff;
-    const int tile = tile_form(s, 2 * f, 0, extra != nullptr);
-    hipError_t e = build_tiles(s, offsets, tile, tile_form(s, d, 1, extra != nullptr), tile_meta, extra, st);
+    hipError_t e = build_tiles(s, offsets, tile, down, tile_meta, extra, st);
     if (e != hipSuccess) return e;
     GemmArgs a = {};
     a.X = (const bf16*)x_perm; a.ldx = d;
@@ -1293,20 +1289,27 @@ hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const in
     return run_grouped<true, EPI_SWIGLU_FWD>(a, tile, st);
 }
 
+hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
+                            const void* wgu, void* a_out, void* b_out, void* h_out, int32_t* tile_meta,
+                            int32_t* extra, hipStream_t st) {
+    const int tile = tile_form(s, 2 * s.d_ff, 0, extra != nullptr);
+    return ffn_gate_up(s, x_perm, offsets, wgu, a_out, b_out, h_out, tile_meta, extra, tile, tile, st, nullptr);
+}
+
 hipError_t mfma_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
                         const void* wgu, const void* wd, void* a_out, void* b_out, void* h_out,
                         void* y, int32_t* tile_meta, int32_t* extra, hipStream_t st, const int32_t* slot_of_row) {
     const int S = s.T * s.k, d = s.d_model, f = s.d_ff;
-    hipError_t e = mfma_ffn_gate_up(s, x_perm, offsets, wgu, a_out, b_out, h_out, tile_meta, extra, st, slot_of_row);
+    const int tile0 = tile_form(s, 2 * f, 0, extra != nullptr), tile1 = tile_form(s, d, 1, extra != nullptr);
+    hipError_t e = ffn_gate_up(s, x_perm, offsets, wgu, a_out, b_out, h_out, tile_meta, extra, tile0, tile1, st, slot_of_row);
     if (e != hipSuccess) return e;
     GemmArgs b = {};
     b.X = (const bf16*)h_out; b.ldx = f;
     b.W = (const bf16*)wd; b.w_stride = debug_w_stride((long long)d * f); b.ldw = f;
     b.K = f; b.N = d;
-    const int tile = tile_form(s, d, 1, extra != nullptr);
-    b.tile_meta = tile == tile_form(s, 2 * f, 0, extra != nullptr) ? tile_meta : extra; b.launch_slot = 1; b.out0 = y; b.ldo = d;
+    b.tile_meta = tile0 == tile1 ? tile_meta : extra; b.launch_slot = 1; b.out0 = y; b.ldo = d;
     if (b.K >= kPairMinK) { b.pair_cnt = pair_counters(tile_meta, s.E, S); b.pair_cap = kPairCap; }
-    return run_grouped<true, EPI_STORE>(b, tile, st);
+    return run_grouped<true, EPI_STORE>(b, tile1, st);
 }
 
 hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a_in, const void* b_in,
@@ -1400,7 +1403,7 @@ bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void*
 
 hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
                              float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,
-                             int32_t* tile_meta, float* wpart, hipStream_t st) {
+                             float* wpart, hipStream_t st) {
     const int d = s.d_model, E = s.E, T = s.T, ez = dz_stride(s);
     // d_w_router = dz^T x: the token axis is cut into chunks whose partial products are summed in a fixed order;
     // as many chunks as give every CU one output tile in a single round, of 256 tokens at least, or 128 where the partial
@@ -1437,7 +1440,7 @@ hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* 
     b.X = (const bf16*)dz; b.ldx = ez;                 // (values between E and ez are zeros)
     b.W = (const bf16*)w; b.w_stride = 0; b.ldw = d;
     b.K = E; b.N = d;
-    b.tile_meta = tile_meta; b.out0 = dx; b.ldo = d;
+    b.out0 = dx; b.ldo = d;
     // Small tiles: the reduction (E indices) is so short that a tile is mostly its start and its end, which two workgroups
     // to a CU overlap (all of the entry point, us, 256 x 256 / 128 x 128 tiles: 32768 tokens, 192 experts, d 1536 117 / 110;
     // 65536, 192, 1536 223 / 211; 32768, 512, 1024 135 / 131; 131072, 384, 576 320 / 303; 4096, 512, 1024 46 / 38).  Many rounds

@@ -10,11 +10,12 @@ namespace unipool {
 hipError_t launch_route_score_topk(const unipool_shape& s, const float* logits, int32_t* topk_idx,
                                    float* topk_gate, int32_t* counts, float* psum,
                                    int32_t* cnt_part, float* psum_part, float* wpart, hipStream_t st);
-// Per-token backward of the score: writes dz (act dtype) and d_sigma.
+// Sums of the block partials.
 hipError_t launch_route_finalize(const unipool_shape& s, const int32_t* cnt_part, const float* psum_part,
                                  int32_t* counts, float* psum, hipStream_t st);
-// dsigma_part: one float per block of dz_tokens_per_block tokens, added up by the kernels of the contractions.
-// (The partial sums have the two areas of the router's block statistics, 2 E floats per 64 tokens.)
+// Per-token backward of the score: writes dz (act dtype) and partial sums of d_sigma, which the kernels of the contractions add
+// up.  dsigma_part: one float per block of dz_tokens_per_block tokens, so 1, 4 or 8 floats per 64 tokens, never more than the E
+// that the area of the partial score sums, where they lie, has for 64 tokens.
 inline int dz_tokens_per_block(const unipool_shape& s) { return s.E < 4 ? kRouterTokensPerBlock : s.E <= 256 ? 16 : 8; }
 hipError_t launch_route_bwd_dz(const unipool_shape& s, const float* logits, const int32_t* topk_idx,
                                const float* dgate, const float* aux_coef, void* dz,
@@ -77,14 +78,13 @@ int num_cus();
 // ---- gemm_mfma.hip: bf16 MFMA grouped GEMMs -----------------------------------------
 bool mfma_ffn_supported(const unipool_shape& s);
 bool mfma_router_supported(const unipool_shape& s);
-hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, float* z,
-                       int32_t* tile_meta, hipStream_t st);
+hipError_t mfma_logits(const unipool_shape& s, const void* x, const void* w, float* z, hipStream_t st);
 hipError_t mfma_ffn_fwd(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
                         const void* wgu, const void* wd, void* a, void* b, void* h, void* y,
                         int32_t* tile_meta, int32_t* extra_meta, hipStream_t st, const int32_t* slot_of_row = nullptr);
 hipError_t mfma_ffn_gate_up(const unipool_shape& s, const void* x_perm, const int32_t* offsets,
-                           const void* wgu, void* a, void* b, void* h, int32_t* tile_meta,
-                           int32_t* extra_meta, hipStream_t st, const int32_t* slot_of_row = nullptr);
+                            const void* wgu, void* a, void* b, void* h, int32_t* tile_meta,
+                            int32_t* extra_meta, hipStream_t st);
 hipError_t mfma_ffn_dgrad(const unipool_shape& s, const void* dy, const void* a, const void* b,
                           const int32_t* offsets, const void* wgu, const void* wd, void* dx,
                           void* d_act, int32_t* tile_meta, int32_t* extra_meta, hipStream_t st);
@@ -98,7 +98,7 @@ int mfma_tile_forms(const unipool_shape& s, bool extra, int n_layers, int accumu
 bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx);
 hipError_t mfma_route_bwd_mm(const unipool_shape& s, const void* x, const void* w, const void* dz,
                              float* dw, void* dx, int dx_accumulate, const float* dsigma_part, float* d_sigma,
-                             int32_t* tile_meta, float* wpart, hipStream_t st);
+                             float* wpart, hipStream_t st);
 
 // ---- ffn_few.hip: bf16 expert FFN forward where an expert has few rows -----------------------
 bool few_rows_supported(const unipool_shape& s);

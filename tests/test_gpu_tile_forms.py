@@ -93,3 +93,26 @@ def test_products(name):
                           (y[r], h[r].astype(np.float64) @ de.T), (dact[r], rdact),
                           (dx[r], dact[r].astype(np.float64) @ we)):
             assert rel_err(got, want) <= TOL["bf16"], (name, e)
+
+
+def test_recomputation_builds_its_own_table_only():
+    """expert_ffn_recompute runs the product of w_gate_up alone: where that of w_down would take the other tile size, its table
+    (in the area of the router gradient's partial products, the last of the workspace) is not built."""
+    import torch
+    import paper_2605_06665_amd as U
+    d, f, counts, sizes = CASES["one-hot-expert"]
+    assert sizes[0] != sizes[1]
+    sh, S, E = _shape(U, d, f, counts), sum(counts), len(counts)
+    g = torch.Generator().manual_seed(1)
+    x, wgu = (torch.randn(s, generator=g).to(torch.bfloat16).cuda() for s in ((S, d), (E, 2 * f, d)))
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
+    ws = torch.full((U.workspace_bytes(sh),), 0xff, dtype=torch.uint8, device="cuda:0")
+    a, b, h = (torch.empty((S, f), dtype=torch.bfloat16, device="cuda:0") for _ in range(3))
+    U.expert_ffn_recompute(sh, x, off, wgu, a, b, h, ws)
+    partials = 64 * ((E + 7) // 8 * 8) * d * 4
+    assert bool((ws[-partials:] == 0xff).all())
+    y = torch.empty((S, d), dtype=torch.bfloat16, device="cuda:0")
+    a2, b2, h2 = (torch.empty_like(t) for t in (a, b, h))
+    U.expert_ffn_fwd(sh, x, off, wgu, torch.zeros((E, d, f), dtype=torch.bfloat16, device="cuda:0"), a2, b2, h2, y, ws)
+    assert not bool((ws[-partials:] == 0xff).all())                          # the forward pass has built it there
+    assert torch.equal(a, a2) and torch.equal(b, b2) and torch.equal(h, h2)
