@@ -25,7 +25,7 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 # HBM bytes per gemm_xw launch from rocprofv3 counter runs of this command (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0,
 # the factors of the 1 GiB copy below), averaged over the four expert-FFN launches of a layer.  A run of
 # bench.py cannot collect counters itself: the value is the one recorded in the profile named below.
-PROFILED_XW_TRAFFIC_BYTES = {"C5": 5.5e9}
+PROFILED_XW_TRAFFIC_BYTES = {"C5": 5.56e9}
 PROFILED_XW_TRAFFIC_SOURCE = ("profiles/gemm_counters_C5.txt: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of "
                               "`bench.py --workload C5`, recorded there; not measured in this run")
 

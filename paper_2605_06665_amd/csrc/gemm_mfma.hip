@@ -1394,8 +1394,9 @@ hipError_t mfma_ffn_wgrad_layer(const unipool_shape& s, const void* x_perm, cons
 bool mfma_route_bwd_supported(const unipool_shape& s, const void* x, const void* w, const void* dx) {
     // Pools that are a multiple of 8 have their operands aligned to 16 bytes.  Others may come at any address: the float
     // kernel reads those value by value; it also takes up to 256 tokens, where its launches are the shorter ones (all of
-    // the entry point, us, this path / the float one: 3 experts, d 256, 16 tokens 20 / 16; 90 experts, d 832, 256 tokens
-    // 31 / 23, 1024 tokens 32 / 32; 500 experts, d 1536, 256 tokens 54 / 51, 512 tokens 56 / 63).
+    // the entry point, us, this path / the float one: 3 experts, d 256, 16 tokens 16.5 / 13.1; 90 experts, d 832, 256 tokens
+    // 19.2 / 14.5, 512 tokens 19.3 / 16.4, 1024 tokens 19.7 / 22.5; 500 experts, d 1536, 256 tokens 25.7 / 26.9, 512 tokens
+    // 27.2 / 38.1).
     if (s.dtype != UNIPOOL_BF16) return false;
     if (s.E % 8 == 0) return true;
     return s.T > 256 && (((uintptr_t)x | (uintptr_t)w | (uintptr_t)dx) & 15) == 0;
