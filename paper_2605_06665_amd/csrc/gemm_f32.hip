@@ -10,10 +10,10 @@
 // tiles pass through registers (the next two stages are requested, without a branch, while one is multiplied) into two LDS
 // buffers as 16-byte pieces, one barrier per stage, whichever index is the contiguous one in memory; neighbouring tiles run
 // on one XCD and meet in its L2.
-// 3003 rows, d = 252, f = 500, 12 experts, us, launches back to back in a graph: both forward products 49 -> 47, both
-// backward products 56 -> 55, weight gradients of two layers 109 -> 73 (with one stage requested ahead, a branch around
-// every load, strided operands transposed on their way into LDS, tiles dealt to the XCDs in turn -> now); 32 experts of
-// 320 x 640, 4500 rows: 96 -> 92, 109 -> 95, 216 -> 154.  The matrix cores are busy half of the time there (74.5 of 148
+// 3003 rows, d = 252, f = 500, 12 experts, us, launches back to back in a graph: both forward products 45 -> 42, both
+// backward products 52 -> 47, weight gradients of two layers 108 -> 70 (with one stage requested ahead, a branch around
+// every load, strided operands transposed on their way into LDS, single tiles dealt to the XCDs in turn -> now); 32 experts of
+// 320 x 640, 4500 rows: 89 -> 85, 106 -> 90, 213 -> 139.  The matrix cores are busy half of the time there (74.5 of 148
 // million cycles of the gate and up projections), the rest is the start of the workgroups and the last round.
 #include "kernels.h"
 
@@ -185,8 +185,13 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     constexpr int BK = WT == 32 ? 32 : 64;     // reduction indices per stage: 2048 values of each operand
     constexpr int CH = BK / 16;                // 16-index chunks per stage
     // LDS rows in floats, so that the 16 x 4 values of a fragment read lie in 64 banks: K-contiguous operands keep their
-    // rows of BK indices, strided ones their rows of BM columns
-    constexpr int LD = BK + 4, LDT = BM + 16;
+    // rows of BK indices and four values of padding, strided ones their rows of BM columns, in groups of 16 that trade places
+    // from row to row.  (With 16 columns of padding instead a CU ran two or three workgroups where it now runs four: weight
+    // gradients, us: 508 experts of 528 x 576, 76 rows of two layers, added 310 -> 263, written 474 -> 408; 315 of 295 x 636, 112
+    // rows of eight 194 -> 162, 400 -> 341; 32 of 320 x 640, 4500 rows 153 -> 139; 12 of 252 x 500, 3003 rows, both backward
+    // products 51.9 -> 48.2.)
+    constexpr int LD = BK + 4, LDT = BM;
+    auto swz = [](int k) { return (BM == 64 ? k & 3 : k >> 1 & 1) * 16; };       // of a strided operand's row k
     constexpr int ABUF = ATR ? BK * LDT : BM * LD, BBUF = BTR ? BK * LDT : BM * LD;
     constexpr int NF = WT / 16;                // 16-wide fragments per wavefront and side
     static_assert(BM * BK == 8 * kThreads, "two groups of four values per thread and operand");
@@ -382,14 +387,14 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
         };
         auto put = [&](float* t, const Raw& v, bool ok, bool tr, int i) __attribute__((always_inline)) {
             const f32x4 f = {(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-            *reinterpret_cast<f32x4*>(t + (tr ? kr[i] * LDT + nq[i] : mq[i] * LD + kq[i])) =
+            *reinterpret_cast<f32x4*>(t + (tr ? kr[i] * LDT + (nq[i] ^ swz(kr[i])) : mq[i] * LD + kq[i])) =
                 ok ? f : f32x4{0.f, 0.f, 0.f, 0.f};
         };
         // operands of the four instructions of chunk c: the lane's row (or column) at indices 4 q + lg
         auto frag = [&](const float* t, bool tr, int r, int c) {
             f32x4 v;
 #pragma unroll
-            for (int q = 0; q < 4; q++) v[q] = t[tr ? (c * 16 + 4 * q + lg) * LDT + r : r * LD + c * 16 + 4 * q + lg];
+            for (int q = 0; q < 4; q++) v[q] = t[tr ? (c * 16 + 4 * q + lg) * LDT + (r ^ swz(lg)) : r * LD + c * 16 + 4 * q + lg];
             return v;
         };
 
