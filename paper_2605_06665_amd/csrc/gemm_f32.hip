@@ -113,7 +113,8 @@ __device__ __forceinline__ int tile_of_block(int total) {
 // The same for weight gradients, whose tiles are as long as their expert has rows: the list is dealt to the XCDs in turn, a row
 // of n_tiles tiles at a time, which share an operand, so that the experts with many rows, wherever they are in the pool, are
 // spread over all of them (in eight parts / dealt, us: 32 experts of 320 x 640, 4500 rows of two layers, about half of them on
-// the first six 332 / 151, on six others 239 / 170, on all alike 155 / 154; whole experts in turn 162, 221, 159).
+// the first six 332 / 151, on six others 239 / 170, on all alike 155 / 154; whole experts in turn 162, 221, 159).  Chunks of one
+// matrix, which are equally long, keep the eight parts (router backward of 90 experts, d 832, 4000 tokens 45 us, dealt 52).
 __device__ __forceinline__ int dealt_tile_of_block(int n_tiles) {
     const int slot = blockIdx.x / 8;
     return (slot / n_tiles * 8 + blockIdx.x % 8) * n_tiles + slot % n_tiles;
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     if constexpr (LAYERS) {
         if (blockIdx.x == 0 && g.sum_part != nullptr) block_sum_256(g.sum_part, g.sum_n, g.sum_out);
         const int per = g.m_tiles * g.n_tiles;
-        const int tile = dealt_tile_of_block(g.n_tiles);
+        const int tile = g.n_layers > 0 ? dealt_tile_of_block(g.n_tiles) : tile_of_block(g.E * per);
         expert = tile / per;
         if (expert >= g.E) return;
         const int r = tile % per;
