@@ -1215,7 +1215,9 @@ double row_tiles(double r, int bm) {
 // small ones two to a CU, the longest CU gets 256 columns either way, and with few rows there is little epilogue to overlap: big
 // ones then (dX of 31 experts, 1280 columns, 6 rows each, share of both backward products: 5.7 to 7.9 % longer in small
 // tiles; 29 of 1600, 44 rows 3 to 4 %; 33 of 1088, 53 rows 3.6 %; 97 of 320, 56 rows 2 %; but 30 of 1152, 61 rows 4 to 5 %
-// shorter, 23 of 1856, 64 rows 1 %).  Over 218 shapes (4 to 512 experts, d_model 64 to 1664, d_ff 64 to 4096, 1 to 37000
+// shorter, 23 of 1856, 64 rows 1 %).  Experts without rows have no tiles: with fewer picks than experts they are left out of the
+// count (both backward products of 96 experts of 1024 x 2816, 64 picks 158 us as if all had rows, now 145; 64 of 768 x 2048, 60
+// picks 89 and 78).  Over 218 shapes (4 to 512 experts, d_model 64 to 1664, d_ff 64 to 4096, 1 to 37000
 // rows per expert, even and skewed routing) both FFN entry points together are 11 % shorter than with big tiles alone, the
 // worst shape 2 % longer and the best 46 % shorter; the worst single entry point is 4 % longer.  One layer, us, big / small: down projection of 16 experts of 768 x 2048, 188 rows each (48 tiles / 192) 41 / 27,
 // dX of these 67 / 39, dH 34 / 27; but gate and up of 192 experts of 1536 x 4096, 341 rows each 1880 / 2700.
@@ -1224,9 +1226,10 @@ int tile_form(const unipool_shape& s, int N, int which, bool extra) {
 #ifdef UNIPOOL_DEBUG_SWITCHES
     if (const char* e = getenv("UNIPOOL_TILES")) return (atoi(e) >> (4 * which)) & 15;    // a digit per product
 #endif
-    const double r = (double)s.T * s.k / s.E;
+    const double S = (double)s.T * s.k;
+    const double used = s.E * -std::expm1(-S / s.E), r = S / used;         // experts with rows, as if the picks were independent
     const double mb = row_tiles(r, kBM), ms = row_tiles(r, kSmallBM);
-    const double nb = s.E * mb * cdiv(N, kBN), ns = s.E * ms * cdiv(N, kSmallBN);
+    const double nb = used * mb * cdiv(N, kBN), ns = used * ms * cdiv(N, kSmallBN);
     const int cus = num_cus();
     const double big = std::ceil(nb / cus) * (kBN + 0.4 * r / mb);
     if (nb <= cus && ns > cus && r < 60) return TILE_BIG;

@@ -113,6 +113,9 @@ def test_tile_forms_of_few_rows(U):
     assert small(230, 8, 30, 1152, 192, B.SMALL_DX)                # 61 rows, 150 or 270
     assert small(95, 2, 31, 1280, 1536, B.SMALL_GATE_UP)           # 372 large tiles: two rounds
     assert small(567, 8, 23, 192, 1856, B.SMALL_DOWN)              # 46 small tiles: one each
+    # fewer picks than experts: those without rows have no tiles
+    assert not small(16, 4, 96, 1024, 2816, B.SMALL_DX)            # 47 experts, 187 large tiles or 374 small ones
+    assert small(30, 2, 64, 768, 2048, B.SMALL_DX)                 # 39 experts, 234 small tiles: one each
 
 
 def test_weight_gradients_in_two_launches_are_long(U):
