@@ -110,14 +110,19 @@ __device__ __forceinline__ int tile_of_block(int total) {
     return slot < per_xcd ? (blockIdx.x % 8) * per_xcd + slot : total;
 }
 
-// The same for weight gradients, whose tiles are as long as their expert has rows: the list is dealt to the XCDs in turn, a row
-// of n_tiles tiles at a time, which share an operand, so that the experts with many rows, wherever they are in the pool, are
-// spread over all of them (in eight parts / dealt, us: 32 experts of 320 x 640, 4500 rows of two layers, about half of them on
+// The same where tiles differ in length: the list is dealt to the XCDs in turn, up to a row of n_tiles tiles at a time (which
+// share an operand), fewer where that gave an XCD less than four turns.  Workgroups past the list get tiles past it.
+// Weight gradients, whose tiles are as long as their expert has rows: the experts with many rows, wherever they are in the pool,
+// are spread over all XCDs (in eight parts / dealt, us: 32 experts of 320 x 640, 4500 rows of two layers, about half of them on
 // the first six 332 / 151, on six others 239 / 170, on all alike 155 / 154; whole experts in turn 162, 221, 159).  Chunks of one
 // matrix, which are equally long, keep the eight parts (router backward of 90 experts, d 832, 4000 tokens 45 us, dealt 52).
-__device__ __forceinline__ int dealt_tile_of_block(int n_tiles) {
-    const int slot = blockIdx.x / 8;
-    return (slot / n_tiles * 8 + blockIdx.x % 8) * n_tiles + slot % n_tiles;
+// Row tiles of pools beyond 64 experts, most of which have few rows: half of the rows with a fifth of the experts, both forward
+// products in eight parts / dealt 158 experts of 40 x 114 17.8 / 15.0, 458 of 44 x 77 34.4 / 29.3; even rows 90 of 128 x 256
+// 19.0 / 18.7, 400 of 64 x 128 16.6 / 17.3.  Up to 64 experts the eight parts share more in L2 (12 of 252 x 500 42.3 / 44.7; 24
+// of 256 x 512, rows by Zipf's law 66.9 / 69.7).
+__device__ __forceinline__ int dealt_tile_of_block(int total, int n_tiles) {
+    const int run = max(1, min(n_tiles, total / 32)), slot = blockIdx.x / 8;
+    return (slot / run * 8 + blockIdx.x % 8) * run + slot % run;
 }
 
 // Row tile of the row groups, BM rows a tile, that this workgroup works on with which of n_tiles column tiles.  Up to 64
@@ -165,7 +170,7 @@ __device__ __forceinline__ RowTile find_row_tile(const int32_t* offsets, int E, 
         if (w < wave) upto += wsum[w];
         total += wsum[w];
     }
-    const int tile = tile_of_block(total * n_tiles), want = tile / n_tiles;
+    const int tile = dealt_tile_of_block(total * n_tiles, n_tiles), want = tile / n_tiles;
     if (want >= total) return RowTile{0, 0, 0, 0};
     const int nth = want - (upto - t0 - t1);       // of this thread's tiles
     if (nth >= 0 && want < upto) {
@@ -213,7 +218,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(const Args g) {
     if constexpr (LAYERS) {
         if (blockIdx.x == 0 && g.sum_part != nullptr) block_sum_256(g.sum_part, g.sum_n, g.sum_out);
         const int per = g.m_tiles * g.n_tiles;
-        const int tile = g.n_layers > 0 ? dealt_tile_of_block(g.n_tiles) : tile_of_block(g.E * per);
+        const int tile = g.n_layers > 0 ? dealt_tile_of_block(g.E * per, g.n_tiles) : tile_of_block(g.E * per);
         expert = tile / per;
         if (expert >= g.E) return;
         const int r = tile % per;
@@ -510,7 +515,8 @@ hipError_t run_rows_wt(Args a, int n_cols, hipStream_t st) {
     constexpr int BM = 2 * WT;
     a.n_tiles = cdiv(n_cols, BM);
     const long long row_tiles = a.offsets ? (long long)a.M / BM + min(a.E, a.M) : cdiv(a.M, BM);
-    const long long grid = (row_tiles * a.n_tiles + 7) / 8 * 8;          // a multiple of eight, see tile_of_block
+    // a multiple of eight, and for dealt_tile_of_block room for the last round of the XCDs
+    const long long grid = ((row_tiles + (a.offsets && a.E > 64 ? 8 : 0)) * a.n_tiles + 7) / 8 * 8;
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
     gemm_f32_kernel<TA, WT, false, BTR, EPI, false><<<(unsigned)grid, kThreads, 0, st>>>(a);
     return hipGetLastError();
@@ -527,7 +533,7 @@ hipError_t run_layers_wt(Args a, int groups, hipStream_t st) {
     a.m_tiles = cdiv(a.M, 2 * WT);
     a.n_tiles = cdiv(a.N, 2 * WT);
     a.E = groups;
-    const long long grid = ((long long)groups * a.m_tiles + 7) / 8 * 8 * a.n_tiles;     // see dealt_tile_of_block
+    const long long grid = (((long long)groups * a.m_tiles + 8) * a.n_tiles + 7) / 8 * 8;      // as in run_rows_wt
     if (grid >= (1LL << 31)) return hipErrorInvalidValue;
     gemm_f32_kernel<TA, WT, true, true, kFloat, true><<<(unsigned)grid, kThreads, 0, st>>>(a);
     return hipGetLastError();
