@@ -114,7 +114,8 @@ __device__ __forceinline__ int tile_of_block(int total) {
 // share an operand), fewer where that gave an XCD less than four turns.  Workgroups past the list get tiles past it.
 // Weight gradients, whose tiles are as long as their expert has rows: the experts with many rows, wherever they are in the pool,
 // are spread over all XCDs (in eight parts / dealt, us: 32 experts of 320 x 640, 4500 rows of two layers, about half of them on
-// the first six 332 / 151, on six others 239 / 170, on all alike 155 / 154; whole experts in turn 162, 221, 159).  Chunks of one
+// the first six 332 / 151, on six others 239 / 170, on all alike 155 / 154; whole experts in turn 162, 221, 159; all of these
+// before LDS rows lost their padding, which made 151 and 154 into 137 and 139).  Chunks of one
 // matrix, which are equally long, keep the eight parts (router backward of 90 experts, d 832, 4000 tokens 45 us, dealt 52).
 // Row tiles of pools beyond 64 experts, most of which have few rows: half of the rows with a fifth of the experts, both forward
 // products in eight parts / dealt 158 experts of 40 x 114 17.8 / 15.0, 458 of 44 x 77 34.4 / 29.3; even rows 90 of 128 x 256

@@ -67,7 +67,7 @@ def test_products(E, d, f, rows, shift):
 
 def test_weight_gradients_of_skewed_pools_use_the_whole_card():
     """As many rows take about as long whether they are spread evenly or half of them are with the first six experts of 32 (4500
-    rows, 320 x 640, two layers: 155 us both; 332 for the second where the experts were cut into eight parts in order)."""
+    rows, 320 x 640, two layers: 137 and 139 us; 332 against 155 where the experts were cut into eight parts in order)."""
     import torch
     import paper_2605_06665_amd as U
     E, d, f, S, L = 32, 320, 640, 4500, 2
