@@ -314,8 +314,14 @@ __global__ __launch_bounds__(256) void permute_small_kernel(const V* __restrict_
 // 7.0 / 3.0; 4001, 2, 192, 1536 11.5 / 8.5, 7.9 / 3.5; 4096, 8, 512, 1024 23 / 17, 12.6 / 6.6.  The adds to one counter go one
 // after the other, at most one per token, which draws the line: with all tokens on one expert 3001 take 7.9 / 6.1, 6144
 // 8.9 / 10.9 (evenly spread 8.7 / 5.8); and every workgroup reads the picks: 32768 tokens, k = 2 55 / 68.
+// A wavefront copies two rows one after the other, a chunk at a time, so rows of more than 8 KiB go in three launches, whose
+// copy has a wavefront per row and four chunks in flight (192 experts, 1000 tokens, k = 1: rows of 8 KiB 9.2 / 8.6, of 12 KiB 10.0 / 10.5, 16 KiB
+// 11.5 / 13.3, 32 KiB 15.6 / 22.9; k = 8, 32 KiB 57 / 120), and so do copies of more than 256 MB, past the last-level cache,
+// which their stores do not pass through (4096 tokens, k = 8, rows of 8 KiB, 268 MB, 62 / 68, of 6 KiB, 201 MB,
+// 50 / 38).
 constexpr int kCountTokens = 16, kCountThreads = 512;
 constexpr int kCountMaxTokens = 4096;
+constexpr size_t kCountMaxRow = 8192, kCountMaxCopy = 256000000;       // bytes
 
 template <typename V, int K>
 __global__ __launch_bounds__(kCountThreads) void permute_count_kernel(
@@ -402,7 +408,8 @@ hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* 
         });
         return hipGetLastError();
     }
-    if (s.T <= kCountMaxTokens) {
+    const bool long_copy = x_perm && (row_bytes > kCountMaxRow || row_bytes * s.T * s.k > kCountMaxCopy);
+    if (s.T <= kCountMaxTokens && !long_copy) {
         const int nblocks = cdiv(s.T, kCountTokens);
         with_top_k(s.k, [&](auto kc) {
             constexpr int K = decltype(kc)::value;

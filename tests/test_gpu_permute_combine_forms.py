@@ -26,7 +26,10 @@ PERMUTES = [(257, 8, 1, 64, "bf16", False), (272, 512, 8, 128, "bf16", False), (
             (999, 90, 3, 37, "f32", False), (1001, 12, 3, 252, "f32", True), (1025, 500, 8, 64, "bf16", False),
             (4095, 192, 2, 64, "bf16", False),
             (4096, 512, 8, 64, "bf16", True), (4096, 16, 1, 64, "bf16", True), (4096, 64, 3, 5, "f32", False),
-            (4097, 64, 3, 5, "f32", False), (4097, 16, 1, 64, "bf16", True)]
+            (4097, 64, 3, 5, "f32", False), (4097, 16, 1, 64, "bf16", True),
+            # rows on both sides of 8 KiB, copies on both sides of 256 MB
+            (300, 24, 2, 4096, "bf16", False), (300, 24, 2, 4160, "bf16", False), (257, 3, 1, 2047, "f32", False),
+            (260, 9, 3, 2049, "f32", True), (3906, 64, 8, 4096, "bf16", False), (3907, 64, 8, 4096, "bf16", False)]
 
 
 @pytest.mark.parametrize("copy", [True, False])
@@ -54,6 +57,34 @@ def test_permute(T, E, k, d, dtype, skew, copy):
     if copy:
         assert torch.equal(xp[:-1], x[torch.from_numpy(slot_of_row // k).long().cuda()])
         assert bool((xp[-1] == 7.0).all())
+
+
+def test_wide_rows_are_copied_as_fast_as_short_ones():
+    """The same 262 MB as 8000 rows of 32 KiB and as 32800 rows of 8 KiB (57 and 58 us; the former 120 where a wavefront copied
+    two rows one after the other)."""
+    import torch
+    import paper_2605_06665_amd as U
+    E, k = 192, 8
+
+    def best_time(T, d):
+        sh = _shape(U, T, d, E, k, U.F32)
+        idx = _picks(np.random.default_rng(T), T, E, k, False)
+        picks, counts = (torch.from_numpy(v.astype(np.int32)).cuda() for v in (idx, np.bincount(idx.ravel(), minlength=E)))
+        x, xp = torch.randn((T, d), device="cuda"), torch.empty((T * k, d), device="cuda")
+        off, ros, sor = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E + 1, T * k, T * k))
+        ws = torch.empty(U.workspace_bytes(sh), dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(20):
+                U.permute(sh, x, picks, counts, xp, off, ros, sor, ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    assert best_time(1000, 8192) <= 1.5 * best_time(4100, 2048)
 
 
 @pytest.mark.parametrize("T,k,d,dtype", [(1, 1, 64, "bf16"), (3, 2, 512, "bf16"), (5, 3, 576, "bf16"), (2048, 8, 1088, "bf16"),
