@@ -321,7 +321,10 @@ __global__ __launch_bounds__(256) void permute_small_kernel(const V* __restrict_
 // 50 / 38).
 constexpr int kCountTokens = 16, kCountThreads = 512;
 constexpr int kCountMaxTokens = 4096;
-constexpr size_t kCountMaxRow = 8192, kCountMaxCopy = 256000000;       // bytes
+// Rows that are not a multiple of 16 bytes are copied value by value, in three launches reading x once per pick: their line is
+// 4 KiB times the picks (three launches / one, 1000 tokens, k = 1: d 1023 10.1 / 7.7, 2047 12.5 / 14 to 23, 4095 23 / 36; k = 8: d 2047
+// 45 / 32, 8191 308 / 179; 260 tokens, k = 2: d 2047 14.7 / 12.5, 8191 37 / 50; but 1000 tokens, k = 2, d 2047 17.6 / 20.3).
+constexpr size_t kCountMaxRow = 8192, kCountMaxOddRow = 4096, kCountMaxCopy = 256000000;       // bytes
 
 template <typename V, int K>
 __global__ __launch_bounds__(kCountThreads) void permute_count_kernel(
@@ -408,7 +411,8 @@ hipError_t launch_permute(const unipool_shape& s, const void* x, const int32_t* 
         });
         return hipGetLastError();
     }
-    const bool long_copy = x_perm && (row_bytes > kCountMaxRow || row_bytes * s.T * s.k > kCountMaxCopy);
+    const bool long_copy = x_perm && (row_bytes % 16 == 0 ? row_bytes > kCountMaxRow || row_bytes * s.T * s.k > kCountMaxCopy
+                                                          : row_bytes > kCountMaxOddRow * s.k);
     if (s.T <= kCountMaxTokens && !long_copy) {
         const int nblocks = cdiv(s.T, kCountTokens);
         with_top_k(s.k, [&](auto kc) {

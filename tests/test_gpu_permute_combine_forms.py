@@ -27,9 +27,9 @@ PERMUTES = [(257, 8, 1, 64, "bf16", False), (272, 512, 8, 128, "bf16", False), (
             (4095, 192, 2, 64, "bf16", False),
             (4096, 512, 8, 64, "bf16", True), (4096, 16, 1, 64, "bf16", True), (4096, 64, 3, 5, "f32", False),
             (4097, 64, 3, 5, "f32", False), (4097, 16, 1, 64, "bf16", True),
-            # rows on both sides of 8 KiB, copies on both sides of 256 MB
-            (300, 24, 2, 4096, "bf16", False), (300, 24, 2, 4160, "bf16", False), (257, 3, 1, 2047, "f32", False),
-            (260, 9, 3, 2049, "f32", True), (3906, 64, 8, 4096, "bf16", False), (3907, 64, 8, 4096, "bf16", False)]
+            # rows on both sides of 8 KiB, or of 4 KiB a pick, copies on both sides of 256 MB
+            (300, 24, 2, 4096, "bf16", False), (300, 24, 2, 4160, "bf16", False), (257, 3, 1, 1023, "f32", False),
+            (257, 3, 1, 1025, "f32", False), (260, 9, 3, 3071, "f32", True), (260, 9, 3, 3073, "f32", True), (3906, 64, 8, 4096, "bf16", False), (3907, 64, 8, 4096, "bf16", False)]
 
 
 @pytest.mark.parametrize("copy", [True, False])
